@@ -344,10 +344,6 @@ struct GWork {
     float* ritz;
     int* nsel;
     int* lneed;             // NormPre-L: 1 where ||T||_F needs the norm pass
-    // exact NormPre-L above kMaxEll active rows
-    float* gam32;           // Gamma, fp32 a_pad x a_pad
-    TriWork tw;             // eigensolver workspace (order a)
-    double* lam;            // leading ell eigenvalues
 };
 
 struct Dims {
@@ -358,6 +354,9 @@ struct Dims {
     int64_t a, b, a_pad, b_pad;
     int ell, ellp, top;
     bool xl;                // exact NormPre-L through the dense eigensolver
+    // Order of the eigenproblem of an xl matrix or a spectrum: the smaller of
+    // a and b, since Psi Psi^T and Psi^T Psi have the same nonzero eigenvalues.
+    int64_t eo, eo_pad;
 };
 
 Dims dims_of(int64_t m, int64_t n, int k, const normpre_hparams& hp) {
@@ -378,8 +377,14 @@ Dims dims_of(int64_t m, int64_t n, int k, const normpre_hparams& hp) {
     d.ellp = (int)round_up(d.ell, kEllPad);
     d.top = std::min(hp.rank, d.ell);
     d.xl = exact_large(hp, d.a);
+    d.eo = std::min(d.a, d.b);
+    d.eo_pad = std::min(d.a_pad, d.b_pad);
     return d;
 }
+
+// Whether the Gram of the shorter side is Psi Psi^T over the rows of the W
+// layout (both operands K-major) rather than Psi^T Psi over its columns.
+bool gram_of_rows(const Dims& d) { return (d.k == 0) == (d.a <= d.b); }
 
 // Newton-Schulz in Gram space (NormPre-G and the Muon reference step).  Every
 // iterate is X_k = Q_k X_0 with Q_k a polynomial in A_0 = X_0 X_0^T, and with
@@ -436,6 +441,20 @@ struct Item {
     int pool_off = 0;     // its first matrix inside the pool
     TileCfg ccfg = TileCfg::Big;   // tile of its Newton-Schulz combines
     bool gns = false;     // Newton-Schulz iterations carried in Gram space
+    int eig = -1;         // eigenproblem group of its pool (d.xl)
+    int eig_off = 0;      // its first matrix inside the group
+};
+
+// The dense eigenproblems of one order in a pool (exact NormPre-L above
+// kMaxEll active rows): reduced and solved together, since the launches of the
+// reduction are a chain whose length is the order, not the matrix count.
+struct EigGroup {
+    int64_t n = 0, npad = 0;
+    int count = 0;
+    int nvals = 0;          // leading eigenpairs wanted: min(l, n)
+    float* gam32 = nullptr; // Gram, fp32 npad x npad; then the WY factors
+    TriWork tw{};
+    double* lam = nullptr;
 };
 
 // Small matrices shared by the items of a round that have the same width:
@@ -461,6 +480,7 @@ struct Pool {
     float* eigs = nullptr;
     float* ritz = nullptr;
     int* nsel = nullptr;
+    std::vector<EigGroup> eig;
     // Ritz pairs through the dense eigensolver (l > kEigJacobiMax)
     TriWork tw{};
     double* lam = nullptr;
@@ -511,24 +531,27 @@ void carve_item(Arena& ar, Item& it, int variant, int opts) {
         w.qlen = ar.take<half_t>(count * d.a_pad * lp);
         w.flen = ar.take<half_t>(count * d.b_pad * lp);
         w.lneed = ar.take<int>(count);
-        if (d.xl) {
-            const int64_t a = d.a;
-            w.gam32 = ar.take<float>(count * d.a_pad * d.a_pad);
-            w.tw.A = ar.take<float>(count * a * a);
-            w.tw.vec = ar.take<double>(count * 4 * a);
-            w.tw.d = ar.take<double>(count * a);
-            w.tw.e = ar.take<double>(count * a);
-            w.tw.tau = ar.take<double>(count * a);
-            w.tw.lu = ar.take<double>(count * d.ell * 6 * a);
-            w.tw.y = ar.take<double>(count * d.ell * a);
-            w.lam = ar.take<double>(count * d.ell);
-        }
         if (source_x) {
             w.xs = ar.take<half_t>(count * mn);
             w.xsq = ar.take<float>(count * d.lp_);
             w.xtot = ar.take<float>(count * 2);
         }
     }
+}
+
+// Eigensolver workspace of c matrices of order n and their nv leading pairs.
+TriWork carve_tri(Arena& ar, int64_t c, int64_t n, int64_t nv) {
+    TriWork t{};
+    t.A = ar.take<float>(c * n * n);
+    t.vec = ar.take<double>(c * 4 * n);
+    t.d = ar.take<double>(c * n);
+    t.e = ar.take<double>(c * n);
+    t.tau = ar.take<double>(c * n);
+    if (nv > 0) {
+        if (tri_needs_lu((int)n)) t.lu = ar.take<double>(c * nv * 6 * n);
+        t.y = ar.take<double>(c * nv * n);
+    }
+    return t;
 }
 
 void carve_pool(Arena& ar, Pool& p, int variant) {
@@ -553,15 +576,22 @@ void carve_pool(Arena& ar, Pool& p, int variant) {
         p.nsel = ar.take<int>(c);
         if (p.ell > kEigJacobiMax) {
             const int64_t n = p.ell, top = p.top;
-            p.tw.A = ar.take<float>(c * n * n);
-            p.tw.vec = ar.take<double>(c * 4 * n);
-            p.tw.d = ar.take<double>(c * n);
-            p.tw.e = ar.take<double>(c * n);
-            p.tw.tau = ar.take<double>(c * n);
-            p.tw.lu = ar.take<double>(c * top * 6 * n);
-            p.tw.y = ar.take<double>(c * top * n);
+            p.tw = carve_tri(ar, c, n, top);
+            // The Cholesky scratch (2 l_pad^2 doubles, l_pad >= 128) is dead
+            // by the time the reflectors' WY factors are formed.
+            p.tw.wy = p.chol;
+            p.tw.stride_wy = 2 * lp * lp;
             p.lam = ar.take<double>(c * top);
             p.zbuf = ar.take<float>(c * top * n);
+        }
+        for (EigGroup& g : p.eig) {
+            g.gam32 = ar.take<float>(g.count * g.npad * g.npad);
+            g.tw = carve_tri(ar, g.count, g.n, g.nvals);
+            // Gamma is dead once symmetrized into A: npad^2 floats (npad >=
+            // 256 and >= n) hold the n / 32 WY factors of 1024 doubles.
+            g.tw.wy = reinterpret_cast<double*>(g.gam32);
+            g.tw.stride_wy = g.npad * g.npad / 2;
+            g.lam = ar.take<double>((int64_t)g.count * g.nvals);
         }
     }
 }
@@ -595,6 +625,20 @@ std::vector<Pool> make_pools(std::vector<Item>& items, int variant) {
             it.pool_off = p.count;
             p.count += it.count;
             if (it.gns) p.gns_count += it.count;
+            if (variant != NORMPRE_VARIANT_L || !it.d.xl) continue;
+            it.eig = -1;
+            for (size_t q = 0; q < p.eig.size(); ++q)
+                if (p.eig[q].n == it.d.eo) it.eig = (int)q;
+            if (it.eig < 0) {
+                EigGroup g;
+                g.n = it.d.eo;
+                g.npad = it.d.eo_pad;
+                g.nvals = (int)std::min<int64_t>(it.d.ell, it.d.eo);
+                p.eig.push_back(g);
+                it.eig = (int)p.eig.size() - 1;
+            }
+            it.eig_off = p.eig[it.eig].count;
+            p.eig[it.eig].count += it.count;
         }
     return pools;
 }
@@ -1516,51 +1560,93 @@ int sketch_power_run(const StepCtx& sc, const std::vector<const Item*>& its) {
 }
 
 // Exact NormPre-L above kMaxEll active rows (App. B, exact eigenspace
-// extraction): Gamma = Psi Psi^T of the active side (fp16 MFMA, fp32), its
-// leading ell = min(r, a) eigenvectors by the fp64 dense eigensolver, written
-// as Y^T in place of the sketch; the common tail (orthonormalization,
-// Rayleigh-Ritz, selection of lambda > 1, apply) then works on exactly the
-// modes C can come from.
-int exact_front(const StepCtx& sc, const Item& it, DebugMat* dbg) {
+// extraction): the Gram of the shorter side of Psi (fp16 MFMA, fp32), its
+// leading eigenvectors by the fp64 dense eigensolver (exact_solve), and from
+// them Y^T in place of the sketch (exact_back); the common tail
+// (orthonormalization, Rayleigh-Ritz, selection of lambda > 1, apply) then
+// works on exactly the modes C can come from.
+int exact_front(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg) {
     const Dims& d = it.d;
     const GWork& w = it.w;
-    const std::vector<int>& idx = (*sc.groups)[it.g].idx;
+    const EigGroup& eg = pl.eig[it.eig];
     const int count = it.count;
-    int rc = run_normalize(sc, d, w, idx, it.first, count, dbg);
+    int rc = run_normalize(sc, d, w, (*sc.groups)[it.g].idx, it.first, count, dbg);
     if (rc) return rc;
     const half_t* src = w.xs ? w.xs : w.psi;
-    const int64_t mn = d.mp * d.np_, ap = d.a_pad, a = d.a;
+    const int64_t mn = d.mp * d.np_, ep = eg.npad, k_len = std::max(d.a_pad, d.b_pad);
+    float* gam = eg.gam32 + it.eig_off * ep * ep;
     {
         Operand A{src, d.np_, mn}, B{src, d.np_, mn};
-        GemmShape sh{(int)ap, (int)ap, (int)d.b_pad, 1, (int)d.b_pad, 0};
+        GemmShape sh{(int)ep, (int)ep, (int)k_len, 1, (int)k_len, 0};
         EpiPartial e{};
-        e.out = w.gam32;
-        e.ld_out = ap;
+        e.out = gam;
+        e.ld_out = ep;
         e.stride_split = 0;
-        e.stride_mat = ap * ap;
-        const double flops = 2.0 * (double)ap * (double)ap * (double)d.b_pad * count;
+        e.stride_mat = ep * ep;
+        const double flops = 2.0 * (double)ep * (double)ep * (double)k_len * count;
+        // The rows of Psi (K-major) when the shorter side is W's rows.
         NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_STREAM, flops, 2.0 * (double)d.m * (double)d.n * count,
-                     [&] { return launch_gemm_gram_f32(d.k == 0 ? 0 : 2, A, B, sh, count, e, sc.s); }),
+                     [&] { return launch_gemm_gram_f32(gram_of_rows(d) ? 0 : 2, A, B, sh, count, e, sc.s); }),
                "exact gamma");
     }
     NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_EIGEN, 0.0, 0.0,
-                 [&] { return launch_gamma_sym(w.gam32, ap, ap * ap, (int)a, w.tw.A, count, sc.s); }),
+                 [&] {
+                     return launch_gamma_sym(gam, ep, ep * ep, (int)eg.n, eg.tw.A + it.eig_off * eg.n * eg.n, count,
+                                             sc.s);
+                 }),
            "exact gamma");
+    return NORMPRE_OK;
+}
+
+// Leading eigenpairs of every matrix of one order.
+int exact_solve(const StepCtx& sc, const EigGroup& eg) {
+    const int n = (int)eg.n, count = eg.count;
     // Algorithmic bytes of the reduction: step j reads and writes the
-    // (a - j - 1)^2 trailing fp32 block once.
-    const double tri_bytes = 8.0 * ((double)(a - 1) * a * (2 * a - 1) / 6.0) * count;
+    // (n - j - 1)^2 trailing fp32 block once.
+    const double tri_bytes = 8.0 * ((double)(n - 1) * n * (2.0 * n - 1) / 6.0) * count;
     NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_EIGEN, 0.0, tri_bytes,
-                 [&] { return launch_tridiagonalize(w.tw, (int)a, count, sc.s); }),
+                 [&] { return launch_tridiagonalize(eg.tw, n, count, sc.s); }),
            "tridiagonalize");
     NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_EIGEN, 0.0, 0.0,
-                 [&] { return launch_tri_eigvals(w.tw, (int)a, 0, d.ell, w.lam, d.ell, count, sc.s); }),
+                 [&] { return launch_tri_eigvals(eg.tw, n, 0, eg.nvals, eg.lam, eg.nvals, count, sc.s); }),
            "bisection");
+    NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_EIGEN, 0.0, 0.0,
+                 [&] { return launch_tri_eigvecs(eg.tw, n, eg.lam, eg.nvals, count, sc.s); }),
+           "eigenvectors");
+    return NORMPRE_OK;
+}
+
+// Y^T (l_pad x a_pad) from the eigenvectors: themselves when Gamma was of the
+// active side; Y = Psi V (the eigenvectors of Gamma up to their lengths)
+// when it was of the other, with V in two fp16 parts so that the product
+// keeps fp32 accuracy.
+int exact_back(const StepCtx& sc, const Item& it, const Pool& pl) {
+    const Dims& d = it.d;
+    const GWork& w = it.w;
+    const EigGroup& eg = pl.eig[it.eig];
     const int64_t lp = d.ellp, maxpad = d.lp_;
+    const double* y = eg.tw.y + (int64_t)it.eig_off * eg.nvals * eg.n;
+    if (d.a <= d.b) {
+        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_EIGEN, 0.0, 0.0,
+                     [&] {
+                         return launch_vec_rows(y, eg.nvals, (int)eg.n, w.v32[0], d.a_pad, (int)lp, lp * maxpad,
+                                                it.count, sc.s);
+                     }),
+               "eigenvectors");
+        return NORMPRE_OK;
+    }
     NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_EIGEN, 0.0, 0.0,
                  [&] {
-                     return launch_tri_eigvecs(w.tw, (int)a, w.lam, d.ell, w.v32[0], ap, (int)lp, lp * maxpad, count,
-                                               sc.s);
+                     return launch_vec_split(y, eg.nvals, (int)eg.n, w.v16[0], w.v16[1], d.b_pad, (int)lp,
+                                             lp * maxpad, it.count, sc.s);
                  }),
+           "eigenvectors");
+    for (int i = 0; i < 2; ++i) {
+        int rc = sketch_product(sc, d, w, it.count, w.v16[i], true, w.v32[i], nullptr, 1.f, w.xs);
+        if (rc) return rc;
+    }
+    NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_EIGEN, 0.0, 0.0,
+                 [&] { return launch_join_split(w.v32[0], w.v32[1], lp * d.a_pad, lp * maxpad, it.count, sc.s); }),
            "eigenvectors");
     return NORMPRE_OK;
 }
@@ -1676,9 +1762,15 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
 
 int run_round_l(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& pools, DebugMat* dbg) {
     for (const Item& it : items) {
-        int rc = it.d.xl ? exact_front(sc, it, dbg) : sketch_front(sc, it, dbg);
+        int rc = it.d.xl ? exact_front(sc, it, pools[it.pool], dbg) : sketch_front(sc, it, dbg);
         if (rc) return rc;
     }
+    for (const Pool& pl : pools)
+        for (const EigGroup& eg : pl.eig)
+            if (int rc = exact_solve(sc, eg)) return rc;
+    for (const Item& it : items)
+        if (it.d.xl)
+            if (int rc = exact_back(sc, it, pools[it.pool])) return rc;
     const auto runs = pool_runs(items, pools);
     for (const auto& run : runs) {
         std::vector<const Item*> sketched;
@@ -2203,8 +2295,13 @@ int normpre_spectrum(normpre_ctx* ctx, int which, int64_t rows, int64_t cols, co
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool gx = which == NORMPRE_SPECTRUM_GX;
-    const int64_t a = d.a, ap = d.a_pad;
+    // The spectrum of the shorter side's Gram: the nonzero eigenvalues are the
+    // same, and the a - b others of a longer active side are zero.
+    const int64_t eo = d.eo, ep = d.eo_pad, k_len = std::max(d.a_pad, d.b_pad);
     Item it;
+    float* gam32 = nullptr;
+    double* lam = nullptr;
+    TriWork tw{};
     it.count = 1;
     it.d = d;
     auto carve = [&](Arena& ar, float*& mcopy) {
@@ -2215,13 +2312,9 @@ int normpre_spectrum(normpre_ctx* ctx, int which, int64_t rows, int64_t cols, co
             g.xsq = ar.take<float>(d.lp_);
             g.xtot = ar.take<float>(2);
         }
-        g.gam32 = ar.take<float>(ap * ap);
-        g.tw.A = ar.take<float>(a * a);
-        g.tw.vec = ar.take<double>(4 * a);
-        g.tw.d = ar.take<double>(a);
-        g.tw.e = ar.take<double>(a);
-        g.tw.tau = ar.take<double>(a);
-        g.lam = ar.take<double>(a);
+        gam32 = ar.take<float>(ep * ep);
+        tw = carve_tri(ar, 1, eo, 0);
+        lam = ar.take<double>(eo);
         mcopy = ar.take<float>(round_up(rows * cols, 4));   // whole 16-byte blocks for the clear
         return ar.off + 256;
     };
@@ -2248,18 +2341,19 @@ int normpre_spectrum(normpre_ctx* ctx, int which, int64_t rows, int64_t cols, co
     {
         const int64_t mn = d.mp * d.np_;
         Operand A{src, d.np_, mn}, B{src, d.np_, mn};
-        GemmShape sh{(int)ap, (int)ap, (int)d.b_pad, 1, (int)d.b_pad, 0};
-        EpiPartial ep{};
-        ep.out = it.w.gam32;
-        ep.ld_out = ap;
-        ep.stride_mat = ap * ap;
-        NP_TRY(launch_gemm_gram_f32(k == 0 ? 0 : 2, A, B, sh, 1, ep, s), "spectrum gram");
+        GemmShape sh{(int)ep, (int)ep, (int)k_len, 1, (int)k_len, 0};
+        EpiPartial eg{};
+        eg.out = gam32;
+        eg.ld_out = ep;
+        eg.stride_mat = ep * ep;
+        NP_TRY(launch_gemm_gram_f32(gram_of_rows(d) ? 0 : 2, A, B, sh, 1, eg, s), "spectrum gram");
     }
-    NP_TRY(launch_gamma_sym(it.w.gam32, ap, ap * ap, (int)a, it.w.tw.A, 1, s), "spectrum gram");
-    NP_TRY(launch_tridiagonalize(it.w.tw, (int)a, 1, s), "tridiagonalize");
-    NP_TRY(launch_tri_eigvals(it.w.tw, (int)a, 0, (int)a, it.w.lam, a, 1, s), "bisection");
-    NP_TRY(hipMemcpyAsync(eigs, it.w.lam, (size_t)a * sizeof(double), hipMemcpyDeviceToHost, s), "copy eigenvalues");
+    NP_TRY(launch_gamma_sym(gam32, ep, ep * ep, (int)eo, tw.A, 1, s), "spectrum gram");
+    NP_TRY(launch_tridiagonalize(tw, (int)eo, 1, s), "tridiagonalize");
+    NP_TRY(launch_tri_eigvals(tw, (int)eo, 0, (int)eo, lam, eo, 1, s), "bisection");
+    NP_TRY(hipMemcpyAsync(eigs, lam, (size_t)eo * sizeof(double), hipMemcpyDeviceToHost, s), "copy eigenvalues");
     NP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
+    std::fill(eigs + eo, eigs + d.a, 0.0);
     ctx->last_stream = s;
     ctx->have_stream = true;
     return NORMPRE_OK;

@@ -1,17 +1,16 @@
 // Dense symmetric eigensolver on the GPU, for the interaction matrix
-// Gamma = Psi Psi^T of one active orientation (n = active rows, up to a few
+// Gamma = Psi Psi^T of one active orientation (n = its order, up to a few
 // thousand):
 //   * Householder reduction to tridiagonal form (working matrix stored in
-//     fp32, all arithmetic and the vectors in fp64): up to n = 192 one
-//     launch with the matrix in LDS; above, one reflector per step: a
-//     one-block kernel forms the reflector of column j, and one streaming
-//     pass over the trailing rows applies the previous step's rank-2 update
-//     and forms the next product p = tau A v in the same read;
+//     fp32, all arithmetic and the vectors in fp64): one launch per column
+//     down to a trailing block of 256, which one workgroup reduces with the
+//     block in registers;
 //   * eigenvalues of the tridiagonal matrix by multisection on Sturm counts
-//     (16 lanes per eigenvalue, any subset of indices);
+//     (a wave per eigenvalue, any subset of indices);
 //   * eigenvectors of the selected eigenvalues by inverse iteration with a
 //     partially pivoted tridiagonal LU, Gram-Schmidt inside clusters of
-//     close eigenvalues, and back-transformation through the reflectors.
+//     close eigenvalues, and back-transformation through the reflectors in
+//     blocks of 32 (compact WY form).
 // Used by the exact variant of NormPre-L (App. B, exact eigenspace
 // extraction: the leading eigenvectors of Gamma span the selected modes), by
 // the Rayleigh-Ritz problems of the sketch wider than the Jacobi's limit,
@@ -25,14 +24,78 @@
 namespace np {
 namespace {
 
-constexpr int kHouseThreads = 1024;
-constexpr int kRowWaves = 4;          // rows per block of the update pass
-constexpr int kVecThreads = 256;      // Gram-Schmidt / back-transformation
+constexpr int kVecThreads = 256;      // Gram-Schmidt
+
+// Sum over the wave in a fixed order by DPP (row shifts, then the two row
+// broadcasts): the total arrives in lane 63 and is read back as a scalar.
+// Six steps of two moves and an add, against six pairs of LDS permutes for
+// __shfl_xor.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_take(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Lane l's value, as a scalar.
+__device__ __forceinline__ double lane_value(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    v += dpp_take<0x111, 0xf>(v);   // row_shr:1
+    v += dpp_take<0x112, 0xf>(v);   // row_shr:2
+    v += dpp_take<0x114, 0xf>(v);   // row_shr:4
+    v += dpp_take<0x118, 0xf>(v);   // row_shr:8
+    v += dpp_take<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v += dpp_take<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return lane_value(v, 63);
+}
+
+// Exchange-and-add of two values: afterwards lanes with bit 5 (bit 4) clear
+// hold a summed over that bit, the others b.
+__device__ __forceinline__ double swap32_add(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ double swap16_add(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+// The same over lane bit 3 (row_ror:8) and bit 2 (row_half_mirror, which
+// also flips bits 0 and 1: the remaining steps sum over those).  A lane sends
+// the value its partner keeps.
+template <int CTRL>
+__device__ __forceinline__ double swap_dpp_add(double a, double b, bool upper) {
+    const double keep = upper ? b : a, send = upper ? a : b;
+    return keep + dpp_take<CTRL, 0xf>(send);
+}
+__device__ __forceinline__ double swap8_add(double a, double b, int lane) {
+    return swap_dpp_add<0x128>(a, b, lane & 8);
+}
+__device__ __forceinline__ double swap4_add(double a, double b, int lane) {
+    return swap_dpp_add<0x141>(a, b, lane & 4);
+}
+__device__ __forceinline__ double sum_quad(double v) {
+    v += dpp_take<0x4e, 0xf>(v);    // quad_perm [2,3,0,1]
+    v += dpp_take<0xb1, 0xf>(v);    // quad_perm [1,0,3,2]
     return v;
+}
+
+// Workgroup barrier that orders LDS only: __syncthreads() also waits for the
+// wave's outstanding global loads and stores.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Sum over the block in a fixed order (every thread returns the same value).
@@ -61,275 +124,637 @@ __global__ void gamma_sym_kernel(const float* g, int64_t ldg, int64_t strideg, i
     }
 }
 
-// Reflector of step j.  vec holds per matrix [v (2 ping-pong slots) | w | p],
-// n doubles each; slot j & 1 receives v_j, slot (j + 1) & 1 holds v_{j-1}.
-// With j > 0 it first completes step j - 1: w = p - (tau/2)(p^T v) v, and
-// takes column j of the current matrix as row j of A (not yet updated by
-// step j - 1) minus that step's rank-2 term.  v_j (v_j[j + 1] = 1, zero at
-// indices <= j) is also stored in row j of A for the back-transformation.
-__global__ void __launch_bounds__(kHouseThreads) tri_house_kernel(float* A, int64_t strideA, int n, int j,
-                                                                  double* vec, int64_t stride_vec, double* dd,
-                                                                  double* ee, double* tau, int64_t stride_n) {
-    __shared__ double red[kHouseThreads / 64];
-    const int z = blockIdx.x, tid = threadIdx.x;
-    float* Az = A + (int64_t)z * strideA;
-    double* V = vec + (int64_t)z * stride_vec;
-    double* vprev = V + (int64_t)((j + 1) & 1) * n;
-    double* vcur = V + (int64_t)(j & 1) * n;
-    double* W = V + 2 * (int64_t)n;
-    const double* P = V + 3 * (int64_t)n;
-    float* row = Az + (int64_t)j * n;
-    double wj = 0.0, vj = 0.0;
-    if (j > 0) {
-        const double tp = tau[(int64_t)z * stride_n + j - 1];
-        double s = 0.0;
-        for (int i = j + tid; i < n; i += kHouseThreads) s += P[i] * vprev[i];
-        s = block_sum_d<kHouseThreads>(s, red);
-        const double K = 0.5 * tp * s;
-        for (int i = j + tid; i < n; i += kHouseThreads) W[i] = P[i] - K * vprev[i];
-        __syncthreads();
-        wj = W[j];
-        vj = vprev[j];
-    }
-    auto col = [&](int i) -> double {
-        const double r = row[i];
-        return j > 0 ? r - vprev[i] * wj - W[i] * vj : r;
-    };
-    const double dj = col(j);
-    const double alpha = j + 1 < n ? col(j + 1) : 0.0;
-    double sig = 0.0;
-    for (int i = j + 2 + tid; i < n; i += kHouseThreads) {
-        const double c = col(i);
-        sig += c * c;
-    }
-    sig = block_sum_d<kHouseThreads>(sig, red);   // also orders the reads above before the writes below
-    double beta = alpha, t = 0.0, scal = 0.0;
-    if (sig > 0.0) {
-        beta = -copysign(sqrt(alpha * alpha + sig), alpha);
-        t = (beta - alpha) / beta;
-        scal = 1.0 / (alpha - beta);
-    }
-    for (int i = tid; i < n; i += kHouseThreads) {
-        const double v = i <= j ? 0.0 : (i == j + 1 ? 1.0 : col(i) * scal);
-        vcur[i] = v;
-        if (i > j) row[i] = (float)v;
-    }
-    if (tid == 0) {
-        dd[(int64_t)z * stride_n + j] = dj;
-        ee[(int64_t)z * stride_n + j] = beta;
-        tau[(int64_t)z * stride_n + j] = t;
-    }
-}
-
-// Rows i > j: A[i, k] -= v_{j-1}[i] w[k] + w[i] v_{j-1}[k] for k > j (step
-// j - 1's update, skipped for j = 0), then p[i] = tau_j sum_k A[i, k] v_j[k]
-// over the updated row.  One wave per row.
-__global__ void __launch_bounds__(kRowWaves * 64) tri_update_kernel(float* A, int64_t strideA, int n, int j,
-                                                                    double* vec, int64_t stride_vec,
-                                                                    const double* tau, int64_t stride_n) {
-    const int z = blockIdx.y, lane = threadIdx.x & 63;
-    const int i = j + 1 + blockIdx.x * kRowWaves + (threadIdx.x >> 6);
-    if (i >= n) return;
-    double* V = vec + (int64_t)z * stride_vec;
-    const double* vprev = V + (int64_t)((j + 1) & 1) * n;
-    const double* vcur = V + (int64_t)(j & 1) * n;
-    const double* W = V + 2 * (int64_t)n;
-    double* P = V + 3 * (int64_t)n;
-    float* Ar = A + (int64_t)z * strideA + (int64_t)i * n;
-    const bool upd = j > 0;
-    const double vi = upd ? vprev[i] : 0.0, wi = upd ? W[i] : 0.0;
-    double dot = 0.0;
-    for (int k = j + 1 + lane; k < n; k += 64) {
-        double a = Ar[k];
-        if (upd) {
-            a -= vi * W[k] + wi * vprev[k];
-            Ar[k] = (float)a;
-        }
-        dot += a * vcur[k];
-    }
-    dot = wave_sum_d(dot);
-    if (lane == 0) P[i] = tau[(int64_t)z * stride_n + j] * dot;
-}
-
-// Householder tridiagonalization of the trailing m x m block (m = n - j0 <=
-// kTriLdsMax) of one matrix per block, in one launch with the block in LDS:
-// per column the reflector from the current column (two block sums),
-// p = tau M v over the trailing rows (one wave per row),
-// w = p - (tau/2)(p^T v) v, and the eager rank-2 update M -= v w^T + w v^T.
-// fp32 storage with fp64 arithmetic, as in the multi-launch reduction, whose
-// outputs (d, e, tau and the reflectors in rows of A) it reproduces.  With
-// j0 > 0 the multi-launch reduction has done columns 0 .. j0 - 1 and left the
-// rank-2 update of column j0 - 1 pending (its reflector and p = tau A v in
-// `vec`): the block is loaded with that update applied.  Larger trailing
-// blocks stay with the multi-launch reduction: one CU's LDS holds neither the
-// square nor, from about m = 200 on, beats the many-CU launches with the
-// packed triangle.
-constexpr int kTriLdsMax = 192;
-constexpr int kTriThreads = 1024;
-
-__global__ void __launch_bounds__(kTriThreads) tri_small_kernel(float* A, int64_t strideA, int n, int j0,
-                                                                const double* vec, int64_t stride_vec, double* dd,
-                                                                double* ee, double* tau, int64_t stride_n) {
-    extern __shared__ float M[];
-    __shared__ double v[kTriLdsMax], w[kTriLdsMax], red[kTriThreads / 64];
-    constexpr int NW = kTriThreads / 64;
-    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = n - j0;
-    float* Ag = A + (int64_t)z * strideA;
-    if (j0 == 0) {
-        for (int q = tid; q < m * m; q += kTriThreads) M[q] = Ag[q];
-    } else {
-        const double* V = vec + (int64_t)z * stride_vec;
-        const double* vp = V + (int64_t)((j0 - 1) & 1) * n;
-        const double* P = V + 3 * (int64_t)n;
-        const double tp = tau[(int64_t)z * stride_n + j0 - 1];
-        double s = 0.0;
-        for (int i = j0 + tid; i < n; i += kTriThreads) s += P[i] * vp[i];
-        const double K = 0.5 * tp * block_sum_d<kTriThreads>(s, red);
-        for (int i = tid; i < m; i += kTriThreads) {
-            v[i] = vp[j0 + i];
-            w[i] = P[j0 + i] - K * vp[j0 + i];
-        }
-        __syncthreads();
-        for (int q = tid; q < m * m; q += kTriThreads) {
-            const int ii = q / m, kk = q - (q / m) * m;
-            M[q] = (float)((double)Ag[(int64_t)(j0 + ii) * n + j0 + kk] - v[ii] * w[kk] - w[ii] * v[kk]);
-        }
-    }
-    __syncthreads();
-    for (int jj = 0; jj < m; ++jj) {
-        const int j = j0 + jj;
-        const float* row = M + jj * m;   // column jj by symmetry
-        const double dj = row[jj];
-        const double alpha = jj + 1 < m ? (double)row[jj + 1] : 0.0;
-        double sig = 0.0;
-        for (int i = jj + 2 + tid; i < m; i += kTriThreads) {
-            const double c = row[i];
-            sig += c * c;
-        }
-        sig = block_sum_d<kTriThreads>(sig, red);
-        double beta = alpha, t = 0.0, scal = 0.0;
-        if (sig > 0.0) {
-            beta = -copysign(sqrt(alpha * alpha + sig), alpha);
-            t = (beta - alpha) / beta;
-            scal = 1.0 / (alpha - beta);
-        }
-        if (tid == 0) {
-            dd[(int64_t)z * stride_n + j] = dj;
-            ee[(int64_t)z * stride_n + j] = beta;
-            tau[(int64_t)z * stride_n + j] = t;
-        }
-        if (t == 0.0) continue;   // H_j = I (uniform across the block)
-        for (int i = jj + 1 + tid; i < m; i += kTriThreads) {
-            const double vi = i == jj + 1 ? 1.0 : (double)row[i] * scal;
-            v[i] = vi;
-            Ag[(int64_t)j * n + j0 + i] = (float)vi;
-        }
-        __syncthreads();
-        // p = t M v, rows i > jj, one wave per row.
-        for (int i = jj + 1 + wave; i < m; i += NW) {
-            const float* mi = M + i * m;
-            double dot = 0.0;
-            for (int k = jj + 1 + lane; k < m; k += 64) dot += (double)mi[k] * v[k];
-            dot = wave_sum_d(dot);
-            if (lane == 0) w[i] = t * dot;
-        }
-        __syncthreads();
-        double pv = 0.0;
-        for (int i = jj + 1 + tid; i < m; i += kTriThreads) pv += w[i] * v[i];
-        const double K = 0.5 * t * block_sum_d<kTriThreads>(pv, red);
-        for (int i = jj + 1 + tid; i < m; i += kTriThreads) w[i] -= K * v[i];
-        __syncthreads();
-        for (int i = jj + 1 + wave; i < m; i += NW) {
-            float* mi = M + i * m;
-            const double vi = v[i], wi = w[i];
-            for (int k = jj + 1 + lane; k < m; k += 64) mi[k] = (float)((double)mi[k] - vi * w[k] - wi * v[k]);
-        }
-        __syncthreads();
-    }
-}
-
-// Number of eigenvalues of the tridiagonal (d, e) below x (Sturm count of
-// the LDL^T pivots; a pivot below pivmin in magnitude is set to -pivmin).
-// e^2 / q uses the hardware reciprocal refined by two Newton steps (within an
-// ulp or two of the quotient, a relative perturbation of each pivot that the
-// backward-stable count absorbs), keeping the dependent chain per step short.
+// fp64 reciprocal and reciprocal square root: the hardware estimates refined
+// by two Newton steps, a shorter chain than the IEEE division and root.
 __device__ __forceinline__ double recip(double q) {
     double r = __builtin_amdgcn_rcp(q);
     r = fma(r, fma(-q, r, 1.0), r);
     return fma(r, fma(-q, r, 1.0), r);
 }
-
-__device__ int sturm_count(const double* __restrict__ d, const double* __restrict__ e, int n, double x,
-                           double pivmin) {
-    double q = d[0] - x;
-    if (fabs(q) < pivmin) q = -pivmin;
-    int c = q < 0.0;
-#pragma unroll 8
-    for (int i = 1; i < n; ++i) {
-        const double ei = e[i - 1];
-        q = (d[i] - x) - ei * ei * recip(q);
-        if (fabs(q) < pivmin) q = -pivmin;
-        c += q < 0.0;
-    }
-    return c;
+__device__ __forceinline__ double rsqrt_d(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
-// Multisection: kMsLanes lanes per eigenvalue, (first + t)-th largest for
-// group t.  Each round the lanes count at kMsLanes interior points of the
-// group's bracket [lo, hi] (splitting it into kMsLanes + 1 equal parts); the
-// bracket becomes the part where the count crosses the eigenvalue's index.
-// Stops at a width of 2 eps max(|lo|, |hi|) + pivmin, or when the points no
-// longer split the bracket.
-constexpr int kMsLanes = 16;
+// Reflector of a column with leading entry alpha and squared norm sig of the
+// entries below it: H = I - t v v^T, v = (1, col * scal), H col = beta e_1.
+struct Reflector {
+    double beta, t, scal;
+};
+__device__ __forceinline__ Reflector reflector(double alpha, double sig) {
+    Reflector r{alpha, 0.0, 0.0};
+    if (sig > 0.0) {
+        const double q = fma(alpha, alpha, sig), rn = rsqrt_d(q);
+        // Squares too small to carry a full reciprocal root (entries below
+        // 1e-150): no reflection, a change far below the matrix's rounding.
+        if (q > 1e-300) {
+            r.beta = -copysign(q * rn, alpha);
+            r.t = fma(fabs(alpha), rn, 1.0);        // (beta - alpha) / beta
+            r.scal = recip(alpha - r.beta);
+        }
+    }
+    return r;
+}
 
-__global__ void __launch_bounds__(64) tri_bisect_kernel(const double* dd, const double* ee, int64_t stride_n, int n,
-                                                        int first, int nvals, double* out, int64_t stride_out) {
-    const int z = blockIdx.y, lane = threadIdx.x, grp = lane / kMsLanes, sub = lane % kMsLanes;
-    const int t = blockIdx.x * (64 / kMsLanes) + grp;
+// Column j of the reduction in one launch.  vec holds per matrix
+// [v (2 ping-pong slots) | p (2 slots)], n doubles each: slot j & 1 of v and p
+// belongs to step j.
+// Every block forms the same reflector v_j from row j of A (rows are only
+// updated through step j - 2, so step j - 1's rank-2 term v w^T + w v^T,
+// w = p - (tau/2)(p^T v) v, is subtracted on the fly), then updates its own
+// rows i > j with step j - 1's term and forms p_j[i] = tau_j A(i, :) v_j from
+// the updated row.  The forming is O(n) and repeated per block, which costs
+// less than a launch of its own (a one-block kernel for it and a second
+// launch took 6.4 of the 21 us per column of an order-2048 matrix).
+// A thread owns the columns c0 + tid + NT u of every row of its block, so the
+// vectors stay in its registers for all of them, and the first RB rows are
+// requested before the reflector is formed.  Row i always belongs to block
+// i mod nb, nb a multiple of 8: with the round-robin dispatch over the 8 XCDs
+// a row meets the same L2 in every launch (16 MB, order 2048, fit the eight
+// L2s).  Bound by the latency of one launch (load, two block sums, row pass,
+// store) down to about order 1000 and by the read and write of the trailing
+// rows above it: order 2048, 9.2 us per column while 1024 or more are left, 7.1
+// and 5.3 us for the next 512 and 256 (14.4 ms in all, 38.5 ms before).
+// Block 0 keeps v_j, and writes v_{j-1} into row j - 1 of A for the
+// back-transformation (no block reads that row any more).
+template <int NT, int U, int RB>
+__global__ void __launch_bounds__(NT) tri_step_kernel(float* A, int64_t strideA, int n, int j, int c0, double* vec,
+                                                      int64_t stride_vec, double* dd, double* ee, double* tau,
+                                                      int64_t stride_n) {
+    constexpr int NW = NT / 64;
+    __shared__ double red1[NW], red2[NW], redp[2][NW][8];
+    static_assert(RB == 8 || RB == 4 || RB == 2, "rows per pass");
+    const int z = blockIdx.y, nb = gridDim.x, x = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool first = j == 0;
+    float* Az = A + (int64_t)z * strideA;
+    double* V = vec + (int64_t)z * stride_vec;
+    const double* __restrict__ vprev = V + (int64_t)((j + 1) & 1) * n;
+    double* vcur = V + (int64_t)(j & 1) * n;
+    const double* __restrict__ pprev = V + (int64_t)(2 + ((j + 1) & 1)) * n;
+    double* pcur = V + (int64_t)(2 + (j & 1)) * n;
+    const float* row = Az + (int64_t)j * n;
+    const int i0 = j + 1 + (x + nb - (j + 1) % nb) % nb;   // first row > j of this block
+    float tile[RB][U];
+    double arow[U], vp[U], w[U], v[U];
+    auto load_tile = [&](int i) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int ir = i + r * nb;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = c0 + tid + NT * u;
+                tile[r][u] = ir < n && k > j && k < n ? Az[(int64_t)ir * n + k] : 0.f;
+            }
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = c0 + tid + NT * u;
+        const bool in = k >= j && k < n;
+        arow[u] = in ? (double)row[k] : 0.0;
+        vp[u] = in && !first ? vprev[k] : 0.0;
+        w[u] = in && !first ? pprev[k] : 0.0;       // p_{j-1} for now
+    }
+    double djj = row[j], alpha = row[j + 1];
+    const double pj = first ? 0.0 : pprev[j], pj1 = first ? 0.0 : pprev[j + 1], vj1 = first ? 0.0 : vprev[j + 1];
+    const double tp = first ? 0.0 : tau[(int64_t)z * stride_n + j - 1];
+    load_tile(i0);
+    // v_{j-1} and p_{j-1} of the pass's rows, row r in lane r.
+    double vl = 0.0, pl = 0.0;
+    auto load_scalars = [&](int i) {
+        const int ir = i + (lane % RB) * nb;
+        vl = !first && ir < n ? vprev[ir] : 0.0;
+        pl = !first && ir < n ? pprev[ir] : 0.0;
+    };
+    load_scalars(i0);
+    double K = 0.0;
+    if (!first) {
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += w[u] * vp[u];
+        s = wave_sum_d(s);
+        if (lane == 0) red1[wave] = s;
+        lds_barrier();
+        s = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) s += red1[q];
+        K = 0.5 * tp * s;
+        const double wj = pj - K;                   // v_{j-1}[j] = 1
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            w[u] -= K * vp[u];
+            arow[u] -= vp[u] * wj + w[u];
+        }
+        djj -= 2.0 * wj;
+        alpha -= vj1 * wj + (pj1 - K * vj1);
+    }
+    double sig = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (c0 + tid + NT * u >= j + 2) sig += arow[u] * arow[u];
+    sig = wave_sum_d(sig);
+    if (lane == 0) red2[wave] = sig;
+    lds_barrier();
+    sig = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) sig += red2[q];
+    const Reflector h = reflector(alpha, sig);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int k = c0 + tid + NT * u;
+        v[u] = k <= j ? 0.0 : (k == j + 1 ? 1.0 : arow[u] * h.scal);
+    }
+    if (x == 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = c0 + tid + NT * u;
+            if (k < n) {
+                vcur[k] = v[u];
+                if (!first && k >= j) Az[(int64_t)(j - 1) * n + k] = (float)vp[u];
+            }
+        }
+        if (tid == 0) {
+            dd[(int64_t)z * stride_n + j] = djj;
+            ee[(int64_t)z * stride_n + j] = h.beta;
+            tau[(int64_t)z * stride_n + j] = h.t;
+        }
+    }
+    int par = 0;
+    for (int i = i0; i < n; i += RB * nb, par ^= 1) {
+        double dot[8];
+        const double wl = pl - K * vl;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) dot[r] = 0.0;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int ir = i + r * nb;
+            if (ir >= n) break;
+            const double vi = lane_value(vl, r), wi = lane_value(wl, r);
+            float* Ar = Az + (int64_t)ir * n;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = c0 + tid + NT * u;
+                const double a = (double)tile[r][u] - (vi * w[u] + wi * vp[u]);
+                if (!first && k > j && k < n) Ar[k] = (float)a;
+                dot[r] += a * v[u];
+            }
+        }
+        if (i + RB * nb < n) {
+            load_tile(i + RB * nb);
+            load_scalars(i + RB * nb);
+        }
+        // Eight dots over 64 lanes: each exchange halves the values a lane
+        // carries, lane bits 5, 4, 3 ending up as the row.
+        double q[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) q[r] = swap32_add(dot[r], dot[r + 4]);
+        q[0] = swap16_add(q[0], q[2]);
+        q[1] = swap16_add(q[1], q[3]);
+        double d = swap8_add(q[0], q[1], lane);
+        d += dpp_take<0x141, 0xf>(d);
+        d = sum_quad(d);
+        if ((lane & 7) == 0) redp[par][wave][((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1)] = d;
+        lds_barrier();
+        if (tid < RB) {
+            double s = 0.0;
+#pragma unroll
+            for (int q2 = 0; q2 < NW; ++q2) s += redp[par][q2][tid];
+            const int ir = i + tid * nb;
+            if (ir < n) pcur[ir] = h.t * s;
+        }
+    }
+}
+
+// Householder tridiagonalization of the trailing m x m block (m = n - j0 <=
+// kTriRegMax) of one matrix per workgroup, the block in registers: thread
+// (wave w, lane) holds the rows 32 s + 2 w + (lane >> 5) and the columns
+// 32 c + (lane & 31), s, c < 8, in fp32 (all arithmetic fp64).  Per column: the
+// wave that owns row jj (= column jj) forms the reflector from its own
+// registers; p = tau M v as eight dots per thread, summed over the 32 column
+// lanes by halving exchanges; w = p - (tau/2)(p^T v) v; then the rank-2 update
+// in registers.  Two barriers per column (v and p alternate between two LDS
+// buffers).  The column loop is unrolled over the 32-row slots, so finished
+// rows and columns drop out at compile time.  2.4 us per column, fp64 issue and
+// the chain of the reflector about equal (with the block in LDS, up to 192
+// columns, the same reduction took 8.4 us per column).
+// With j0 > 0 the per-column launches have done columns 0 .. j0 - 1 and left
+// the rank-2 update of column j0 - 1 pending (its reflector and p = tau A v in
+// `vec`): the block is loaded with that update applied.
+constexpr int kTriRegMax = 256;
+constexpr int kTriThreads = 1024;
+
+struct TriRegShared {
+    double v[2][kTriRegMax], p[2][kTriRegMax], t[2];
+};
+
+// The columns 32 S0 .. 32 S0 + 31 of the block; dd, ee, tau and Ag (the block in
+// A, row stride n) start at the block's first column.
+template <int S0>
+__device__ __forceinline__ void tri_reg_cols(float (&M)[8][8], TriRegShared& sh, int& par, int m, float* Ag, int n,
+                                             double* dd, double* ee, double* tau) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, cl = lane & 31;
+    for (int jr = 0; jr < 32; ++jr, par ^= 1) {
+        const int jj = 32 * S0 + jr;
+        if (jj >= m) break;
+        if (wave == jr >> 1) {
+            // Row jj sits in one half of this wave; both halves get it.
+            double x[8], sig = 0.0;
+#pragma unroll
+            for (int c = S0; c < 8; ++c) {
+                x[c] = __shfl(M[S0][c], ((jr & 1) << 5) | cl, 64);
+                if (32 * c + cl >= jj + 2) sig += x[c] * x[c];
+            }
+            sig = wave_sum_d(half ? 0.0 : sig);       // counted once
+            const double dj = lane_value(x[S0], jr);
+            const double alpha = jr < 31 ? lane_value(x[S0], jr + 1) : S0 < 7 ? lane_value(x[S0 < 7 ? S0 + 1 : 7], 0) : 0.0;
+            const Reflector h = reflector(alpha, sig);
+#pragma unroll
+            for (int c = S0; c < 8; ++c) {
+                const int k = 32 * c + cl;
+                const double vk = k <= jj ? 0.0 : (k == jj + 1 ? 1.0 : x[c] * h.scal);
+                if (half == 0) {
+                    sh.v[par][k] = vk;
+                    if (k > jj && k < m) Ag[(int64_t)jj * n + k] = (float)vk;
+                }
+            }
+            if (lane == 0) {
+                sh.t[par] = h.t;
+                dd[jj] = dj;
+                ee[jj] = h.beta;
+                tau[jj] = h.t;
+            }
+        }
+        lds_barrier();
+        const double t = sh.t[par];
+        if (t == 0.0) continue;   // H = I (uniform across the block)
+        {
+            double vc[8], dot[8];
+#pragma unroll
+            for (int c = S0; c < 8; ++c) vc[c] = sh.v[par][32 * c + cl];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                dot[s] = 0.0;
+                if (s >= S0)
+#pragma unroll
+                    for (int c = S0; c < 8; ++c) dot[s] += (double)M[s][c] * vc[c];
+                __builtin_amdgcn_sched_barrier(0);      // register pressure
+            }
+            double q0 = swap16_add(dot[0], dot[4]), q1 = swap16_add(dot[1], dot[5]);
+            double q2 = swap16_add(dot[2], dot[6]), q3 = swap16_add(dot[3], dot[7]);
+            q0 = swap8_add(q0, q2, lane);
+            q1 = swap8_add(q1, q3, lane);
+            const double d = sum_quad(swap4_add(q0, q1, lane));
+            const int s = ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
+            const int i = 32 * s + 2 * wave + half;
+            if ((lane & 3) == 0) sh.p[par][i] = i > jj ? t * d : 0.0;
+        }
+        // The fp64 copies of M are made anew below: kept across the barrier
+        // (the compiler's choice) they would not fit the registers.
+#pragma unroll
+        for (int s = S0; s < 8; ++s)
+#pragma unroll
+            for (int c = S0; c < 8; ++c) asm volatile("" : "+v"(M[s][c]));
+        lds_barrier();
+        double vc[8], wc[8], pv = 0.0;
+#pragma unroll
+        for (int c = S0; c < 8; ++c) {
+            vc[c] = sh.v[par][32 * c + cl];
+            wc[c] = sh.p[par][32 * c + cl];
+            pv += wc[c] * vc[c];
+        }
+        if (half) pv = 0.0;
+        const double K = 0.5 * t * wave_sum_d(pv);
+#pragma unroll
+        for (int c = S0; c < 8; ++c) wc[c] -= K * vc[c];
+#pragma unroll
+        for (int s = S0; s < 8; ++s) {
+            const int i = 32 * s + 2 * wave + half;
+            const double vi = sh.v[par][i], wi = sh.p[par][i] - K * vi;
+#pragma unroll
+            for (int c = S0; c < 8; ++c) M[s][c] = (float)((double)M[s][c] - vi * wc[c] - wi * vc[c]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kTriThreads) tri_reg_kernel(float* A, int64_t strideA, int n, int j0,
+                                                              const double* vec, int64_t stride_vec, double* dd,
+                                                              double* ee, double* tau, int64_t stride_n) {
+    __shared__ TriRegShared sh;
+    __shared__ double red[kTriThreads / 64];
+    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int half = lane >> 5, cl = lane & 31;
+    const int m = n - j0;
+    float* Ag = A + (int64_t)z * strideA;
+    float M[8][8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int i = 32 * s + 2 * wave + half, k = 32 * c + cl;
+            M[s][c] = i < m && k < m ? Ag[(int64_t)(j0 + i) * n + j0 + k] : 0.f;
+        }
+    if (j0 > 0) {
+        const double* V = vec + (int64_t)z * stride_vec;
+        const double* vp = V + (int64_t)((j0 - 1) & 1) * n;
+        const double* P = V + (int64_t)(2 + ((j0 - 1) & 1)) * n;
+        const double tp = tau[(int64_t)z * stride_n + j0 - 1];
+        double vt = 0.0, pt = 0.0;
+        if (tid < m) {
+            vt = vp[j0 + tid];
+            pt = P[j0 + tid];
+            Ag[(int64_t)(j0 - 1) * n + j0 + tid] = (float)vt;
+        }
+        const double K = 0.5 * tp * block_sum_d<kTriThreads>(vt * pt, red);
+        if (tid < kTriRegMax) {
+            sh.v[0][tid] = vt;
+            sh.p[0][tid] = pt - K * vt;
+        }
+        __syncthreads();
+        double vc[8], wc[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            vc[c] = sh.v[0][32 * c + cl];
+            wc[c] = sh.p[0][32 * c + cl];
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const double vi = sh.v[0][32 * s + 2 * wave + half], wi = sh.p[0][32 * s + 2 * wave + half];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) M[s][c] = (float)((double)M[s][c] - vi * wc[c] - wi * vc[c]);
+        }
+        __syncthreads();
+    }
+    int par = 0;
+    float* Ab = Ag + (int64_t)j0 * n + j0;
+    double* db = dd + (int64_t)z * stride_n + j0;
+    double* eb = ee + (int64_t)z * stride_n + j0;
+    double* ub = tau + (int64_t)z * stride_n + j0;
+    tri_reg_cols<0>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<1>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<2>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<3>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<4>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<5>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<6>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<7>(M, sh, par, m, Ab, n, db, eb, ub);
+}
+
+// Eigenvalues by multisection, one wave per eigenvalue ((first + t)-th largest
+// for wave t): each round the 64 lanes count the eigenvalues below 64 interior
+// points of the bracket, which shrinks 65x.  The count is the number of sign
+// changes of the leading principal minors of T - x I,
+//   p_{i+1} = (d_i - x) p_i - e_{i-1}^2 p_{i-1},
+// whose dependent chain is one FMA per step (the LDL^T pivots' form needs a
+// reciprocal); the pair is rescaled by a power of two every kSturmRun steps.
+// T is scaled by a power of two to norm at most 1, and every e^2 is raised to at
+// least 2^-200 (a perturbation of at most 2^-99, far below the rounding of T),
+// so neither overflow nor a vanishing pair can occur between rescalings.  The
+// scaled (d, e^2) pairs are staged in LDS once per block.  Stops at a width of
+// 2 eps max(|lo|, |hi|) + 2^-70 (of the scaled T).  All 2048
+// eigenvalues of order 2048 take 0.75 ms (16 lanes per eigenvalue and pivots
+// with a reciprocal: 1.89 ms).
+constexpr int kBisectWaves = 4;
+constexpr int kSturmRun = 8;
+
+__global__ void __launch_bounds__(64 * kBisectWaves) tri_bisect_kernel(const double* dd, const double* ee,
+                                                                       int64_t stride_n, int n, int first, int nvals,
+                                                                       double* out, int64_t stride_out) {
+    extern __shared__ double2 de[];     // (d_i, e_{i-1}^2), scaled; padded to a multiple of kSturmRun
+    __shared__ double rlo[kBisectWaves], rhi[kBisectWaves];
+    const int z = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const double* d = dd + (int64_t)z * stride_n;
     const double* e = ee + (int64_t)z * stride_n;
-    // Gershgorin interval, the wave's lanes splitting the rows.
-    double lo = DBL_MAX, hi = -DBL_MAX, emax = 0.0;
-    for (int i = lane; i < n; i += 64) {
+    // Gershgorin interval.
+    double lo = DBL_MAX, hi = -DBL_MAX;
+    for (int i = tid; i < n; i += 64 * kBisectWaves) {
         const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0);
         lo = fmin(lo, d[i] - r);
         hi = fmax(hi, d[i] + r);
-        if (i + 1 < n) emax = fmax(emax, e[i] * e[i]);
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         lo = fmin(lo, __shfl_xor(lo, o, 64));
         hi = fmax(hi, __shfl_xor(hi, o, 64));
-        emax = fmax(emax, __shfl_xor(emax, o, 64));
     }
-    const double pivmin = DBL_MIN * fmax(1.0, emax);
+    if (lane == 0) {
+        rlo[wave] = lo;
+        rhi[wave] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kBisectWaves; ++q) {
+        lo = fmin(lo, rlo[q]);
+        hi = fmax(hi, rhi[q]);
+    }
     const double span = fmax(fabs(lo), fabs(hi));
-    lo -= 2.0 * DBL_EPSILON * span + pivmin;
-    hi += 2.0 * DBL_EPSILON * span + pivmin;
+    const int t = blockIdx.x * kBisectWaves + wave;
+    if (!(span > 0.0)) {                // T = 0 (or not a number: the bound says so)
+        if (t < nvals && lane == 0) out[(int64_t)z * stride_out + t] = span;
+        return;
+    }
+    int ex;
+    (void)frexp(span, &ex);             // span = f 2^ex, f in [1/2, 1)
+    const int np8 = (n + kSturmRun - 1) / kSturmRun * kSturmRun;
+    for (int i = tid; i < np8; i += 64 * kBisectWaves) {
+        const double es = i > 0 && i < n ? ldexp(e[i - 1], -ex) : 0.0;
+        // Past the end: d = 4 > x and no coupling, which adds no sign change.
+        de[i] = make_double2(i < n ? ldexp(d[i], -ex) : 4.0, i < n ? fmax(es * es, 0x1p-200) : 0.0);
+    }
+    __syncthreads();
     if (t >= nvals) return;
+    lo = ldexp(lo, -ex) - 2.0 * DBL_EPSILON;
+    hi = ldexp(hi, -ex) + 2.0 * DBL_EPSILON;
     // smallest x with count(x) > idx, idx counted from the bottom
     const int idx = n - 1 - (first + t);
-    constexpr double kInv = 1.0 / (kMsLanes + 1);
     for (int it = 0; it < 100; ++it) {
         const double w = hi - lo;
-        if (w <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
-        auto pt = [&](int k) { return lo + (w * (double)k) * kInv; };
-        const bool above = sturm_count(d, e, n, pt(sub + 1), pivmin) > idx;
-        const unsigned mask =
-            (unsigned)(__ballot(above) >> (grp * kMsLanes)) & ((1u << kMsLanes) - 1u);
-        // First point whose count exceeds idx (kMsLanes: none does).
-        const int s = mask ? __builtin_ctz(mask) : kMsLanes;
+        if (w <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 0x1p-70) break;
+        auto pt = [&](int k) { return lo + (w * (double)k) * (1.0 / 65.0); };
+        const double x = pt(lane + 1);
+        double p = 1.0, pp = 0.0;
+        int changes = 0;
+        for (int i = 0; i < np8; i += kSturmRun) {
+            double2 v[kSturmRun];
+#pragma unroll
+            for (int q = 0; q < kSturmRun; ++q) v[q] = de[i + q];
+#pragma unroll
+            for (int q = 0; q < kSturmRun; ++q) {
+                const double pn = fma(v[q].x - x, p, -v[q].y * pp);
+                changes += (unsigned)((__double2hiint(pn) ^ __double2hiint(p))) >> 31;
+                pp = p;
+                p = pn;
+            }
+            const int sc = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));
+            p = ldexp(p, sc);
+            pp = ldexp(pp, sc);
+        }
+        const unsigned long long mask = __ballot(changes > idx);
+        // First point whose count exceeds idx (64: none does).
+        const int s = mask ? __builtin_ctzll(mask) : 64;
         const double nlo = s > 0 ? pt(s) : lo;
-        const double nhi = s < kMsLanes ? pt(s + 1) : hi;
+        const double nhi = s < 64 ? pt(s + 1) : hi;
         if (!(nlo > lo) && !(nhi < hi)) break;
         lo = nlo;
         hi = nhi;
     }
-    if (sub == 0) out[(int64_t)z * stride_out + t] = 0.5 * (lo + hi);
+    if (lane == 0) out[(int64_t)z * stride_out + t] = ldexp(0.5 * (lo + hi), ex);
 }
 
-// Inverse iteration, one thread per eigenvalue k of matrix z: partially
+// Inverse iteration with the factors in LDS, for orders up to kInvLdsMax: one
+// wave per block, `vpb` eigenvalues of one matrix in its first lanes.  The same
+// partially pivoted LU of T - lambda_k I, start vector and solves as
+// tri_inverse_kernel below; the factorization is repeated by each launch (it
+// costs about one solve) instead of being kept in memory.  A step's chain is a
+// few fp64 operations and its operands come from LDS a run of steps ahead,
+// where the global-memory form waits on L2 at every eight steps: 32 vectors of
+// four matrices of order 768 take 0.47 ms for both launches, 256 vectors of
+// order 264 0.18 ms (0.72 ms).  The order limit is the 160 KB of LDS.
+constexpr int kInvLdsMax = 2800;
+constexpr int kInvRun = 8;
+inline int64_t inv_lds_bytes(int n, int vpb) { return (int64_t)n * (16 + 41 * (int64_t)vpb); }
+
+__global__ void __launch_bounds__(64) tri_inverse_lds_kernel(const double* dd, const double* ee, int64_t stride_n,
+                                                             int n, const double* lam, int64_t stride_lam, int nvals,
+                                                             double* y, int solves, int init, int vpb) {
+    extern __shared__ double sh[];
+    const int z = blockIdx.y, lane = threadIdx.x, k0 = blockIdx.x * vpb;
+    const int nk = min(vpb, nvals - k0);            // eigenvalues of this block
+        double2* de = reinterpret_cast<double2*>(sh);   // (d_i, e_i)
+    double* base = sh + 2 * n;
+    double* dl = base + lane;
+    double* ig = base + (int64_t)n * vpb + lane;
+    double* du = base + 2 * (int64_t)n * vpb + lane;
+    double* du2 = base + 3 * (int64_t)n * vpb + lane;
+    double* yw = base + 4 * (int64_t)n * vpb + lane;
+    unsigned char* pv = reinterpret_cast<unsigned char*>(base + 5 * (int64_t)n * vpb) + lane;
+    const double* d0 = dd + (int64_t)z * stride_n;
+    const double* e0 = ee + (int64_t)z * stride_n;
+    double* yz = y + ((int64_t)z * nvals + k0) * (int64_t)n;
+    double tn = 0.0;
+    for (int i = lane; i < n; i += 64) {
+        const double di = d0[i], ei = i + 1 < n ? e0[i] : 0.0, em = i > 0 ? e0[i - 1] : 0.0;
+        de[i] = make_double2(di, ei);
+        tn = fmax(tn, fabs(di) + fabs(ei) + fabs(em));
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) tn = fmax(tn, __shfl_xor(tn, o, 64));
+    if (!init)
+        for (int k = 0; k < nk; ++k)
+            for (int i = lane; i < n; i += 64) yw[(int64_t)i * vpb + k - lane] = yz[(int64_t)k * n + i];
+    __syncthreads();
+    double scale = 1.0;
+    if (lane < nk) {
+        const int k = k0 + lane;
+        const double lk = lam[(int64_t)z * stride_lam + k];
+        // Pivot floor eps ||T||; the bound keeps its reciprocal finite for T = 0.
+        const double floor_piv = fmax(tn * DBL_EPSILON, 0x1p-900);
+        auto floored = [&](double g) { return fabs(g) < floor_piv ? (g < 0.0 ? -floor_piv : floor_piv) : g; };
+        // Start vector: a fixed pseudo-random sequence in [-1, 1], distinct per k.
+        uint32_t h = 0x9e3779b9u * (uint32_t)(k + 1);
+        auto draw = [&]() {
+            h ^= h << 13; h ^= h >> 17; h ^= h << 5;
+            return ((double)(h >> 8) * (1.0 / 8388608.0)) - 1.0;
+        };
+        // Factorization and the first solve's forward sweep in one pass.
+        // g, u: the current diagonal and superdiagonal entries of row i (row
+        // i + 1 of the matrix is still untouched when step i starts); c: the
+        // running entry of P L solve.
+        double g = de[0].x - lk, u = de[0].y, c = init ? draw() : yw[0];
+        auto lu_step = [&](int i, double l, double dn, double un, double nx) {
+            const int o = i * vpb;
+            const double gn = dn - lk;
+            const bool keep = fabs(g) >= fabs(l);
+            const double r = recip(floored(keep ? g : l));
+            const double f = (keep ? l : g) * r, m = keep ? u : gn;
+            dl[o] = f;
+            ig[o] = r;
+            du[o] = m;
+            du2[o] = keep ? 0.0 : un;
+            pv[o] = !keep;
+            g = (keep ? gn : u) - f * m;
+            u = keep ? un : -f * un;
+            const double a = keep ? c : nx;
+            yw[o] = a;
+            c = (keep ? nx : c) - f * a;
+        };
+        int i0 = 0;
+        for (; i0 + kInvRun < n; i0 += kInvRun) {
+            double2 w[kInvRun + 1];
+            double nx[kInvRun];
+#pragma unroll
+            for (int q = 0; q <= kInvRun; ++q) w[q] = de[i0 + q];
+#pragma unroll
+            for (int q = 0; q < kInvRun; ++q) nx[q] = init ? draw() : yw[(i0 + q + 1) * vpb];
+#pragma unroll
+            for (int q = 0; q < kInvRun; ++q) lu_step(i0 + q, w[q].y, w[q + 1].x, w[q + 1].y, nx[q]);
+        }
+        for (; i0 + 1 < n; ++i0)
+            lu_step(i0, de[i0].y, de[i0 + 1].x, de[i0 + 1].y, init ? draw() : yw[(i0 + 1) * vpb]);
+        ig[(n - 1) * vpb] = recip(floored(g));
+        for (int sv = 0; sv < solves; ++sv) {
+            if (sv > 0) {
+                // Forward: P L, the running entry c = y[i] in a register.
+                c = yw[0] * scale;
+                auto fwd = [&](int i, double nx, double f, bool swap) {
+                    const double a = swap ? nx : c;
+                    yw[i * vpb] = a;
+                    c = (swap ? c : nx) - f * a;
+                };
+                i0 = 0;
+                for (; i0 + kInvRun < n; i0 += kInvRun) {
+                    double nx[kInvRun], fl[kInvRun];
+                    int pf[kInvRun];
+#pragma unroll
+                    for (int q = 0; q < kInvRun; ++q) {
+                        const int o = (i0 + q) * vpb;
+                        nx[q] = yw[o + vpb] * scale;
+                        fl[q] = dl[o];
+                        pf[q] = pv[o];
+                    }
+#pragma unroll
+                    for (int q = 0; q < kInvRun; ++q) fwd(i0 + q, nx[q], fl[q], pf[q]);
+                }
+                for (; i0 + 1 < n; ++i0) fwd(i0, yw[(i0 + 1) * vpb] * scale, dl[i0 * vpb], pv[i0 * vpb]);
+            }
+            // Backward: U with two superdiagonals, y[i + 1] and y[i + 2] carried.
+            double y1 = c * ig[(n - 1) * vpb], y2 = 0.0, mx = fabs(y1);
+            yw[(n - 1) * vpb] = y1;
+            auto bwd = [&](int i, double yv, double uu, double u2, double gi) {
+                const double y0 = (yv - u2 * y2 - uu * y1) * gi;
+                yw[i * vpb] = y0;
+                mx = fmax(mx, fabs(y0));
+                y2 = y1;
+                y1 = y0;
+            };
+            for (i0 = n - 2; i0 >= kInvRun - 1; i0 -= kInvRun) {
+                double yv[kInvRun], uu[kInvRun], u2[kInvRun], gi[kInvRun];
+#pragma unroll
+                for (int q = 0; q < kInvRun; ++q) {
+                    const int o = (i0 - q) * vpb;
+                    yv[q] = yw[o];
+                    uu[q] = du[o];
+                    u2[q] = du2[o];
+                    gi[q] = ig[o];
+                }
+#pragma unroll
+                for (int q = 0; q < kInvRun; ++q) bwd(i0 - q, yv[q], uu[q], u2[q], gi[q]);
+            }
+            for (; i0 >= 0; --i0) bwd(i0, yw[i0 * vpb], du[i0 * vpb], du2[i0 * vpb], ig[i0 * vpb]);
+            scale = mx > 0.0 ? recip(mx) : 1.0;
+        }
+    }
+    __syncthreads();
+    for (int k = 0; k < nk; ++k) {
+        const double sk = lane_value(scale, k);
+        for (int i = lane; i < n; i += 64) yz[(int64_t)k * n + i] = yw[(int64_t)i * vpb + k - lane] * sk;
+    }
+}
+
+// Inverse iteration for orders above kInvLdsMax, one thread per eigenvalue k of
+// matrix z: partially
 // pivoted LU of T - lambda_k I, then `solves` solves of y (start: a fixed
 // pseudo-random vector when init is set, else y as left by the previous
 // launch), each followed by scaling to max |y_i| = 1.  The factors
@@ -497,35 +922,169 @@ __global__ void __launch_bounds__(kVecThreads) vec_cluster_mgs_kernel(const doub
     }
 }
 
-// u = H_0 H_1 ... H_{n-1} y_k (reflector j in row j of A, v_j[j + 1] = 1),
-// in place in y; then written as row k of the fp32 output (ld, zero padded
-// to ld), rows nvals .. rows_out - 1 zero.
-__global__ void __launch_bounds__(kVecThreads) tri_backtransform_kernel(const float* A, int64_t strideA, int n,
-                                                                       const double* tau, int64_t stride_n,
-                                                                       double* y, int nvals, float* out,
-                                                                       int64_t ld_out, int64_t stride_out) {
-    __shared__ double red[kVecThreads / 64];
-    const int z = blockIdx.y, k = blockIdx.x, tid = threadIdx.x;
-    float* o = out + (int64_t)z * stride_out + (int64_t)k * ld_out;
-    if (k >= nvals) {
-        for (int64_t i = tid; i < ld_out; i += kVecThreads) o[i] = 0.f;
-        return;
-    }
-    double* u = y + ((int64_t)z * nvals + k) * (int64_t)n;
+// Compact WY form of the reflectors in panels of kWy: H_{j0} ... H_{j0+31} =
+// I - V T V^T with T upper triangular, T(k, k) = tau_k and
+// T(0..k-1, k) = -tau_k T(0..k-1, 0..k-1) V(:, 0..k-1)^T v_k.  One block per panel
+// and matrix: V^T V from LDS slabs of 64 columns, then T, one row per lane.
+// Reflector j is row j of A from column j + 1 on (v_j[j + 1] = 1).
+constexpr int kWy = 32;
+
+__global__ void __launch_bounds__(256) wy_t_kernel(const float* A, int64_t strideA, int n, const double* tau,
+                                                   int64_t stride_n, double* wy, int64_t stride_wy) {
+    __shared__ float vs[kWy][65];
+    __shared__ double G[kWy][kWy + 1];
+    const int z = blockIdx.y, j0 = blockIdx.x * kWy, tid = threadIdx.x;
     const float* Az = A + (int64_t)z * strideA;
-    const double* tz = tau + (int64_t)z * stride_n;
-    for (int j = n - 1; j >= 0; --j) {
-        const double t = tz[j];
-        if (t == 0.0) continue;
-        const float* v = Az + (int64_t)j * n;
-        double s = 0.0;
-        for (int i = j + 1 + tid; i < n; i += kVecThreads) s += v[i] * u[i];
-        s = block_sum_d<kVecThreads>(s, red);
-        const double f = t * s;
-        for (int i = j + 1 + tid; i < n; i += kVecThreads) u[i] -= f * v[i];
+    const int gk = (tid >> 4) * 2, gl = (tid & 15) * 2;   // 2 x 2 entries of V^T V
+    double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+    for (int i0 = (j0 + 1) & ~63; i0 < n; i0 += 64) {
+#pragma unroll
+        for (int t = 0; t < kWy * 64 / 256; ++t) {
+            const int q = tid + 256 * t, r = q >> 6, i = i0 + (q & 63), j = j0 + r;
+            const float a = Az[(int64_t)min(j, n - 1) * n + min(i, n - 1)];
+            vs[r][q & 63] = j < n && i > j && i < n ? a : 0.f;
+        }
+        __syncthreads();
+#pragma unroll 8
+        for (int c = 0; c < 64; ++c) {
+            const double a0 = vs[gk][c], a1 = vs[gk + 1][c], b0 = vs[gl][c], b1 = vs[gl + 1][c];
+            acc[0][0] += a0 * b0;
+            acc[0][1] += a0 * b1;
+            acc[1][0] += a1 * b0;
+            acc[1][1] += a1 * b1;
+        }
         __syncthreads();
     }
-    for (int64_t i = tid; i < ld_out; i += kVecThreads) o[i] = i < n ? (float)u[i] : 0.f;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) G[gk + a][gl + b] = acc[a][b];
+    __syncthreads();
+    if (tid < kWy) {
+        double t[kWy];
+        double* o = wy + (int64_t)z * stride_wy + (int64_t)blockIdx.x * kWy * kWy + tid * kWy;
+#pragma unroll
+        for (int k = 0; k < kWy; ++k) {
+            const double tk = j0 + k < n ? tau[(int64_t)z * stride_n + j0 + k] : 0.0;
+            double s = 0.0;
+#pragma unroll
+            for (int l = 0; l < k; ++l) s += t[l] * G[l][k];
+            t[k] = k < tid ? 0.0 : (k == tid ? tk : -tk * s);
+            o[k] = t[k];
+        }
+    }
+}
+
+// u = H_0 H_1 ... H_{n-1} y_k in place in y, one block per vector, u in LDS: per
+// panel from the last, s = V^T u (a wave per four reflectors), c = T s,
+// u -= V c.  0.38 us per reflector at order 768 (one reflector at a time, two
+// barriers each: 2.4 us).
+constexpr int kBackThreads = 512;
+
+__global__ void __launch_bounds__(kBackThreads) wy_apply_kernel(const float* A, int64_t strideA, int n,
+                                                                const double* wy, int64_t stride_wy, double* y,
+                                                                int nvals) {
+    extern __shared__ double ul[];      // n
+    __shared__ double sv[kWy], cv[kWy];
+    const int z = blockIdx.y, k = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int R = kWy / (kBackThreads / 64);
+    double* u = y + ((int64_t)z * nvals + k) * (int64_t)n;
+    const float* Az = A + (int64_t)z * strideA;
+    const double* Tz = wy + (int64_t)z * stride_wy;
+    for (int i = tid; i < n; i += kBackThreads) ul[i] = u[i];
+    __syncthreads();
+    const int tr = tid >> 3, tc = tid & 7;      // c = T s: eight lanes per row
+    for (int p = (n - 1) / kWy; p >= 0; --p) {
+        const int j0 = p * kWy;
+        double tq[kWy / 8];
+        if (tid < 8 * kWy)
+#pragma unroll
+            for (int q = 0; q < kWy / 8; ++q) tq[q] = Tz[(int64_t)p * kWy * kWy + tr * kWy + tc + 8 * q];
+        // Reflector rows of this wave (clamped: row n - 1 stands in past the
+        // end, its T entries are zero).  The masks concern the first 32
+        // entries only; the loads are unconditional, so they overlap.
+        const float* vr[R];
+        double s[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            vr[r] = Az + (int64_t)min(j0 + R * wave + r, n - 1) * n;
+            s[r] = 0.0;
+        }
+#pragma unroll 4
+        for (int i = j0 + 1 + lane; i < n; i += 64) {
+            const double ui = ul[i];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float a = vr[r][i];
+                s[r] += (double)(i > j0 + R * wave + r ? a : 0.f) * ui;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double v = wave_sum_d(s[r]);
+            if (lane == 0) sv[R * wave + r] = v;
+        }
+        __syncthreads();
+        if (tid < 8 * kWy) {
+            double c = 0.0;
+#pragma unroll
+            for (int q = 0; q < kWy / 8; ++q) c += tq[q] * sv[tc + 8 * q];
+            c += dpp_take<0x141, 0xf>(c);
+            c = sum_quad(c);
+            if (tc == 0) cv[tr] = c;
+        }
+        __syncthreads();
+        for (int i = j0 + 1 + tid; i < n; i += kBackThreads) {
+            const float* col = Az + (int64_t)j0 * n + i;
+            double acc = 0.0;
+#pragma unroll 16
+            for (int r = 0; r < kWy; ++r) {
+                const float a = col[(int64_t)min(r, n - 1 - j0) * n];
+                acc += (double)(j0 + r < i ? a : 0.f) * cv[r];
+            }
+            ul[i] -= acc;
+        }
+        __syncthreads();
+    }
+    for (int i = tid; i < n; i += kBackThreads) u[i] = ul[i];
+}
+
+// The eigenvectors y (nvals x n per matrix, contiguous) as fp32 rows (ld,
+// zero padded to ld; rows nvals .. rows_out - 1 zero).
+__global__ void __launch_bounds__(256) vec_rows_kernel(const double* y, int nvals, int n, float* out, int64_t ld_out,
+                                                       int64_t stride_out) {
+    const int z = blockIdx.y, k = blockIdx.x;
+    float* o = out + (int64_t)z * stride_out + (int64_t)k * ld_out;
+    const double* u = y + ((int64_t)z * nvals + k) * (int64_t)n;
+    for (int64_t i = threadIdx.x; i < ld_out; i += 256) o[i] = k < nvals && i < n ? (float)u[i] : 0.f;
+}
+
+// The same as two fp16 parts, hi = fp16(y) and lo = fp16(2^11 (y - hi)):
+// together 22 bits, so hi Psi + 2^-11 lo Psi carries y to fp32 accuracy.
+__global__ void __launch_bounds__(256) vec_split_kernel(const double* y, int nvals, int n, half_t* hi, half_t* lo,
+                                                        int64_t ld_out, int64_t stride_out) {
+    const int z = blockIdx.y, k = blockIdx.x;
+    const int64_t o = (int64_t)z * stride_out + (int64_t)k * ld_out;
+    const double* u = y + ((int64_t)z * nvals + k) * (int64_t)n;
+    for (int64_t i = threadIdx.x; i < ld_out; i += 256) {
+        const double v = k < nvals && i < n ? u[i] : 0.0;
+        const half_t h = (half_t)(float)v;
+        hi[o + i] = h;
+        lo[o + i] = (half_t)(float)((v - (double)(float)h) * 2048.0);
+    }
+}
+// a += 2^-11 b, float4-wise over `rows` x len per matrix (one stride).
+__global__ void __launch_bounds__(256) join_split_kernel(float4* a, const float4* b, int64_t n4, int64_t stride4) {
+    const int64_t o = (int64_t)blockIdx.y * stride4;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+        float4 x = a[o + i];
+        const float4 v = b[o + i];
+        x.x += v.x * 0x1p-11f;
+        x.y += v.y * 0x1p-11f;
+        x.z += v.z * 0x1p-11f;
+        x.w += v.w * 0x1p-11f;
+        a[o + i] = x;
+    }
 }
 
 // Summed fp64 Gram partials (upper 32 x 32 tiles, chunks x l_pad x l_pad)
@@ -576,58 +1135,106 @@ hipError_t launch_gamma_sym(const float* g, int64_t ldg, int64_t strideg, int n,
 
 hipError_t launch_tridiagonalize(const TriWork& w, int n, int batch, hipStream_t s) {
     if (n < 1) return hipErrorInvalidValue;
-    // Columns 0 .. j0 - 1 two launches each, then the trailing block of at
-    // most kTriLdsMax in one launch.
-    const int j0 = std::max(0, n - kTriLdsMax);
+    // Columns 0 .. j0 - 1 one launch each, then the trailing block of at most
+    // kTriRegMax in one launch.
+    const int j0 = std::max(0, n - kTriRegMax);
     for (int j = 0; j < j0; ++j) {
-        hipLaunchKernelGGL(tri_house_kernel, dim3(batch), dim3(kHouseThreads), 0, s, w.A, (int64_t)n * n, n, j,
-                           w.vec, 4 * (int64_t)n, w.d, w.e, w.tau, (int64_t)n);
+        // Columns from c0 (a multiple of 64, for aligned rows) on; threads and
+        // columns per thread by what is left, RB rows per pass.
+        const int c0 = j & ~63, cols = n - c0, rows = n - j - 1;
+        auto step = [&](auto kern, int nt, int rb) {
+            // One pass of rows per block while the blocks fit the chip at once
+            // (2048 threads per CU), more passes beyond; a multiple of 8.
+            const int fit = std::max(8, 256 * (2048 / nt) / batch & ~7);
+            const int nb = std::min(((rows + rb - 1) / rb + 7) & ~7, fit);
+            hipLaunchKernelGGL(kern, dim3(nb, batch), dim3(nt), 0, s, w.A, (int64_t)n * n, n, j, c0, w.vec,
+                               4 * (int64_t)n, w.d, w.e, w.tau, (int64_t)n);
+        };
+        if (cols <= 512) step(tri_step_kernel<256, 2, 8>, 256, 8);
+        else if (cols <= 1024) step(tri_step_kernel<256, 4, 8>, 256, 8);
+        else if (cols <= 2048) step(tri_step_kernel<512, 4, 8>, 512, 8);
+        else if (cols <= 4096) step(tri_step_kernel<512, 8, 4>, 512, 4);
+        else if (cols <= 8192) step(tri_step_kernel<1024, 8, 2>, 1024, 2);
+        else return hipErrorInvalidValue;
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int rows = n - j - 1;
-        hipLaunchKernelGGL(tri_update_kernel, dim3((rows + kRowWaves - 1) / kRowWaves, batch),
-                           dim3(kRowWaves * 64), 0, s, w.A, (int64_t)n * n, n, j, w.vec, 4 * (int64_t)n, w.tau,
-                           (int64_t)n);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
-    const int m = n - j0;
-    hipLaunchKernelGGL(tri_small_kernel, dim3(batch), dim3(kTriThreads), (size_t)m * m * sizeof(float), s, w.A,
-                       (int64_t)n * n, n, j0, w.vec, 4 * (int64_t)n, w.d, w.e, w.tau, (int64_t)n);
+    hipLaunchKernelGGL(tri_reg_kernel, dim3(batch), dim3(kTriThreads), 0, s, w.A, (int64_t)n * n, n, j0, w.vec,
+                       4 * (int64_t)n, w.d, w.e, w.tau, (int64_t)n);
     return hipGetLastError();
 }
 
 hipError_t launch_tri_eigvals(const TriWork& w, int n, int first, int nvals, double* out, int64_t stride_out,
                               int batch, hipStream_t s) {
     if (nvals < 1) return hipSuccess;
-    constexpr int per_block = 64 / kMsLanes;
-    hipLaunchKernelGGL(tri_bisect_kernel, dim3((nvals + per_block - 1) / per_block, batch), dim3(64), 0, s, w.d,
-                       w.e, (int64_t)n, n, first, nvals, out, stride_out);
+    const size_t lds = (size_t)((n + kSturmRun - 1) / kSturmRun * kSturmRun) * sizeof(double2);
+    hipLaunchKernelGGL(tri_bisect_kernel, dim3((nvals + kBisectWaves - 1) / kBisectWaves, batch),
+                       dim3(64 * kBisectWaves), lds, s, w.d, w.e, (int64_t)n, n, first, nvals, out, stride_out);
     return hipGetLastError();
 }
 
-hipError_t launch_tri_eigvecs(const TriWork& w, int n, const double* lam, int nvals, float* out, int64_t ld_out,
-                              int rows_out, int64_t stride_out, int batch, hipStream_t s) {
-    if (nvals < 1 || nvals > rows_out) return hipErrorInvalidValue;
-    const dim3 g((nvals + 63) / 64, batch);
-    hipLaunchKernelGGL(tri_inverse_kernel, g, dim3(64), 0, s, w.d, w.e, (int64_t)n, n, lam, (int64_t)nvals, nvals,
-                       w.lu, w.y, 2, 1);
-    hipError_t e = hipGetLastError();
+// Orders above this keep the inverse iteration's factors in global memory
+// (TriWork::lu).
+bool tri_needs_lu(int n) { return n > kInvLdsMax; }
+
+hipError_t launch_tri_eigvecs(const TriWork& w, int n, const double* lam, int nvals, int batch, hipStream_t s) {
+    if (nvals < 1) return hipErrorInvalidValue;
+    auto inverse = [&](int solves, int init) {
+        if (tri_needs_lu(n)) {
+            hipLaunchKernelGGL(tri_inverse_kernel, dim3((nvals + 63) / 64, batch), dim3(64), 0, s, w.d, w.e,
+                               (int64_t)n, n, lam, (int64_t)nvals, nvals, w.lu, w.y, solves, init);
+        } else {
+            // Few eigenvalues per block: the blocks' chains run side by side
+            // on the CUs.  Up to four while there are more than 256 blocks.
+            int vpb = 1;
+            while (vpb < 4 && (int64_t)((nvals + vpb - 1) / vpb) * batch > 256 &&
+                   inv_lds_bytes(n, 2 * vpb) <= 80 * 1024)
+                vpb *= 2;
+            hipLaunchKernelGGL(tri_inverse_lds_kernel, dim3((nvals + vpb - 1) / vpb, batch), dim3(64),
+                               (size_t)inv_lds_bytes(n, vpb), s, w.d, w.e, (int64_t)n, n, lam, (int64_t)nvals, nvals,
+                               w.y, solves, init, vpb);
+        }
+        return hipGetLastError();
+    };
+    auto orthonormal = [&]() {
+        hipLaunchKernelGGL(vec_cluster_mgs_kernel, dim3(nvals, batch), dim3(kVecThreads), 0, s, lam, (int64_t)nvals,
+                           n, nvals, w.y);
+        return hipGetLastError();
+    };
+    hipError_t e = inverse(2, 1);
+    if (e == hipSuccess) e = orthonormal();
+    if (e == hipSuccess) e = inverse(1, 0);
+    if (e == hipSuccess) e = orthonormal();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(vec_cluster_mgs_kernel, dim3(nvals, batch), dim3(kVecThreads), 0, s, lam, (int64_t)nvals, n,
-                       nvals, w.y);
+    hipLaunchKernelGGL(wy_t_kernel, dim3((n + kWy - 1) / kWy, batch), dim3(256), 0, s, w.A, (int64_t)n * n, n, w.tau,
+                       (int64_t)n, w.wy, w.stride_wy);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(tri_inverse_kernel, g, dim3(64), 0, s, w.d, w.e, (int64_t)n, n, lam, (int64_t)nvals, nvals,
-                       w.lu, w.y, 1, 0);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(vec_cluster_mgs_kernel, dim3(nvals, batch), dim3(kVecThreads), 0, s, lam, (int64_t)nvals, n,
-                       nvals, w.y);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(tri_backtransform_kernel, dim3(rows_out, batch), dim3(kVecThreads), 0, s, w.A, (int64_t)n * n,
-                       n, w.tau, (int64_t)n, w.y, nvals, out, ld_out, stride_out);
+    hipLaunchKernelGGL(wy_apply_kernel, dim3(nvals, batch), dim3(kBackThreads), (size_t)n * sizeof(double), s, w.A,
+                       (int64_t)n * n, n, w.wy, w.stride_wy, w.y, nvals);
+    return hipGetLastError();
+}
+
+hipError_t launch_vec_rows(const double* y, int nvals, int n, float* out, int64_t ld_out, int rows_out,
+                           int64_t stride_out, int batch, hipStream_t s) {
+    if (nvals > rows_out || n > ld_out) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(vec_rows_kernel, dim3(rows_out, batch), dim3(256), 0, s, y, nvals, n, out, ld_out, stride_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_vec_split(const double* y, int nvals, int n, half_t* hi, half_t* lo, int64_t ld_out, int rows_out,
+                            int64_t stride_out, int batch, hipStream_t s) {
+    if (nvals > rows_out || n > ld_out) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(vec_split_kernel, dim3(rows_out, batch), dim3(256), 0, s, y, nvals, n, hi, lo, ld_out,
+                       stride_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_join_split(float* a, const float* b, int64_t count, int64_t stride, int batch, hipStream_t s) {
+    if (count % 4 || stride % 4) return hipErrorInvalidValue;
+    const int64_t n4 = count / 4;
+    hipLaunchKernelGGL(join_split_kernel, dim3((unsigned)std::min<int64_t>(1024, (n4 + 255) / 256), batch), dim3(256),
+                       0, s, reinterpret_cast<float4*>(a), reinterpret_cast<const float4*>(b), n4, stride / 4);
     return hipGetLastError();
 }
 
@@ -647,7 +1254,9 @@ hipError_t launch_eig_select_dense(const EigArgs& a, const TriWork& w, double* l
     if (e != hipSuccess) return e;
     e = launch_tri_eigvals(w, n, 0, top, lam, top, batch, s);
     if (e != hipSuccess) return e;
-    e = launch_tri_eigvecs(w, n, lam, top, zbuf, n, top, (int64_t)top * n, batch, s);
+    e = launch_tri_eigvecs(w, n, lam, top, batch, s);
+    if (e != hipSuccess) return e;
+    e = launch_vec_rows(w.y, top, n, zbuf, n, top, (int64_t)top * n, batch, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(select_k_kernel, dim3((unsigned)(((int64_t)lp * lp + 255) / 256), batch), dim3(256), 0, s,
                        lam, top, zbuf, n, lp, a.kmat, a.ritz, a.ritz_stride, a.nsel);

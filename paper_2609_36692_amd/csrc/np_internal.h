@@ -413,7 +413,9 @@ hipError_t launch_add_diag(half_t* q, int64_t sp, int count, float a, hipStream_
 // ------------------------------------------ dense symmetric eigensolver ---
 // Workspace of one launch of matrices of equal order n (per matrix: A n x n
 // fp32, vec 4 n, d / e / tau n each; per matrix and requested eigenvector:
-// lu 5 n, y n; fp64 unless stated).
+// y n, and lu 6 n where tri_needs_lu(n); fp64 unless stated; per matrix
+// wy_doubles(n) for the reflectors' WY factors, stride_wy apart, which may
+// share memory with what is dead once the eigenvalues are known).
 struct TriWork {
     float* A;       // the matrix on entry; reflectors in its rows on exit
     double* vec;
@@ -422,7 +424,11 @@ struct TriWork {
     double* tau;
     double* lu;     // inverse iteration: 6 n doubles per eigenvector
     double* y;
+    double* wy;
+    int64_t stride_wy;
 };
+bool tri_needs_lu(int n);
+inline int64_t wy_doubles(int64_t n) { return (n + 31) / 32 * 1024; }
 // Symmetrized copy of the leading n x n block of an fp32 matrix (ld ldg).
 hipError_t launch_gamma_sym(const float* g, int64_t ldg, int64_t strideg, int n, float* A, int batch,
                             hipStream_t s);
@@ -432,10 +438,16 @@ hipError_t launch_tridiagonalize(const TriWork& w, int n, int batch, hipStream_t
 hipError_t launch_tri_eigvals(const TriWork& w, int n, int first, int nvals, double* out, int64_t stride_out,
                               int batch, hipStream_t s);
 // Unit eigenvectors of A for the given eigenvalues (nvals per matrix,
-// descending), as fp32 rows of out (ld_out >= n, zero padded; rows nvals ..
-// rows_out - 1 zero).
-hipError_t launch_tri_eigvecs(const TriWork& w, int n, const double* lam, int nvals, float* out, int64_t ld_out,
-                              int rows_out, int64_t stride_out, int batch, hipStream_t s);
+// descending) into w.y (nvals x n fp64 per matrix).
+hipError_t launch_tri_eigvecs(const TriWork& w, int n, const double* lam, int nvals, int batch, hipStream_t s);
+// nvals vectors of n doubles per matrix as fp32 rows of out (ld_out >= n, zero
+// padded; rows nvals .. rows_out - 1 zero), or as fp16 parts hi + 2^-11 lo.
+hipError_t launch_vec_rows(const double* y, int nvals, int n, float* out, int64_t ld_out, int rows_out,
+                           int64_t stride_out, int batch, hipStream_t s);
+hipError_t launch_vec_split(const double* y, int nvals, int n, half_t* hi, half_t* lo, int64_t ld_out, int rows_out,
+                            int64_t stride_out, int batch, hipStream_t s);
+// a += 2^-11 b over count floats per matrix (count and stride multiples of 4).
+hipError_t launch_join_split(float* a, const float* b, int64_t count, int64_t stride, int batch, hipStream_t s);
 // Ritz pairs through the dense eigensolver (for l above the Jacobi kernels'
 // sweet spot): Gamma_Q from the summed fp64 Gram partials, its top
 // min(r, l) eigenpairs, the selection lambda > 1 and K = Z_C diag(lambda^-1/2
