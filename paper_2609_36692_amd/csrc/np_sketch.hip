@@ -14,6 +14,7 @@
 #include "np_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace np {
 namespace {
@@ -235,6 +236,7 @@ __global__ void __launch_bounds__(256) gram64_kernel(Gram64Items t, int ell_pad,
 // column as numerically dependent: its row of R and of R^{-1} is zero, so the
 // matching column of Q = Y R^{-1} is zero and it never reaches the selection.
 constexpr double kDropTol = 1e-12;
+constexpr int kCholRegMax = 192;    // largest l of the register kernel
 // fp64 1/sqrt(x) and 1/x for x > 0: the hardware estimates refined by two
 // Newton steps, accurate to fp64 rounding with a much shorter dependent chain
 // than the IEEE square-root and division sequences (which sit on the
@@ -251,295 +253,264 @@ __device__ __forceinline__ double rcp_f64(double x) {
     return fma(y, fma(-x, y, 1.0), y);
 }
 
-constexpr int kCholLdsMax = 96;
 constexpr int kSmallThreads = 512;
 
-constexpr int kCholThreads = 1024;
-// Upper-triangle entries (i <= j) owned per thread: l (l + 1) / 2 entries for
-// l <= kCholLdsMax over NT threads.
-template <int NT>
-constexpr int chol_own() { return (kCholLdsMax * (kCholLdsMax + 1) / 2 + NT - 1) / NT; }
-// Threads of the LDS kernel (measured: 512 a little ahead of 256 and 1024).
-constexpr int kCholLdsThreads = 512;
+// Cholesky and inverse of one l x l matrix per workgroup, l <= kCholG T, all in
+// registers: elimination of the rows of [G | I] turns G into (scaled) R and I
+// into (scaled) R^{-T}, so the inverse costs no pass of its own.  Thread
+// (ti, tj) holds the entries (ti + kCholG a, tj + kCholG b): of the G part the
+// tiles a <= b, of the inverse part a >= b.  Two pivots per step: both pivot
+// rows go through LDS (two buffers, one barrier per step) and every thread
+// eliminates the second by the first for the columns it needs, so the chain
+// of a step is one exchange, two reciprocals and a few FMAs.  256 threads: with
+// 1024 and a quarter of the entries each, the LDS reads of the pivot row by 16
+// waves took twice as long.  Per launch: 48 matrices of l = 40 17 us (45 us with
+// the matrix in LDS, one pivot per barrier, and the inverse one column per
+// thread); 112 of l = 72 34 us and 22 us for the chunk sums (137 us); one of
+// l = 264 in its two-level form 0.2 ms in all (0.73 ms in row panels).
+constexpr int kCholG = 16;
+constexpr int kCholThreads = kCholG * kCholG;
+template <int T>
+struct CholRegs {
+    double g[T][T], e[T][T];
+};
+struct CholShared {
+    // pivot rows k, k + 1 as [G | inverse], the original diagonal, kept pivots,
+    // transposing tile
+    double row[2][2][2 * kCholRegMax], diag0[kCholRegMax + 1], pivot[kCholRegMax + 1];
+    double tile[2][kCholG][kCholG + 1];
+};
 
-// l <= kCholLdsMax: the whole matrix lives in LDS (fp64, row stride l + 1);
-// R^{-1} overwrites R in place.
-template <int NT>
-__global__ void __launch_bounds__(NT) chol_inv_kernel(const double* partial, int chunks, int ell, int ell_pad,
-                                                      float* rinv) {
-    constexpr int kCholOwn = chol_own<NT>();
-    extern __shared__ double dynd[];
-    const int z = blockIdx.x, tid = threadIdx.x;
-    const double* p = partial + (int64_t)z * chunks * ell_pad * ell_pad;
-    const int ld = ell + 1;
-    // One square buffer.  Step k reads the updated upper row k, leaves the
-    // finished row k of R in the lower triangle (R(k, j) at [j][k]) and
-    // updates the upper trailing block, so it never reads what it writes and
-    // one barrier per step suffices.  R^{-1} then fills the upper triangle,
-    // one column per thread, reading R from the lower triangle.
-    double* R = dynd;
-    float* out = rinv + (int64_t)z * ell_pad * ell_pad;
-    __shared__ double diag0[kCholLdsMax];
-    __shared__ double inv_diag[kCholLdsMax];
-    for (int q = tid; q < ell * ell; q += NT) {
-        const int c = q / ell, d = q - (q / ell) * ell;
-        if (d >= c) {
-            const double g = gram_at(p, ell_pad, c, d);
-            R[c * ld + d] = g;
-            if (c == d) diag0[c] = g;
-        }
-    }
-    __syncthreads();
-    {
-        // The trailing updates of this thread's fixed entries, no index
-        // arithmetic in the step loop.
-        int own[kCholOwn];
-        const int ne = ell * (ell + 1) / 2;
+template <int T, int A0>
+__device__ __forceinline__ void chol_columns(CholRegs<T>& r, CholShared& sh, int& par, int ell) {
+    const int tid = threadIdx.x, ti = tid / kCholG, tj = tid % kCholG;
+    for (int kk = 0; kk < kCholG; kk += 2, par ^= 1) {
+        const int k = kCholG * A0 + kk;
+        if (k >= ell) return;
+        const double *g0 = sh.row[par][0], *g1 = sh.row[par][1];
+        const double *e0 = g0 + kCholRegMax, *e1 = g1 + kCholRegMax;
+        const double piv0 = g0[k], a01 = g0[k + 1], a11 = g1[k + 1], d0 = sh.diag0[k], d1 = sh.diag0[k + 1];
+        double rg0[T], rg1[T], re0[T], re1[T], rf0[T], rf1[T];
 #pragma unroll
-        for (int m = 0; m < kCholOwn; ++m) {
-            int e = tid + m * NT, i = 0;
-            if (e < ne) {
-                while (e >= ell - i) { e -= ell - i; ++i; }
-                own[m] = (i << 16) | (i + e);
+        for (int b = A0; b < T; ++b) {
+            rg0[b] = g0[tj + kCholG * b];
+            rg1[b] = g1[tj + kCholG * b];
+            rf0[b] = g0[ti + kCholG * b];
+            rf1[b] = g1[ti + kCholG * b];
+        }
+#pragma unroll
+        for (int b = 0; b <= A0; ++b) {
+            re0[b] = e0[tj + kCholG * b];
+            re1[b] = e1[tj + kCholG * b];
+        }
+        const bool keep0 = d0 > 0.0 && piv0 > kDropTol * d0;
+        const double ip0 = keep0 ? rcp_f64(piv0) : 0.0, f01 = a01 * ip0, piv1 = fma(-f01, a01, a11);
+        const bool keep1 = d1 > 0.0 && piv1 > kDropTol * d1;
+        const double ip1 = keep1 ? rcp_f64(piv1) : 0.0;
+        if (tid == 0) {
+            sh.pivot[k] = keep0 ? piv0 : 0.0;
+            sh.pivot[k + 1] = keep1 ? piv1 : 0.0;
+        }
+#pragma unroll
+        for (int b = A0; b < T; ++b) {
+            rg1[b] = fma(-f01, rg0[b], rg1[b]);
+            rf1[b] = fma(-f01, rf0[b], rf1[b]);
+        }
+#pragma unroll
+        for (int b = 0; b <= A0; ++b) re1[b] = fma(-f01, re0[b], re1[b]);
+#pragma unroll
+        for (int a = A0; a < T; ++a) {
+            const double f0 = a > A0 || ti > kk ? rf0[a] * ip0 : 0.0;
+            const double f1 = a > A0 || ti > kk + 1 ? rf1[a] * ip1 : 0.0;
+#pragma unroll
+            for (int b = a; b < T; ++b) r.g[a][b] = fma(-f1, rg1[b], fma(-f0, rg0[b], r.g[a][b]));
+#pragma unroll
+            for (int b = 0; b <= A0; ++b) r.e[a][b] = fma(-f1, re1[b], fma(-f0, re0[b], r.e[a][b]));
+        }
+        // The next two pivot rows into the other buffer.
+        const int nk = (kk + 2) % kCholG;
+        if (ti == nk || ti == nk + 1) {
+            double* ng = sh.row[par ^ 1][ti - nk];
+            double* ne = ng + kCholRegMax;
+            auto put = [&](auto at) {
+                constexpr int A1 = decltype(at)::value;
+                if constexpr (A1 < T) {
+#pragma unroll
+                    for (int b = A1; b < T; ++b) ng[tj + kCholG * b] = r.g[A1][b];
+#pragma unroll
+                    for (int b = 0; b <= A1; ++b) ne[tj + kCholG * b] = r.e[A1][b];
+                }
+            };
+            if (nk > 0) put(std::integral_constant<int, A0>{});
+            else put(std::integral_constant<int, A0 + 1>{});
+        }
+        __syncthreads();
+    }
+    if constexpr (A0 + 1 < T) chol_columns<T, A0 + 1>(r, sh, par, ell);
+}
+
+// The block of order ell at row and column `off` of the l x l matrix: SUM takes
+// it (off = 0, the whole matrix) from the chunk partials and also clears the
+// rest of rinv, else it is read from src (ld ell_pad); the diagonal that the
+// dropping test compares with is always the Gram's own.  x64, when given,
+// receives R^{-1} (upper triangle) in fp64.  Entries past ell but inside
+// ell_pad are loaded and discarded, so the loads need no branches.
+template <int T, bool SUM>
+__global__ void __launch_bounds__(kCholThreads) chol_reg_kernel(const double* src, int64_t stride, int ell,
+                                                                int ell_pad, const double* partial, int off,
+                                                                double* x64, int64_t stride_x, float* rinv) {
+    __shared__ CholShared sh;
+    const int z = blockIdx.x, tid = threadIdx.x, ti = tid / kCholG, tj = tid % kCholG;
+    const double* part = partial + (int64_t)z * kGramChunks * ell_pad * ell_pad;
+    const double* p = SUM ? part : src + (int64_t)z * stride;
+    CholRegs<T> r;
+    for (int q = tid; q < 2 * 2 * 2 * kCholRegMax; q += kCholThreads) (&sh.row[0][0][0])[q] = 0.0;
+    if (tid <= kCholRegMax) sh.diag0[tid] = !SUM && tid < ell ? gram_at(part, ell_pad, off + tid, off + tid) : 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < T; ++a) {
+#pragma unroll
+        for (int b = a; b < T; ++b) {
+            const int i = ti + kCholG * a, j = tj + kCholG * b;
+            const int c = min(min(i, j), ell - 1), d = min(max(i, j), ell - 1);
+            double v = 0.0;
+            const double* q = p + (int64_t)c * ell_pad + d;
+            if constexpr (SUM) {
+                double w[kGramChunks];
+#pragma unroll
+                for (int u = 0; u < kGramChunks; ++u) w[u] = q[(int64_t)u * ell_pad * ell_pad];
+#pragma unroll
+                for (int u = 0; u < kGramChunks; ++u) v += w[u];
             } else {
-                own[m] = -1;
+                v = q[0];
             }
-        }
-        for (int k = 0; k < ell; ++k) {
-            const double piv = R[k * ld + k];
-            const bool keep = diag0[k] > 0.0 && piv > kDropTol * diag0[k];
-            const double irk = keep ? rsqrt_f64(piv) : 0.0;
-            const double ipiv = irk * irk;
-            if (tid == 0) inv_diag[k] = irk;
-            for (int j = k + 1 + tid; j < ell; j += NT) R[j * ld + k] = R[k * ld + j] * irk;
-#pragma unroll
-            for (int m = 0; m < kCholOwn; ++m) {
-                if (own[m] < 0) break;
-                const int i = own[m] >> 16, j = own[m] & 0xffff;
-                if (i > k) R[i * ld + j] -= R[k * ld + i] * R[k * ld + j] * ipiv;
-            }
-            __syncthreads();
+            r.g[a][b] = j < ell && i < ell ? v : 0.0;
+            if (SUM && a == b && i == j && j < ell) sh.diag0[j] = v;
         }
     }
-    // X = R^{-1}: X(i, j) = -(sum_{i < k <= j} R(i, k) X(k, j)) / R(i, i),
-    // X(i, i) = 1 / R(i, i); rows of dropped columns are zero.  One column per
-    // thread, bottom up, no barriers.
-    auto x_entry = [&](int i, int j) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        int k = i + 1;
-        for (; k + 3 <= j; k += 4) {
-            s0 += R[k * ld + i] * R[k * ld + j];
-            s1 += R[(k + 1) * ld + i] * R[(k + 1) * ld + j];
-            s2 += R[(k + 2) * ld + i] * R[(k + 2) * ld + j];
-            s3 += R[(k + 3) * ld + i] * R[(k + 3) * ld + j];
-        }
-        for (; k <= j; ++k) s0 += R[k * ld + i] * R[k * ld + j];
-        return -((s0 + s1) + (s2 + s3)) * inv_diag[i];
-    };
-    for (int j = tid; j < ell; j += NT) {
-        R[j * ld + j] = inv_diag[j];
-        for (int i = j - 1; i >= 0; --i) R[i * ld + j] = x_entry(i, j);
+#pragma unroll
+    for (int a = 0; a < T; ++a)
+#pragma unroll
+        for (int b = 0; b <= a; ++b) r.e[a][b] = a == b && ti == tj ? 1.0 : 0.0;
+    __syncthreads();
+    if (ti < 2) {
+#pragma unroll
+        for (int b = 0; b < T; ++b) sh.row[0][ti][tj + kCholG * b] = r.g[0][b];
+        sh.row[0][ti][kCholRegMax + tj] = r.e[0][0];
     }
     __syncthreads();
-    for (int q = tid; q < ell_pad * ell_pad; q += NT) {
-        const int i = q / ell_pad, j = q - (q / ell_pad) * ell_pad;
-        out[q] = (i < ell && j < ell && j >= i) ? (float)R[i * ld + j] : 0.f;
-    }
-}
-
-// l > kCholLdsMax (the whole matrix fits in LDS up to l = 138, but one pivot
-// per barrier over the whole trailing matrix is slower from about l = 100 on):
-// R and X = R^{-1} live in a global scratch slice (two l_pad^2 fp64 squares,
-// upper triangles only, L2-resident at these sizes) and the work runs in row
-// panels staged through LDS, so the global traffic is one read and write of
-// the trailing triangle per panel rather than per pivot.
-//   Cholesky (right-looking), panel of kPanelC rows k0..: factor the panel
-//   rows in LDS (one barrier per pivot), scale them into rows of R, then
-//   subtract their outer products from the trailing upper triangle in 4x4
-//   register tiles.
-//   Inverse, row panels of kPanelI rows bottom up: with rows below the panel
-//   of X final, T = R(I, below) X(below, :) per column (a column and four
-//   panel rows per thread), then X(I, j) = R(I, I)^{-1} (e_j - T(:, j)) by
-//   back substitution, one column per thread in registers.
-constexpr int kPanelC = 32;
-constexpr int kPanelI = 16;
-
-// Copies src[c] -> dst[c] for c in [c0, c1), lane-strided, with eight loads
-// in flight per lane before the first store (one L2 latency per 512 entries).
-__device__ __forceinline__ void row_to_lds(double* dst, const double* src, int c0, int c1, int lane) {
-    for (int c = c0 + lane; c < c1; c += 512) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = c + 64 * u < c1 ? src[c + 64 * u] : 0.0;
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (c + 64 * u < c1) dst[c + 64 * u] = v[u];
-    }
-}
-
-__global__ void __launch_bounds__(kCholThreads) chol_inv_panel_kernel(const double* partial, int chunks, int ell,
-                                                                      int ell_pad, double* scratch, float* rinv) {
-    constexpr int NT = kCholThreads;
-    extern __shared__ double dynd[];
-    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
-    constexpr int NG = NT / 64;
-    const double* p = partial + (int64_t)z * chunks * ell_pad * ell_pad;
-    const int ld = ell_pad, pst = ell + 1;
-    double* W = scratch + (int64_t)z * 2 * ell_pad * ell_pad;
-    double* X = W + (int64_t)ell_pad * ell_pad;
+    int par = 0;
+    chol_columns<T, 0>(r, sh, par, ell);
+    // R^{-1}(j, i) = e(i, j) / sqrt(pivot i), transposed through LDS by tiles.
     float* out = rinv + (int64_t)z * ell_pad * ell_pad;
-    __shared__ double diag0[384];
-    __shared__ double pivot[384];
-    __shared__ double inv_diag[384];
-    // Entries of the output outside the upper triangle of the l x l block
-    // are zero; the inverse writes the rest.
-    for (int i = grp; i < ell_pad; i += NG)
-        for (int j = lane; j < ell_pad; j += 64)
-            if (!(i < ell && j < ell && j >= i)) out[(int64_t)i * ell_pad + j] = 0.f;
-    for (int i = grp; i < ell; i += NG)
-        for (int j0 = i + lane; j0 < ell; j0 += 256) {
-            double g[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) g[u] = j0 + 64 * u < ell ? gram_at(p, ell_pad, i, j0 + 64 * u) : 0.0;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = j0 + 64 * u;
-                if (j < ell) {
-                    W[(int64_t)i * ld + j] = g[u];
-                    if (i == j) diag0[i] = g[u];
-                }
-            }
-        }
+    double* xo = x64 ? x64 + (int64_t)z * stride_x : nullptr;
     __syncthreads();
-
-    double* P = dynd;  // kPanelC x pst
-    for (int k0 = 0; k0 < ell; k0 += kPanelC) {
-        const int kb = min(kPanelC, ell - k0), w = ell - k0;
-        for (int r = grp; r < kb; r += NG) row_to_lds(P + r * pst, W + (int64_t)(k0 + r) * ld + k0, r, w, lane);
-        __syncthreads();
-        for (int r = 0; r < kb; ++r) {
-            const int k = k0 + r;
-            const double piv = P[r * pst + r];
-            const bool keep = diag0[k] > 0.0 && piv > kDropTol * diag0[k];
-            const double ipiv = keep ? rcp_f64(piv) : 0.0;
-            if (tid == 0) pivot[k] = keep ? piv : 0.0;
-            const double* pr = P + r * pst;
-            for (int rr = r + 1 + grp; rr < kb; rr += NG) {
-                const double f = pr[rr] * ipiv;
-                double* prr = P + rr * pst;
-#pragma unroll 4
-                for (int c = rr + lane; c < w; c += 64) prr[c] -= f * pr[c];
-            }
+    int flip = 0;
+#pragma unroll
+    for (int a = 0; a < T; ++a) {
+        if (kCholG * a >= ell) break;
+        const int i = ti + kCholG * a;
+        const double pv = i < ell ? sh.pivot[i] : 0.0, s = pv > 0.0 ? rsqrt_f64(pv) : 0.0;
+#pragma unroll
+        for (int b = 0; b <= a; ++b, flip ^= 1) {
+            sh.tile[flip][tj][ti] = r.e[a][b] * s;
             __syncthreads();
-        }
-        // Rows of R: the pivot rows scaled by 1 / sqrt(pivot) (zero when dropped).
-        for (int r = grp; r < kb; r += NG) {
-            const double pv = pivot[k0 + r];
-            const double s = pv > 0.0 ? rsqrt_f64(pv) : 0.0;
-            if (lane == 0) inv_diag[k0 + r] = s;
-            for (int c = r + lane; c < w; c += 64) {
-                const double v = P[r * pst + c] * s;
-                P[r * pst + c] = v;
-                W[(int64_t)(k0 + r) * ld + k0 + c] = v;
+            const int jo = kCholG * b + ti, io = kCholG * a + tj;      // row, column of R^{-1}
+            if (jo <= io && io < ell) {
+                const double v = sh.tile[flip][ti][tj];
+                out[(int64_t)jo * ell_pad + io] = (float)v;
+                if (xo) xo[(int64_t)jo * ell_pad + io] = v;
             }
         }
-        __syncthreads();
-        const int t0 = kb, t = w - kb, nbk = (t + 3) >> 2;
-        for (int b = tid; b < nbk * nbk; b += NT) {
-            const int bi = b / nbk, bj = b - bi * nbk;
-            if (bi > bj) continue;
-            const int ci = t0 + 4 * bi, cj = t0 + 4 * bj;
-            double acc[4][4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int i = ci + a, j = cj + e;
-                    acc[a][e] = (j < w && i <= j) ? W[(int64_t)(k0 + i) * ld + k0 + j] : 0.0;
-                }
-#pragma unroll 4
-            for (int r = 0; r < kb; ++r) {
-                double vi[4], vj[4];
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    vi[a] = ci + a < w ? P[r * pst + ci + a] : 0.0;
-                    vj[a] = cj + a < w ? P[r * pst + cj + a] : 0.0;
-                }
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[a][e] -= vi[a] * vj[e];
-            }
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int i = ci + a, j = cj + e;
-                    if (j < w && i <= j) W[(int64_t)(k0 + i) * ld + k0 + j] = acc[a][e];
-                }
-        }
-        __syncthreads();
     }
+    if (SUM)
+        for (int q = tid; q < ell_pad * ell_pad; q += kCholThreads) {
+            const int i = q / ell_pad, j = q - (q / ell_pad) * ell_pad;
+            if (!(i <= j && j < ell)) out[q] = 0.f;
+        }
+}
 
-    double* Rp = dynd;                  // kPanelI x pst: rows of R from column i0
-    double* T = dynd + kPanelI * pst;   // kPanelI x pst: R(I, below) X(below, :)
-    for (int i0 = ((ell - 1) / kPanelI) * kPanelI; i0 >= 0; i0 -= kPanelI) {
-        const int kb = min(kPanelI, ell - i0), w = ell - i0, nc = w - kb;
-        for (int r = grp; r < kPanelI; r += NG) {
-            double* dst = Rp + r * pst;
-            const int c0 = r < kb ? r : w;
-            for (int c = lane; c < c0; c += 64) dst[c] = 0.0;
-            row_to_lds(dst, W + (int64_t)(i0 + r) * ld + i0, c0, w, lane);
+// Dense G (upper triangle, ld ell_pad) from the chunk partials in many blocks;
+// zeros in the lower triangle of x (R^{-1} in fp64) and in the entries of rinv
+// outside the upper triangle.
+__global__ void __launch_bounds__(256) chol_sum_kernel(const double* partial, int ell, int ell_pad, double* g,
+                                                       double* x, int64_t stride, float* rinv) {
+    const int z = blockIdx.y, q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= ell_pad * ell_pad) return;
+    const int i = q / ell_pad, j = q - (q / ell_pad) * ell_pad;
+    const double* p = partial + (int64_t)z * kGramChunks * ell_pad * ell_pad;
+    if (i <= j && j < ell) {
+        g[(int64_t)z * stride + q] = gram_at(p, ell_pad, i, j);
+    } else {
+        x[(int64_t)z * stride + q] = 0.0;
+        rinv[(int64_t)z * ell_pad * ell_pad + q] = 0.f;
+    }
+}
+
+// C = C0 +- A B in fp64 for the blocks of a two-level factorization: A(i, k) =
+// a[i ai + k ak], B(k, j) = b[k bk + j bj], C at c[i ldc + j] (and / or fp32 c32).
+// 32 x 32 output tiles, 2 x 2 per thread.
+struct SmallDgemm {
+    const double* a; int64_t ai, ak, stride_a;
+    const double* b; int64_t bk, bj, stride_b;
+    const double* c0; int64_t ldc0, stride_c0;  // null: 0
+    double sign;
+    double* c; int64_t ldc, stride_c;           // may be null
+    float* c32; int64_t ldc32, stride_c32;      // may be null
+    int m, n, k;
+};
+__global__ void __launch_bounds__(256) small_dgemm_kernel(SmallDgemm p) {
+    __shared__ double as[32][33], bs[32][33];   // [k][i], [k][j]
+    const int z = blockIdx.z, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
+    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+    const double* a = p.a + (int64_t)z * p.stride_a;
+    const double* b = p.b + (int64_t)z * p.stride_b;
+    double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+    double ra[4], rb[4];        // the next slab, in flight during this one's FMAs
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int q = tid + 256 * t, hi = q >> 5, lo = q & 31;
+            // The unit-stride index along the lanes; clamped, then masked.
+            const int ka = k0 + (p.ai == 1 ? hi : lo), ia = i0 + (p.ai == 1 ? lo : hi);
+            const int kb = k0 + (p.bj == 1 ? hi : lo), jb = j0 + (p.bj == 1 ? lo : hi);
+            const double va = a[min(ia, p.m - 1) * p.ai + min(ka, p.k - 1) * p.ak];
+            const double vb = b[min(kb, p.k - 1) * p.bk + min(jb, p.n - 1) * p.bj];
+            ra[t] = ia < p.m && ka < p.k ? va : 0.0;
+            rb[t] = jb < p.n && kb < p.k ? vb : 0.0;
+        }
+    };
+    load(0);
+    for (int k0 = 0; k0 < p.k; k0 += 32) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int q = tid + 256 * t, hi = q >> 5, lo = q & 31;
+            as[p.ai == 1 ? hi : lo][p.ai == 1 ? lo : hi] = ra[t];
+            bs[p.bj == 1 ? hi : lo][p.bj == 1 ? lo : hi] = rb[t];
         }
         __syncthreads();
-        for (int q = tid; q < (kPanelI / 4) * nc; q += NT) {
-            const int g = q / nc, jc = q - g * nc;
-            const double* r0 = Rp + 4 * g * pst + kb;
-            const double* xc = X + (int64_t)(i0 + kb) * ld + i0 + kb + jc;  // X(i0 + kb + u, j) = xc[u ld]
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            // Eight independent loads in flight per thread: the column of X
-            // comes from L2, one latency per eight rows.
-            int u = 0;
-            for (; u + 8 <= jc + 1; u += 8) {
-                double xv[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) xv[e] = xc[(int64_t)(u + e) * ld];
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) acc[a] += r0[a * pst + u + e] * xv[e];
-            }
-            for (; u <= jc; ++u) {
-                const double x = xc[(int64_t)u * ld];
-#pragma unroll
-                for (int a = 0; a < 4; ++a) acc[a] += r0[a * pst + u] * x;
-            }
-#pragma unroll
-            for (int a = 0; a < 4; ++a) T[(4 * g + a) * pst + jc] = acc[a];
-        }
-        __syncthreads();
-        for (int jc = tid; jc < w; jc += NT) {
-            double x[kPanelI];
-#pragma unroll
-            for (int r = kPanelI - 1; r >= 0; --r) {
-                double s = 0.0;
-                if (r < kb) {
-                    s = (jc == r ? 1.0 : 0.0) - (jc >= kb ? T[r * pst + jc - kb] : 0.0);
-#pragma unroll
-                    for (int r2 = r + 1; r2 < kPanelI; ++r2) s -= Rp[r * pst + r2] * x[r2];
-                    s *= inv_diag[i0 + r];
-                }
-                x[r] = s;
-            }
-#pragma unroll
-            for (int r = 0; r < kPanelI; ++r)
-                if (r < kb && r <= jc) {
-                    X[(int64_t)(i0 + r) * ld + i0 + jc] = x[r];
-                    out[(int64_t)(i0 + r) * ell_pad + i0 + jc] = (float)x[r];
-                }
+        if (k0 + 32 < p.k) load(k0 + 32);
+#pragma unroll 8
+        for (int k = 0; k < 32; ++k) {
+            const double x0 = as[k][ty], x1 = as[k][ty + 16], y0 = bs[k][tx], y1 = bs[k][tx + 16];
+            acc[0][0] = fma(x0, y0, acc[0][0]);
+            acc[0][1] = fma(x0, y1, acc[0][1]);
+            acc[1][0] = fma(x1, y0, acc[1][0]);
+            acc[1][1] = fma(x1, y1, acc[1][1]);
         }
         __syncthreads();
     }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int i = i0 + ty + 16 * u, j = j0 + tx + 16 * v;
+            if (i >= p.m || j >= p.n) continue;
+            double x = p.sign * acc[u][v];
+            if (p.c0) x += p.c0[(int64_t)z * p.stride_c0 + i * p.ldc0 + j];
+            if (p.c) p.c[(int64_t)z * p.stride_c + i * p.ldc + j] = x;
+            if (p.c32) p.c32[(int64_t)z * p.stride_c32 + i * p.ldc32 + j] = (float)x;
+        }
 }
 
 // ------------------------------------------------------------- M^T V ----
@@ -1235,16 +1206,67 @@ hipError_t launch_gram64(const Gram64Items& t, int ell_pad, double* partial, hip
 hipError_t launch_chol_inv(const double* partial, int chunks, int ell, int ell_pad, double* scratch, float* rinv,
                            int batch, hipStream_t s) {
     if (ell < 1 || ell > 384 || ell_pad < ell || ell_pad > 384 || chunks != kGramChunks) return hipErrorInvalidValue;
-    if (ell <= kCholLdsMax) {
-        const size_t lds = (size_t)(ell + 1) * (ell + 1) * sizeof(double);
-        hipLaunchKernelGGL(chol_inv_kernel<kCholLdsThreads>, dim3(batch), dim3(kCholLdsThreads), lds, s, partial,
-                           chunks, ell, ell_pad, rinv);
-    } else {
-        const size_t lds = (size_t)std::max(kPanelC, 2 * kPanelI) * (ell + 1) * sizeof(double);
-        hipLaunchKernelGGL(chol_inv_panel_kernel, dim3(batch), dim3(kCholThreads), lds, s, partial, chunks, ell,
-                           ell_pad, scratch, rinv);
+    const int64_t lp2 = (int64_t)ell_pad * ell_pad, ld = ell_pad;
+    // Up to 64 the workgroup sums the chunk partials itself (16 of them per
+    // entry, all in flight); above, many blocks do in a launch of their own.
+    if (ell <= 64) {
+        auto run = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(batch), dim3(kCholThreads), 0, s, (const double*)nullptr, (int64_t)0, ell,
+                               ell_pad, partial, 0, (double*)nullptr, (int64_t)0, rinv);
+        };
+        switch ((ell + kCholG - 1) / kCholG) {
+            case 1: run(chol_reg_kernel<1, true>); break;
+            case 2: run(chol_reg_kernel<2, true>); break;
+            case 3: run(chol_reg_kernel<3, true>); break;
+            default: run(chol_reg_kernel<4, true>); break;
+        }
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    // scratch per matrix: G, then X = R^{-1} (ell_pad^2 doubles each).
+    const int64_t st = 2 * lp2;
+    double *G = scratch, *X = scratch + lp2;
+    hipLaunchKernelGGL(chol_sum_kernel, dim3((unsigned)((lp2 + 255) / 256), batch), dim3(256), 0, s, partial, ell,
+                       ell_pad, G, X, st, rinv);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    auto factor = [&](int off, int n, const double* src, bool x64) {
+        auto run = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(batch), dim3(kCholThreads), 0, s, src, st, n, ell_pad, partial, off,
+                               x64 ? X + off * (ld + 1) : nullptr, st, rinv + off * (ld + 1));
+        };
+        switch ((n + 2 * kCholG - 1) / (2 * kCholG)) {
+            case 1: run(chol_reg_kernel<2, false>); break;
+            case 2: run(chol_reg_kernel<4, false>); break;
+            case 3: run(chol_reg_kernel<6, false>); break;
+            case 4: run(chol_reg_kernel<8, false>); break;
+            case 5: run(chol_reg_kernel<10, false>); break;
+            default: run(chol_reg_kernel<12, false>); break;
+        }
+        return hipGetLastError();
+    };
+    if (ell <= kCholRegMax) return factor(0, ell, G, false);
+    // Two levels: [G11 G12; . G22], about half the rows each (a pivot of a
+    // smaller block costs less).
+    //   R12 = R11^{-T} G12 (kept transposed under G11), S = G22 - R12^T R12,
+    //   X12 = -X11 (R12 X22).
+    const int l1 = (int)round_up((ell + 1) / 2, kCholG), l2 = ell - l1;
+    double* G12 = G + l1;                           // then R12 X22
+    double* R12t = G + (int64_t)l1 * ld;            // l2 x l1
+    double* G22 = G + (int64_t)l1 * (ld + 1);       // then S
+    double* X22 = X + (int64_t)l1 * (ld + 1);
+    auto gemm = [&](const double* ga, int64_t ai, int64_t ak, const double* gb, int64_t bk, int64_t bj,
+                    const double* c0, double sign, double* c, float* c32, int m, int n, int k) {
+        const SmallDgemm p{ga, ai, ak, st, gb, bk, bj, st, c0, ld, st, sign, c, ld, st, c32, ld, lp2, m, n, k};
+        hipLaunchKernelGGL(small_dgemm_kernel, dim3((n + 31) / 32, (m + 31) / 32, batch), dim3(256), 0, s, p);
+        return hipGetLastError();
+    };
+    e = factor(0, l1, G, true);
+    if (e == hipSuccess) e = gemm(G12, 1, ld, X, ld, 1, nullptr, 1.0, R12t, nullptr, l2, l1, l1);
+    if (e == hipSuccess) e = gemm(R12t, ld, 1, R12t, 1, ld, G22, -1.0, G22, nullptr, l2, l2, l1);
+    if (e == hipSuccess) e = factor(l1, l2, G22, true);
+    if (e == hipSuccess) e = gemm(R12t, 1, ld, X22, ld, 1, nullptr, 1.0, G12, nullptr, l1, l2, l2);
+    if (e == hipSuccess) e = gemm(X, ld, 1, G12, ld, 1, nullptr, -1.0, nullptr, rinv + l1, l1, l2, l1);
+    return e;
 }
 
 hipError_t launch_small_mul(const SmallMulArgs& a, hipStream_t s) {

@@ -1,0 +1,63 @@
+"""NormPre-L over sketch widths l at the edges of the l x l kernels: the
+Cholesky's tiles of 16, the summed Gram above 64, the two-level factorization
+above 192 (with its uneven halves), and rank-deficient sketches whose dependent
+columns are dropped in either half."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import normpre_oracle as O
+from paper_2609_36692_amd import normpre as N
+from paper_2609_36692_amd import workloads as WL
+from parity_util import check_update
+
+pytestmark = pytest.mark.gpu
+
+U16 = 2.0 ** -11
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    c = N.normpre_init(0)
+    yield c
+    N.normpre_destroy(c)
+
+
+def _step(ctx, mats, t, rank, oversample):
+    Ws, Gs, Ms = ([x[i].cuda().clone() for x in mats] for i in range(3))
+    hp = N.normpre_default_hparams(lr=1.0, weight_decay=0.0, step=t, rank=rank, oversample=oversample)
+    N.normpre_step(ctx, N.NORMPRE_VARIANT_L, Ws, Gs, Ms, hp)
+    torch.cuda.synchronize()
+    for i, (mat, W) in enumerate(zip(mats, Ws)):
+        ref = O.normpre_step(*(x.numpy() for x in mat), t,
+                             O.HParams(lr=1.0, weight_decay=0.0, rank=rank, oversample=oversample), "L", matrix_id=i)
+        lam = ref["ritz_values"][ref["ritz_values"] > 1.0][: ref["n_selected"]]
+        kappa = math.sqrt(float(np.sum(lam))) / max(np.linalg.norm(ref["t"]), 1e-300)
+        u = mat[0].double().numpy() - W.cpu().double().numpy()
+        # fp16 operands of the apply, amplified by kappa along the selected modes
+        err = check_update(f"L width {rank + oversample} {tuple(mat[0].shape)} t={t}", u, ref["update"],
+                           max(1e-2, 8.0 * U16 * kappa))
+        print(f"  l={ref['ell']} |C|={ref['n_selected']} update err {err:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("ell", [1, 2, 3, 15, 16, 17, 32, 33, 48, 49, 63, 64, 65, 96, 97, 104, 105, 128, 129, 160,
+                                 161, 192, 193, 208, 209, 256, 257, 383, 384])
+def test_widths(ctx, ell):
+    print(f"L width {ell}", flush=True)
+    wl = WL.Workload("t", 90, [(400, 520)], "lowrank", 1.0, rank=8)
+    mats = [WL.make_matrix(wl, i, "cpu", shape=(400, 520)) for i in range(2)]
+    _step(ctx, mats, 0, max(1, ell - 3), min(3, ell - 1))
+
+
+@pytest.mark.parametrize("ell,true_rank", [(24, 5), (72, 10), (120, 60), (250, 40), (250, 200)])
+@pytest.mark.parametrize("t", [0, 1])
+def test_rank_deficient(ctx, ell, true_rank, t):
+    print(f"L width {ell}, rank {true_rank} t={t}", flush=True)
+    g = torch.Generator().manual_seed(5)
+    m = torch.randn(300, true_rank, generator=g) @ torch.randn(true_rank, 410, generator=g)
+    w = 0.02 * torch.randn(300, 410, generator=g)
+    _step(ctx, [(w, m, torch.zeros_like(m))], t, ell - 8, 8)
