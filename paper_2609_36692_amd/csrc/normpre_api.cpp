@@ -404,12 +404,6 @@ bool gram_space_ns(int variant, const Dims& d, const normpre_hparams& hp) {
     return std::max(d.m, d.n) >= 2 * std::min(d.m, d.n);
 }
 
-// Length chunk of the fp64 Gram: >= 256 for parallel blocks and at most
-// kGramChunks chunks (the consumers always sum kGramChunks slots).
-int gram_chunk_len(int64_t len) {
-    return (int)std::max<int64_t>(256, round_up((len + kGramChunks - 1) / kGramChunks, 64));
-}
-
 int ns_tiles(const Dims& d) { return (int)((d.mp / 128) * (d.np_ / 128)); }
 // Tiles of the NormPre-L apply passes (64 x 128).
 int apply_tiles(const Dims& d) { return (int)((d.mp / 64) * (d.np_ / 128)); }
@@ -474,6 +468,7 @@ struct Pool {
     half_t* rmat = nullptr;
     int qcur = 0;
     double* gpart = nullptr;
+    int gslots = kGramChunks;   // slots of its Gram partial sums
     double* chol = nullptr;
     float* rinv = nullptr;
     float* kmat = nullptr;
@@ -639,6 +634,13 @@ std::vector<Pool> make_pools(std::vector<Item>& items, int variant) {
             }
             it.eig_off = p.eig[it.eig].count;
             p.eig[it.eig].count += it.count;
+        }
+    if (variant == NORMPRE_VARIANT_L)
+        for (size_t q = 0; q < pools.size(); ++q) {
+            int64_t len = 0;
+            for (const Item& it : items)
+                if (it.pool == (int)q) len = std::max(len, it.d.lp_);
+            pools[q].gslots = gram64_slots(pools[q].ell, pools[q].count, len);
         }
     return pools;
 }
@@ -1413,6 +1415,7 @@ int gram64_run(const StepCtx& sc, const std::vector<const Item*>& run, const Poo
     const int64_t lp = pl.ellp, off0 = run[0]->pool_off;
     Gram64Items t{};
     t.ell = pl.ell;
+    t.chunks = pl.gslots;
     for (const Item* it : run) {
         const int g = t.n++;
         int64_t len = 0;
@@ -1421,10 +1424,9 @@ int gram64_run(const StepCtx& sc, const std::vector<const Item*>& run, const Poo
         t.ld[g] = len;
         t.stride[g] = lp * it->d.lp_;
         t.len[g] = len;
-        t.chunk_len[g] = gram_chunk_len(len);
         t.zbeg[g + 1] = t.zbeg[g] + it->count;
     }
-    double* out = pl.gpart + off0 * kGramChunks * lp * lp;
+    double* out = pl.gpart + off0 * pl.gslots * lp * lp;
     NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0, [&] { return launch_gram64(t, (int)lp, out, sc.s); }),
            "gram64");
     return NORMPRE_OK;
@@ -1466,7 +1468,7 @@ int cholqr_round(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>&
     for (const Pool& pl : pools)
         NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
                      [&] {
-                         return launch_chol_inv(pl.gpart, kGramChunks, pl.ell, pl.ellp, pl.chol, pl.rinv, pl.count,
+                         return launch_chol_inv(pl.gpart, pl.gslots, pl.ell, pl.ellp, pl.chol, pl.rinv, pl.count,
                                                 sc.s);
                      }),
                "cholesky");
@@ -1801,7 +1803,7 @@ int run_round_l(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
     // Ritz pairs and selection, one launch per pool.
     for (const Pool& pl : pools) {
         EigArgs ea{};
-        ea.partial = pl.gpart; ea.chunks = kGramChunks;
+        ea.partial = pl.gpart; ea.chunks = pl.gslots;
         ea.ell = pl.ell; ea.ell_pad = pl.ellp; ea.rank = sc.hp->rank;
         ea.scratch = pl.eigs; ea.kmat = pl.kmat;
         ea.ritz = pl.ritz; ea.ritz_stride = pl.top; ea.nsel = pl.nsel;

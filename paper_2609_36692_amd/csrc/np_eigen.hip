@@ -1087,7 +1087,7 @@ __global__ void __launch_bounds__(256) join_split_kernel(float4* a, const float4
     }
 }
 
-// Summed fp64 Gram partials (upper 32 x 32 tiles, chunks x l_pad x l_pad)
+// Summed fp64 Gram partials (upper 16 x 16 tiles, chunks x l_pad x l_pad)
 // -> symmetric n x n fp32 matrix.
 __global__ void gram_to_mat_kernel(const double* partial, int chunks, int ell_pad, int n, float* A) {
     const int z = blockIdx.y;
@@ -1095,7 +1095,7 @@ __global__ void gram_to_mat_kernel(const double* partial, int chunks, int ell_pa
     float* Az = A + (int64_t)z * n * n;
     for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n * n; idx += gridDim.x * blockDim.x) {
         const int c = idx / n, d = idx - (idx / n) * n;
-        Az[idx] = (float)gram_at(part, ell_pad, c, d);
+        Az[idx] = (float)gram_at(part, ell_pad, c, d, chunks);
     }
 }
 
@@ -1245,7 +1245,7 @@ namespace np {
 hipError_t launch_eig_select_dense(const EigArgs& a, const TriWork& w, double* lam, float* zbuf, int batch,
                                    hipStream_t s) {
     const int n = a.ell, lp = a.ell_pad, top = std::min(a.rank, n);
-    if (a.chunks != kGramChunks || n < 1 || n > lp) return hipErrorInvalidValue;
+    if (a.chunks < 1 || a.chunks > kGramChunks || n < 1 || n > lp) return hipErrorInvalidValue;
     const unsigned gb = (unsigned)std::min<int64_t>(1024, ((int64_t)n * n + 255) / 256);
     hipLaunchKernelGGL(gram_to_mat_kernel, dim3(gb, batch), dim3(256), 0, s, a.partial, a.chunks, lp, n, w.A);
     hipError_t e = hipGetLastError();

@@ -306,42 +306,40 @@ struct ReduceGroups {
 };
 hipError_t launch_reduce_splits_grouped(const ReduceGroups& g, hipStream_t s);
 
-// Fixed number of length-chunk slots of the fp64 Gram partial sums (unused
-// slots hold zeros); its consumers always add all of them.
+// Largest number of length-chunk slots of the fp64 Gram partial sums.
 constexpr int kGramChunks = 16;
 
 // fp64 Gram of the rows of l-major fp32 matrices V (l_pad x len each):
-// partial[z][chunk][c][d] = sum_{j in chunk} V[c][j] V[d][j], upper tiles.
-// Every launch writes all kGramChunks chunk slots of chunk_len (slots past
-// len hold zeros).
+// partial[z][slot][c][d] = sum_{j in slot} V[c][j] V[d][j], the upper 16 x 16
+// tiles.  Every launch writes all `chunks` slots (gram64_slots, a multiple of 4).
 struct Gram64Items {
     int n;
     int ell;                                     // rows of each matrix that enter the Gram
+    int chunks;
     int zbeg[kMaxItems + 1];
     const float* v[kMaxItems];
     int64_t ld[kMaxItems];
     int64_t stride[kMaxItems];
     int64_t len[kMaxItems];
-    int chunk_len[kMaxItems];
 };
 hipError_t launch_gram64(const Gram64Items& t, int ell_pad, double* partial, hipStream_t s);
-// Element (c, d) of the summed Gram (full symmetric view of the upper 64 x 64
-// tiles gram64 writes): the kGramChunks partial sums are all requested
-// before any is added, so one memory latency covers the element; they are
-// added in chunk order.
-__device__ __forceinline__ double gram_at(const double* p, int ell_pad, int c, int d) {
-    if ((c >> 6) > (d >> 6)) { const int t = c; c = d; d = t; }
+int gram64_slots(int ell, int count, int64_t max_len);
+// Element (c, d) of the summed Gram (full symmetric view of the upper tiles
+// gram64 writes), added in slot order with four slots' loads in flight.
+__device__ __forceinline__ double gram_at(const double* p, int ell_pad, int c, int d, int chunks) {
+    if ((c >> 4) > (d >> 4)) { const int t = c; c = d; d = t; }
     const double* q = p + (int64_t)c * ell_pad + d;
     const int64_t cs = (int64_t)ell_pad * ell_pad;
-    double v[kGramChunks];
-#pragma unroll
-    for (int k = 0; k < kGramChunks; ++k) v[k] = q[k * cs];
     double s = 0.0;
+    for (int k = 0; k < chunks; k += 4) {
+        double v[4];
 #pragma unroll
-    for (int k = 0; k < kGramChunks; ++k) s += v[k];
+        for (int u = 0; u < 4; ++u) v[u] = q[(k + u) * cs];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += v[u];
+    }
     return s;
 }
-int gram64_chunks(int64_t len, int chunk_len);
 
 // Cholesky (with dropping of numerically dependent columns) of the summed
 // Gram, then R^{-1}; writes fp32 Rinv (l_pad x l_pad, zero padded).

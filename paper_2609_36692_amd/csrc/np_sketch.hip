@@ -123,110 +123,106 @@ __device__ __forceinline__ int item_of(const T& t, int z) {
     return g;
 }
 
-// 64 x 64 output tile (tc <= td) over one chunk of the length dimension, in
-// 4 x 4 register blocks, one per thread, only those with rows and columns
-// below l, and on a diagonal tile only the upper ones (written to both
-// triangles): waves without a block skip the products, so padding and
-// symmetry cost no fp64 FMAs.  The tile's rows stream through LDS 64 columns
-// at a time (columns major, so a thread reads its four rows as one float4).
-// Every entry sums in a fixed order; chunks past the item's length write
-// zeros.  Lengths and chunk lengths are multiples of 64.
-__global__ void __launch_bounds__(256) gram64_kernel(Gram64Items t, int ell_pad, double* partial) {
-    const int z = blockIdx.z, chunk = blockIdx.y;
+// fp64 Gram by v_mfma_f64_16x16x4: lane (i, q) = (lane % 16, lane / 16) supplies
+// row i, k = q of the A operand and column i, k = q of the B operand, and receives
+// rows q + 4 r, column i of the product (registers r).  Both operands are rows
+// of the same V in the same form, so a 16-column run of V is one float4 per
+// lane and operand, converted to fp64 and used as four k-steps (element e of
+// the float4 as step e: any order of k serves), with no LDS.  A block takes
+// three of the upper 16 x 16 tiles (their count is a multiple of three for most
+// l) in each of its eight waves, every wave a part of the length, summed
+// through LDS in the order of the parts; the grid adds `chunks` slots of parts
+// and the groups of tiles.  Short blocks, since the lengths of one launch differ
+// up to eleven times (one block of all tiles with longer parts left CUs with
+// two long blocks each).  Bound by the fp64 matrix rate and the blocks' start and
+// reduction.  112 matrices of l = 72 and 512 to 5632 columns: 195 -> 86 us per
+// launch; 48 of l = 40: 26 -> 19 us; one of l = 264 and 16384 columns: 64 -> 29
+// us; one of l = 24: 10 -> 4.6 us (before: fp64 FMAs on 64 x 64 tiles in LDS).
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kGramWaves = 8, kGramTiles = 3;
+
+__global__ void __launch_bounds__(64 * kGramWaves) gram64_kernel(Gram64Items t, int ell_pad, double* partial) {
+    __shared__ double red[kGramWaves][kGramTiles * 4][64];
+    const int z = blockIdx.z, slot = blockIdx.y;
     const int g = item_of(t, z);
     const int64_t ld = t.ld[g], len = t.len[g];
-    const int chunk_len = t.chunk_len[g], ell = t.ell;
-    const int tiles = ell_pad / 64;
-    int tc = 0, left = blockIdx.x;
-    while (left >= tiles - tc) { left -= tiles - tc; ++tc; }
-    const int td = tc + left;
-    const bool diag = tc == td;
-    __shared__ float sc[64][68], sd[64][68];
-    float (*sb)[68] = diag ? sc : sd;
-    const int tid = threadIdx.x;
-    // This thread's block (bi, bj): row blocks of 4 below l in each tile.
-    // When the tile has few blocks (small l), `split` adjacent lanes share a
-    // block, each taking every split-th column of a slab, and their sums are
-    // combined by shuffles at the end (a fixed order).
-    const int nbc = min(16, (ell - 64 * tc + 3) / 4), nbd = min(16, (ell - 64 * td + 3) / 4);
-    const int nact = diag ? nbc * (nbc + 1) / 2 : nbc * nbd;
-    int split = 1;
-    while (split < 8 && nact * split * 2 <= 256) split *= 2;
-    const int blk = tid / split, part = tid - blk * split;
-    int bi = -1, bj = -1;
-    if (diag) {
-        int w = blk, r = 0;
-        while (r < nbc && w >= nbc - r) { w -= nbc - r; ++r; }
-        if (r < nbc) { bi = r; bj = r + w; }
-    } else if (blk < nact) {
-        bi = blk / nbd;
-        bj = blk - bi * nbd;
+    const int ell = t.ell, nb = (ell + 15) / 16, nt = nb * (nb + 1) / 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int row = lane & 15, q = lane >> 4;
+    const int t0 = blockIdx.x * kGramTiles;
+    // Tile (r, c) of each of this wave's tiles, in row-major upper order.
+    int tr[kGramTiles], tc[kGramTiles];
+    {
+        int w = min(t0, nt - 1), r = 0;
+        while (w >= nb - r) { w -= nb - r; ++r; }
+        int c = r + w;
+#pragma unroll
+        for (int u = 0; u < kGramTiles; ++u) {
+            tr[u] = r;
+            tc[u] = c;
+            if (t0 + u + 1 < nt && ++c == nb) { ++r; c = r; }
+        }
     }
-    const float* vz = t.v[g] + (int64_t)(z - t.zbeg[g]) * t.stride[g];
-    double acc[4][4];
+    const int parts = t.chunks * kGramWaves;
+    const int64_t part_len = (len / 16 + parts - 1) / parts * 16;
+    const int64_t j0 = (int64_t)(slot * kGramWaves + wave) * part_len, j1 = min(len, j0 + part_len);
+    const float* v = t.v[g] + (int64_t)(z - t.zbeg[g]) * t.stride[g];
+    const float* pa[kGramTiles];
+    const float* pb[kGramTiles];
+    float ma[kGramTiles], mb[kGramTiles];   // 0 for rows past l
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < kGramTiles; ++u) {
+        const int ra = 16 * tr[u] + row, rb = 16 * tc[u] + row;
+        pa[u] = v + (int64_t)min(ra, ell - 1) * ld + 4 * q;
+        pb[u] = v + (int64_t)min(rb, ell - 1) * ld + 4 * q;
+        ma[u] = ra < ell ? 1.f : 0.f;
+        mb[u] = rb < ell ? 1.f : 0.f;
+    }
+    f64x4 acc[kGramTiles];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[u][e] = 0.0;
-    const int64_t j0 = (int64_t)chunk * chunk_len, j1 = min(len, j0 + chunk_len);
-    const int lr = tid >> 2, lc = (tid & 3) * 16;
-    const bool rc = 64 * tc + lr < ell, rd = 64 * td + lr < ell;
-    // The next slab's global loads are in flight during this slab's FMAs.
-    float4 a[4], b[4];
-    auto gload = [&](int64_t jb) {
-        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int u = 0; u < kGramTiles; ++u) acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+    float4 a[kGramTiles], b[kGramTiles];
+    auto load = [&](int64_t j) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            a[u] = rc ? *(const float4*)(vz + (int64_t)(64 * tc + lr) * ld + jb + lc + 4 * u) : zero;
-            b[u] = !diag && rd ? *(const float4*)(vz + (int64_t)(64 * td + lr) * ld + jb + lc + 4 * u) : zero;
+        for (int u = 0; u < kGramTiles; ++u) {
+            a[u] = *(const float4*)(pa[u] + j);
+            b[u] = *(const float4*)(pb[u] + j);
         }
     };
-    if (j0 < j1) gload(j0);
-    for (int64_t jb = j0; jb < j1; jb += 64) {
+    if (j0 < j1) load(j0);
+    for (int64_t j = j0; j < j1; j += 16) {
+        float4 ca[kGramTiles], cb[kGramTiles];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            sc[lc + 4 * u][lr] = a[u].x;
-            sc[lc + 4 * u + 1][lr] = a[u].y;
-            sc[lc + 4 * u + 2][lr] = a[u].z;
-            sc[lc + 4 * u + 3][lr] = a[u].w;
-            if (!diag) {
-                sd[lc + 4 * u][lr] = b[u].x;
-                sd[lc + 4 * u + 1][lr] = b[u].y;
-                sd[lc + 4 * u + 2][lr] = b[u].z;
-                sd[lc + 4 * u + 3][lr] = b[u].w;
-            }
+        for (int u = 0; u < kGramTiles; ++u) {
+            ca[u] = a[u];
+            cb[u] = b[u];
         }
-        __syncthreads();
-        if (jb + 64 < j1) gload(jb + 64);
-        if (bi >= 0) {
-#pragma unroll 4
-            for (int jj = part; jj < 64; jj += split) {
-                const float4 xa = *(const float4*)&sc[jj][4 * bi];
-                const float4 xb = *(const float4*)&sb[jj][4 * bj];
-                const double av[4] = {xa.x, xa.y, xa.z, xa.w}, bv[4] = {xb.x, xb.y, xb.z, xb.w};
+        if (j + 16 < j1) load(j + 16);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[u][e] = fma(av[u], bv[e], acc[u][e]);
+            for (int u = 0; u < kGramTiles; ++u) {
+                const float xa = e == 0 ? ca[u].x : e == 1 ? ca[u].y : e == 2 ? ca[u].z : ca[u].w;
+                const float xb = e == 0 ? cb[u].x : e == 1 ? cb[u].y : e == 2 ? cb[u].z : cb[u].w;
+                acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(ma[u] != 0.f ? xa : 0.f),
+                                                              (double)(mb[u] != 0.f ? xb : 0.f), acc[u], 0, 0, 0);
             }
-        }
-        __syncthreads();
     }
-    // The split lanes of a block are adjacent in one wave (split divides 64).
-    for (int o = 1; o < split; o <<= 1)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < kGramTiles; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[u][e] += __shfl_xor(acc[u][e], o, 64);
-    if (bi < 0 || part != 0) return;
-    double* out = partial + ((int64_t)z * kGramChunks + chunk) * ell_pad * ell_pad;
-    const int r0 = 64 * tc + 4 * bi, c0 = 64 * td + 4 * bj;
+        for (int r = 0; r < 4; ++r) red[wave][4 * u + r][lane] = acc[u][r];
+    __syncthreads();
+    double* out = partial + ((int64_t)z * t.chunks + slot) * ell_pad * ell_pad;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < kGramTiles; ++u)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            out[(int64_t)(r0 + u) * ell_pad + c0 + e] = acc[u][e];
-            if (diag) out[(int64_t)(c0 + e) * ell_pad + r0 + u] = acc[u][e];
+        for (int r = 0; r < 4; ++r) {
+            if ((4 * u + r) % kGramWaves != wave || t0 + u >= nt) continue;
+            double sum = 0.0;
+#pragma unroll
+            for (int k = 0; k < kGramWaves; ++k) sum += red[k][4 * u + r][lane];
+            out[(int64_t)(16 * tr[u] + q + 4 * r) * ell_pad + 16 * tc[u] + row] = sum;
         }
 }
 
@@ -269,6 +265,7 @@ constexpr int kSmallThreads = 512;
 // thread); 112 of l = 72 34 us and 22 us for the chunk sums (137 us); one of
 // l = 264 in its two-level form 0.2 ms in all (0.73 ms in row panels).
 constexpr int kCholG = 16;
+constexpr int kGramSum = 4;
 constexpr int kCholThreads = kCholG * kCholG;
 template <int T>
 struct CholRegs {
@@ -354,18 +351,19 @@ __device__ __forceinline__ void chol_columns(CholRegs<T>& r, CholShared& sh, int
 // rest of rinv, else it is read from src (ld ell_pad); the diagonal that the
 // dropping test compares with is always the Gram's own.  x64, when given,
 // receives R^{-1} (upper triangle) in fp64.  Entries past ell but inside
-// ell_pad are loaded and discarded, so the loads need no branches.
+// ell_pad are loaded and discarded, so the loads need no branches.  SUM takes
+// kGramSum slots.
 template <int T, bool SUM>
 __global__ void __launch_bounds__(kCholThreads) chol_reg_kernel(const double* src, int64_t stride, int ell,
-                                                                int ell_pad, const double* partial, int off,
-                                                                double* x64, int64_t stride_x, float* rinv) {
+                                                                int ell_pad, const double* partial, int chunks,
+                                                                int off, double* x64, int64_t stride_x, float* rinv) {
     __shared__ CholShared sh;
     const int z = blockIdx.x, tid = threadIdx.x, ti = tid / kCholG, tj = tid % kCholG;
-    const double* part = partial + (int64_t)z * kGramChunks * ell_pad * ell_pad;
+    const double* part = partial + (int64_t)z * chunks * ell_pad * ell_pad;
     const double* p = SUM ? part : src + (int64_t)z * stride;
     CholRegs<T> r;
     for (int q = tid; q < 2 * 2 * 2 * kCholRegMax; q += kCholThreads) (&sh.row[0][0][0])[q] = 0.0;
-    if (tid <= kCholRegMax) sh.diag0[tid] = !SUM && tid < ell ? gram_at(part, ell_pad, off + tid, off + tid) : 0.0;
+    if (tid <= kCholRegMax) sh.diag0[tid] = !SUM && tid < ell ? gram_at(part, ell_pad, off + tid, off + tid, chunks) : 0.0;
     __syncthreads();
 #pragma unroll
     for (int a = 0; a < T; ++a) {
@@ -376,11 +374,11 @@ __global__ void __launch_bounds__(kCholThreads) chol_reg_kernel(const double* sr
             double v = 0.0;
             const double* q = p + (int64_t)c * ell_pad + d;
             if constexpr (SUM) {
-                double w[kGramChunks];
+                double w[kGramSum];
 #pragma unroll
-                for (int u = 0; u < kGramChunks; ++u) w[u] = q[(int64_t)u * ell_pad * ell_pad];
+                for (int u = 0; u < kGramSum; ++u) w[u] = q[(int64_t)u * ell_pad * ell_pad];
 #pragma unroll
-                for (int u = 0; u < kGramChunks; ++u) v += w[u];
+                for (int u = 0; u < kGramSum; ++u) v += w[u];
             } else {
                 v = q[0];
             }
@@ -433,14 +431,14 @@ __global__ void __launch_bounds__(kCholThreads) chol_reg_kernel(const double* sr
 // Dense G (upper triangle, ld ell_pad) from the chunk partials in many blocks;
 // zeros in the lower triangle of x (R^{-1} in fp64) and in the entries of rinv
 // outside the upper triangle.
-__global__ void __launch_bounds__(256) chol_sum_kernel(const double* partial, int ell, int ell_pad, double* g,
+__global__ void __launch_bounds__(256) chol_sum_kernel(const double* partial, int chunks, int ell, int ell_pad, double* g,
                                                        double* x, int64_t stride, float* rinv) {
     const int z = blockIdx.y, q = blockIdx.x * 256 + threadIdx.x;
     if (q >= ell_pad * ell_pad) return;
     const int i = q / ell_pad, j = q - (q / ell_pad) * ell_pad;
-    const double* p = partial + (int64_t)z * kGramChunks * ell_pad * ell_pad;
+    const double* p = partial + (int64_t)z * chunks * ell_pad * ell_pad;
     if (i <= j && j < ell) {
-        g[(int64_t)z * stride + q] = gram_at(p, ell_pad, i, j);
+        g[(int64_t)z * stride + q] = gram_at(p, ell_pad, i, j, chunks);
     } else {
         x[(int64_t)z * stride + q] = 0.0;
         rinv[(int64_t)z * ell_pad * ell_pad + q] = 0.f;
@@ -672,7 +670,7 @@ __global__ void __launch_bounds__(kSmallThreads) eig_select_kernel(EigArgs a) {
     const double* part = a.partial + (int64_t)z * a.chunks * lp * lp;
     for (int q = tid; q < n * n; q += NT) {
         const int c = q / n, d = q - (q / n) * n;
-        A[c * ld + d] = (float)gram_at(part, lp, c, d);
+        A[c * ld + d] = (float)gram_at(part, lp, c, d, a.chunks);
         Z[c * ld + d] = c == d ? 1.f : 0.f;
     }
     __syncthreads();
@@ -802,7 +800,7 @@ __global__ void __launch_bounds__(kSmallThreads) eig_select_packed_kernel(EigArg
     const double* part = a.partial + (int64_t)z * a.chunks * lp * lp;
     for (int q = tid; q < n * n; q += NT) {
         const int c = q / n, d = q - (q / n) * n;
-        if (c <= d) A[pk(c, d, n)] = (float)gram_at(part, lp, c, d);
+        if (c <= d) A[pk(c, d, n)] = (float)gram_at(part, lp, c, d, a.chunks);
         Zt[(int64_t)c * lp + d] = c == d ? 1.f : 0.f;
     }
     __syncthreads();
@@ -999,7 +997,7 @@ __global__ void __launch_bounds__(NT) eig_select_rr_kernel(EigArgs a) {
     const double* part = a.partial + (int64_t)z * a.chunks * lp * lp;
     for (int q = tid; q < n * ld; q += NT) {
         const int c = q / ld, d = q - (q / ld) * ld;
-        Ac[q] = d < n ? (float)gram_at(part, lp, c, d) : 0.f;
+        Ac[q] = d < n ? (float)gram_at(part, lp, c, d, a.chunks) : 0.f;
         Z[q] = c == d ? 1.f : 0.f;
     }
     const int n2 = n + (n & 1), n1 = n2 - 1, npairs = n2 / 2;
@@ -1188,51 +1186,60 @@ hipError_t launch_reduce_splits_grouped(const ReduceGroups& g, hipStream_t s) {
     return hipGetLastError();
 }
 
-int gram64_chunks(int64_t len, int chunk_len) { return (int)((len + chunk_len - 1) / chunk_len); }
+// Slots of the partial sums: 4 (32 parts of the length), or 16 for few long
+// matrices, whose parts' chains would leave the chip idle.
+static int gram_groups(int ell) {
+    const int nb = (ell + 15) / 16;
+    return (nb * (nb + 1) / 2 + kGramTiles - 1) / kGramTiles;
+}
+int gram64_slots(int ell, int count, int64_t max_len) {
+    return (int64_t)count * gram_groups(ell) * 4 * kGramWaves < 1024 && max_len > 4096 ? kGramChunks : 4;
+}
 
 hipError_t launch_gram64(const Gram64Items& t, int ell_pad, double* partial, hipStream_t s) {
-    if (ell_pad % 64 || t.ell < 1 || t.ell > ell_pad || t.n < 1 || t.n > kMaxItems || t.zbeg[0] != 0)
+    if (ell_pad % 64 || t.ell < 1 || t.ell > ell_pad || t.n < 1 || t.n > kMaxItems || t.zbeg[0] != 0 ||
+        t.chunks < 1 || t.chunks > kGramChunks)
         return hipErrorInvalidValue;
     for (int g = 0; g < t.n; ++g)
-        if (t.chunk_len[g] % 64 || t.len[g] % 64 || t.ld[g] % 4 ||
-            gram64_chunks(t.len[g], t.chunk_len[g]) > kGramChunks || t.zbeg[g + 1] <= t.zbeg[g])
-            return hipErrorInvalidValue;
-    const int tiles = ell_pad / 64;
-    dim3 grid(tiles * (tiles + 1) / 2, kGramChunks, t.zbeg[t.n]);
-    hipLaunchKernelGGL(gram64_kernel, grid, dim3(256), 0, s, t, ell_pad, partial);
+        if (t.len[g] % 16 || t.ld[g] % 4 || t.stride[g] % 4 || t.zbeg[g + 1] <= t.zbeg[g]) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gram64_kernel, dim3(gram_groups(t.ell), t.chunks, t.zbeg[t.n]), dim3(64 * kGramWaves), 0, s, t,
+                       ell_pad, partial);
     return hipGetLastError();
 }
 
 hipError_t launch_chol_inv(const double* partial, int chunks, int ell, int ell_pad, double* scratch, float* rinv,
                            int batch, hipStream_t s) {
-    if (ell < 1 || ell > 384 || ell_pad < ell || ell_pad > 384 || chunks != kGramChunks) return hipErrorInvalidValue;
+    if (ell < 1 || ell > 384 || ell_pad < ell || ell_pad > 384 || chunks < 1 || chunks > kGramChunks)
+        return hipErrorInvalidValue;
     const int64_t lp2 = (int64_t)ell_pad * ell_pad, ld = ell_pad;
-    // Up to 64 the workgroup sums the chunk partials itself (16 of them per
-    // entry, all in flight); above, many blocks do in a launch of their own.
-    if (ell <= 64) {
+    // Up to 96 the workgroup sums few slots itself, its loads all in flight;
+    // otherwise many blocks do in a launch of their own.
+    if (ell <= 96 && chunks == kGramSum) {
         auto run = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3(batch), dim3(kCholThreads), 0, s, (const double*)nullptr, (int64_t)0, ell,
-                               ell_pad, partial, 0, (double*)nullptr, (int64_t)0, rinv);
+                               ell_pad, partial, chunks, 0, (double*)nullptr, (int64_t)0, rinv);
         };
         switch ((ell + kCholG - 1) / kCholG) {
             case 1: run(chol_reg_kernel<1, true>); break;
             case 2: run(chol_reg_kernel<2, true>); break;
             case 3: run(chol_reg_kernel<3, true>); break;
-            default: run(chol_reg_kernel<4, true>); break;
+            case 4: run(chol_reg_kernel<4, true>); break;
+            case 5: run(chol_reg_kernel<5, true>); break;
+            default: run(chol_reg_kernel<6, true>); break;
         }
         return hipGetLastError();
     }
     // scratch per matrix: G, then X = R^{-1} (ell_pad^2 doubles each).
     const int64_t st = 2 * lp2;
     double *G = scratch, *X = scratch + lp2;
-    hipLaunchKernelGGL(chol_sum_kernel, dim3((unsigned)((lp2 + 255) / 256), batch), dim3(256), 0, s, partial, ell,
-                       ell_pad, G, X, st, rinv);
+    hipLaunchKernelGGL(chol_sum_kernel, dim3((unsigned)((lp2 + 255) / 256), batch), dim3(256), 0, s, partial, chunks,
+                       ell, ell_pad, G, X, st, rinv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     auto factor = [&](int off, int n, const double* src, bool x64) {
         auto run = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3(batch), dim3(kCholThreads), 0, s, src, st, n, ell_pad, partial, off,
-                               x64 ? X + off * (ld + 1) : nullptr, st, rinv + off * (ld + 1));
+            hipLaunchKernelGGL(kern, dim3(batch), dim3(kCholThreads), 0, s, src, st, n, ell_pad, partial, chunks,
+                               off, x64 ? X + off * (ld + 1) : nullptr, st, rinv + off * (ld + 1));
         };
         switch ((n + 2 * kCholG - 1) / (2 * kCholG)) {
             case 1: run(chol_reg_kernel<2, false>); break;
@@ -1285,7 +1292,7 @@ hipError_t launch_small_mul(const SmallMulArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_eig_select(const EigArgs& a, int batch, hipStream_t s) {
-    if (a.ell > 384 || a.ell_pad > 384 || a.chunks != kGramChunks) return hipErrorInvalidValue;
+    if (a.ell > 384 || a.ell_pad > 384 || a.chunks < 1 || a.chunks > kGramChunks) return hipErrorInvalidValue;
     if (a.ell <= kEigRRMax) {
         const size_t lds = (size_t)3 * a.ell * (a.ell + 1) * sizeof(float);
         if (a.ell <= 64)
