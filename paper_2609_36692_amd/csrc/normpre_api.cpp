@@ -26,16 +26,15 @@ constexpr int64_t kMaxDim = int64_t(1) << 20;
 constexpr int64_t kMaxElems = int64_t(1) << 31;
 constexpr int kMaxRowLen = 32768;   // row-active register kernel limit
 constexpr int kMaxEll = 384;
-// Widths of Gamma_Q above this go to the dense eigensolver (tridiagonal
-// reduction, bisection, inverse iteration) instead of the Jacobi kernels.
-constexpr int kEigJacobiMax = 104;
+// Up to this width the dense eigensolver's workspace for Gamma_Q fits buffers
+// of the pool that are idle by then.
+constexpr int kEigAliasMax = 104;
 // Exact NormPre-L above kMaxEll active rows: dense fp64 eigensolver on the
 // a x a interaction matrix (tridiagonal reduction, bisection, inverse
 // iteration), up to this many active rows.
 constexpr int64_t kMaxExactRows = 8192;
 constexpr int kColRowChunk = 128;   // rows per block in the column-active pass
 constexpr int kMaxSplits = 16;
-constexpr int kEigSweeps = 30;
 // NormPre-L: largest share of ||Psi||_F^2 in the selected modes for which
 // ||T||_F^2 is taken in closed form (see sketch_back).
 constexpr float kClosedNormFrac = 0.25f;
@@ -476,7 +475,7 @@ struct Pool {
     float* ritz = nullptr;
     int* nsel = nullptr;
     std::vector<EigGroup> eig;
-    // Ritz pairs through the dense eigensolver (l > kEigJacobiMax)
+    // Ritz pairs through the dense eigensolver (l > ritz_small_max())
     TriWork tw{};
     double* lam = nullptr;
     float* zbuf = nullptr;
@@ -569,15 +568,32 @@ void carve_pool(Arena& ar, Pool& p, int variant) {
         p.eigs = ar.take<float>(c * 2 * lp * lp);
         p.ritz = ar.take<float>(c * (int64_t)p.top);
         p.nsel = ar.take<int>(c);
-        if (p.ell > kEigJacobiMax) {
+        if (p.ell > ritz_small_max()) {
             const int64_t n = p.ell, top = p.top;
-            p.tw = carve_tri(ar, c, n, top);
-            // The Cholesky scratch (2 l_pad^2 doubles, l_pad >= 128) is dead
-            // by the time the reflectors' WY factors are formed.
-            p.tw.wy = p.chol;
-            p.tw.stride_wy = 2 * lp * lp;
-            p.lam = ar.take<double>(c * top);
-            p.zbuf = ar.take<float>(c * top * n);
+            if (p.ell <= kEigAliasMax) {
+                // The matrix and the small vectors in `eigs` (2 l_pad^2 floats
+                // per matrix), the eigenvectors after the WY factors in the
+                // Cholesky scratch: l_pad = 128 holds n = 104 of both.
+                Arena e{reinterpret_cast<char*>(p.eigs), 0, 0}, y{reinterpret_cast<char*>(p.chol), 0, 0};
+                p.tw.wy = y.take<double>(c * wy_doubles(n));
+                p.tw.stride_wy = wy_doubles(n);
+                p.tw.y = y.take<double>(c * top * n);
+                p.tw.A = e.take<float>(c * n * n);
+                p.tw.vec = e.take<double>(c * 4 * n);
+                p.tw.d = e.take<double>(c * n);
+                p.tw.e = e.take<double>(c * n);
+                p.tw.tau = e.take<double>(c * n);
+                p.lam = e.take<double>(c * top);
+                p.zbuf = e.take<float>(c * top * n);
+            } else {
+                p.tw = carve_tri(ar, c, n, top);
+                // The Cholesky scratch (2 l_pad^2 doubles, l_pad >= 128) is
+                // dead by the time the reflectors' WY factors are formed.
+                p.tw.wy = p.chol;
+                p.tw.stride_wy = 2 * lp * lp;
+                p.lam = ar.take<double>(c * top);
+                p.zbuf = ar.take<float>(c * top * n);
+            }
         }
         for (EigGroup& g : p.eig) {
             g.gam32 = ar.take<float>(g.count * g.npad * g.npad);
@@ -1805,12 +1821,11 @@ int run_round_l(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
         EigArgs ea{};
         ea.partial = pl.gpart; ea.chunks = pl.gslots;
         ea.ell = pl.ell; ea.ell_pad = pl.ellp; ea.rank = sc.hp->rank;
-        ea.scratch = pl.eigs; ea.kmat = pl.kmat;
+        ea.kmat = pl.kmat;
         ea.ritz = pl.ritz; ea.ritz_stride = pl.top; ea.nsel = pl.nsel;
-        ea.max_sweeps = kEigSweeps;
         NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
                      [&] {
-                         return pl.ell > kEigJacobiMax
+                         return pl.ell > ritz_small_max()
                                     ? launch_eig_select_dense(ea, pl.tw, pl.lam, pl.zbuf, pl.count, sc.s)
                                     : launch_eig_select(ea, pl.count, sc.s);
                      }),

@@ -13,13 +13,14 @@
 //     blocks of 32 (compact WY form).
 // Used by the exact variant of NormPre-L (App. B, exact eigenspace
 // extraction: the leading eigenvectors of Gamma span the selected modes), by
-// the Rayleigh-Ritz problems of the sketch wider than the Jacobi's limit,
+// the Rayleigh-Ritz problems of the sketch (one workgroup each up to l = 80),
 // and by the spectral diagnostics of the normalized and unnormalized Grams
 // (App. A, spectral dynamics).  Matrices of one launch share n (grid y).
 #include "np_internal.h"
 
 #include <algorithm>
 #include <cfloat>
+#include <type_traits>
 
 namespace np {
 namespace {
@@ -70,19 +71,13 @@ __device__ __forceinline__ double swap16_add(double a, double b) {
     const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
     return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
 }
-// The same over lane bit 3 (row_ror:8) and bit 2 (row_half_mirror, which
-// also flips bits 0 and 1: the remaining steps sum over those).  A lane sends
-// the value its partner keeps.
+// The same over the lower lane bits by DPP (row_ror:8 flips bit 3;
+// row_half_mirror bits 2, 1 and 0, of which the lower two are summed over
+// afterwards; quad_perm bits 1 and 0).  A lane sends the value its partner keeps.
 template <int CTRL>
 __device__ __forceinline__ double swap_dpp_add(double a, double b, bool upper) {
     const double keep = upper ? b : a, send = upper ? a : b;
     return keep + dpp_take<CTRL, 0xf>(send);
-}
-__device__ __forceinline__ double swap8_add(double a, double b, int lane) {
-    return swap_dpp_add<0x128>(a, b, lane & 8);
-}
-__device__ __forceinline__ double swap4_add(double a, double b, int lane) {
-    return swap_dpp_add<0x141>(a, b, lane & 4);
 }
 __device__ __forceinline__ double sum_quad(double v) {
     v += dpp_take<0x4e, 0xf>(v);    // quad_perm [2,3,0,1]
@@ -96,6 +91,45 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+constexpr int kDppBit3 = 0x128, kDppBit2 = 0x141, kDppBit1 = 0x4e, kDppBit0 = 0xb1;
+
+// N values per lane summed over the 32 lanes of each half wave (W = 32) or over
+// the wave (W = 64): every exchange halves the values a lane carries.  The
+// lanes end with the sum of value `slot` (none where slot >= N); of the lanes
+// that share one, `first` is set in the first.
+template <int W, int BIT, int N>
+__device__ __forceinline__ double sum_values(const double (&v)[N], int lane, int& slot, bool& first) {
+    constexpr int H = (N + 1) / 2;
+    const bool up = lane & BIT;
+    if constexpr (BIT == 0) {
+        return v[0];
+    } else if constexpr (N == 1) {
+        double r[1];
+        if constexpr (BIT == 32) r[0] = swap32_add(v[0], v[0]);
+        else if constexpr (BIT == 16) r[0] = swap16_add(v[0], v[0]);
+        else r[0] = v[0] + dpp_take<BIT == 8 ? kDppBit3 : BIT == 4 ? kDppBit2 : BIT == 2 ? kDppBit1 : kDppBit0, 0xf>(v[0]);
+        first = first && !up;
+        return sum_values<W, BIT / 2, 1>(r, lane, slot, first);
+    } else {
+        double r[H];
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const double a = v[i], b = i + H < N ? v[i + H < N ? i + H : i] : 0.0;
+            if constexpr (BIT == 32) r[i] = swap32_add(a, b);
+            else if constexpr (BIT == 16) r[i] = swap16_add(a, b);
+            else r[i] = swap_dpp_add<BIT == 8 ? kDppBit3 : BIT == 4 ? kDppBit2 : BIT == 2 ? kDppBit1 : kDppBit0>(a, b, up);
+        }
+        slot += up ? H : 0;
+        return sum_values<W, BIT / 2, H>(r, lane, slot, first);
+    }
+}
+template <int W, int N>
+__device__ __forceinline__ double sum_values(const double (&v)[N], int lane, int& slot, bool& first) {
+    slot = 0;
+    first = true;
+    return sum_values<W, W / 2, N>(v, lane, slot, first);
 }
 
 // Sum over the block in a fixed order (every thread returns the same value).
@@ -183,8 +217,7 @@ __global__ void __launch_bounds__(NT) tri_step_kernel(float* A, int64_t strideA,
                                                       int64_t stride_vec, double* dd, double* ee, double* tau,
                                                       int64_t stride_n) {
     constexpr int NW = NT / 64;
-    __shared__ double red1[NW], red2[NW], redp[2][NW][8];
-    static_assert(RB == 8 || RB == 4 || RB == 2, "rows per pass");
+    __shared__ double red1[NW], red2[NW], redp[2][NW][RB];
     const int z = blockIdx.y, nb = gridDim.x, x = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool first = j == 0;
@@ -283,10 +316,10 @@ __global__ void __launch_bounds__(NT) tri_step_kernel(float* A, int64_t strideA,
     }
     int par = 0;
     for (int i = i0; i < n; i += RB * nb, par ^= 1) {
-        double dot[8];
+        double dot[RB];
         const double wl = pl - K * vl;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) dot[r] = 0.0;
+        for (int r = 0; r < RB; ++r) dot[r] = 0.0;
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             const int ir = i + r * nb;
@@ -305,17 +338,10 @@ __global__ void __launch_bounds__(NT) tri_step_kernel(float* A, int64_t strideA,
             load_tile(i + RB * nb);
             load_scalars(i + RB * nb);
         }
-        // Eight dots over 64 lanes: each exchange halves the values a lane
-        // carries, lane bits 5, 4, 3 ending up as the row.
-        double q[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) q[r] = swap32_add(dot[r], dot[r + 4]);
-        q[0] = swap16_add(q[0], q[2]);
-        q[1] = swap16_add(q[1], q[3]);
-        double d = swap8_add(q[0], q[1], lane);
-        d += dpp_take<0x141, 0xf>(d);
-        d = sum_quad(d);
-        if ((lane & 7) == 0) redp[par][wave][((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1)] = d;
+        int rs;
+        bool first_lane;
+        const double d = sum_values<64>(dot, lane, rs, first_lane);
+        if (first_lane) redp[par][wave][rs] = d;
         lds_barrier();
         if (tid < RB) {
             double s = 0.0;
@@ -329,13 +355,13 @@ __global__ void __launch_bounds__(NT) tri_step_kernel(float* A, int64_t strideA,
 
 // Householder tridiagonalization of the trailing m x m block (m = n - j0 <=
 // kTriRegMax) of one matrix per workgroup, the block in registers: thread
-// (wave w, lane) holds the rows 32 s + 2 w + (lane >> 5) and the columns
-// 32 c + (lane & 31), s, c < 8, in fp32 (all arithmetic fp64).  Per column: the
+// (wave w, lane) holds the rows 16 s + 2 w + (lane >> 5), s < 16, and the columns
+// 32 c + (lane & 31), c < 8, in fp32 (all arithmetic fp64).  Per column: the
 // wave that owns row jj (= column jj) forms the reflector from its own
-// registers; p = tau M v as eight dots per thread, summed over the 32 column
-// lanes by halving exchanges; w = p - (tau/2)(p^T v) v; then the rank-2 update
+// registers; p = tau M v as up to sixteen dots per thread, summed over the 32
+// column lanes by halving exchanges; w = p - (tau/2)(p^T v) v; then the rank-2 update
 // in registers.  Two barriers per column (v and p alternate between two LDS
-// buffers).  The column loop is unrolled over the 32-row slots, so finished
+// buffers).  The column loop is unrolled over the 16-row slots, so finished
 // rows and columns drop out at compile time.  2.4 us per column, fp64 issue and
 // the chain of the reflector about equal (with the block in LDS, up to 192
 // columns, the same reduction took 8.4 us per column).
@@ -343,38 +369,46 @@ __global__ void __launch_bounds__(NT) tri_step_kernel(float* A, int64_t strideA,
 // the rank-2 update of column j0 - 1 pending (its reflector and p = tau A v in
 // `vec`): the block is loaded with that update applied.
 constexpr int kTriRegMax = 256;
-constexpr int kTriThreads = 1024;
+constexpr int kTriWaves = 8, kTriThreads = 64 * kTriWaves, kTriSlots = kTriRegMax / (2 * kTriWaves);
 
+template <int C>
 struct TriRegShared {
-    double v[2][kTriRegMax], p[2][kTriRegMax], t[2];
+    double v[2][32 * C], p[2][32 * C], t[2];
 };
 
-// The columns 32 S0 .. 32 S0 + 31 of the block; dd, ee, tau and Ag (the block in
-// A, row stride n) start at the block's first column.
-template <int S0>
-__device__ __forceinline__ void tri_reg_cols(float (&M)[8][8], TriRegShared& sh, int& par, int m, float* Ag, int n,
+// The columns of the row slots S, S + 1, ... of an m x m block held by NW waves:
+// slot s of thread (wave, half wave) is row 2 NW s + 2 wave + half, its column c
+// of 32 the column 32 c + (lane & 31).  dd, ee, tau and Ag (where the
+// reflectors go, row stride n) start at the block's first column.
+template <int NW, int R, int C, int S>
+__device__ __forceinline__ void tri_reg_cols(float (&M)[R][C], TriRegShared<C>& sh, int& par, int m, float* Ag, int n,
                                              double* dd, double* ee, double* tau) {
+    constexpr int RS = 2 * NW, C0 = RS * S / 32;     // rows per slot, first live column block
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, cl = lane & 31;
-    for (int jr = 0; jr < 32; ++jr, par ^= 1) {
-        const int jj = 32 * S0 + jr;
+    for (int jr = 0; jr < RS; ++jr, par ^= 1) {
+        const int jj = RS * S + jr;
         if (jj >= m) break;
         if (wave == jr >> 1) {
-            // Row jj sits in one half of this wave; both halves get it.
-            double x[8], sig = 0.0;
+            // Row jj (= column jj) sits in one half of this wave.
+            const bool mine = half == (jr & 1);
+            double x[C], sig = 0.0;
 #pragma unroll
-            for (int c = S0; c < 8; ++c) {
-                x[c] = __shfl(M[S0][c], ((jr & 1) << 5) | cl, 64);
+            for (int c = C0; c < C; ++c) {
+                x[c] = M[S][c];
                 if (32 * c + cl >= jj + 2) sig += x[c] * x[c];
             }
-            sig = wave_sum_d(half ? 0.0 : sig);       // counted once
-            const double dj = lane_value(x[S0], jr);
-            const double alpha = jr < 31 ? lane_value(x[S0], jr + 1) : S0 < 7 ? lane_value(x[S0 < 7 ? S0 + 1 : 7], 0) : 0.0;
+            sig = wave_sum_d(mine ? sig : 0.0);
+            const int l0 = (jr & 1) << 5;
+            const double dj = lane_value(x[C0], l0 | (jj & 31));
+            const double alpha = (jj & 31) < 31 ? lane_value(x[C0], l0 | ((jj + 1) & 31))
+                                 : C0 + 1 < C   ? lane_value(x[C0 + 1 < C ? C0 + 1 : C0], l0)
+                                                : 0.0;
             const Reflector h = reflector(alpha, sig);
 #pragma unroll
-            for (int c = S0; c < 8; ++c) {
+            for (int c = C0; c < C; ++c) {
                 const int k = 32 * c + cl;
                 const double vk = k <= jj ? 0.0 : (k == jj + 1 ? 1.0 : x[c] * h.scal);
-                if (half == 0) {
+                if (mine) {
                     sh.v[par][k] = vk;
                     if (k > jj && k < m) Ag[(int64_t)jj * n + k] = (float)vk;
                 }
@@ -390,70 +424,68 @@ __device__ __forceinline__ void tri_reg_cols(float (&M)[8][8], TriRegShared& sh,
         const double t = sh.t[par];
         if (t == 0.0) continue;   // H = I (uniform across the block)
         {
-            double vc[8], dot[8];
+            double vc[C], dot[R - S];
 #pragma unroll
-            for (int c = S0; c < 8; ++c) vc[c] = sh.v[par][32 * c + cl];
+            for (int c = C0; c < C; ++c) vc[c] = sh.v[par][32 * c + cl];
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                dot[s] = 0.0;
-                if (s >= S0)
+            for (int s = S; s < R; ++s) {
+                dot[s - S] = 0.0;
 #pragma unroll
-                    for (int c = S0; c < 8; ++c) dot[s] += (double)M[s][c] * vc[c];
+                for (int c = C0; c < C; ++c) dot[s - S] += (double)M[s][c] * vc[c];
                 __builtin_amdgcn_sched_barrier(0);      // register pressure
             }
-            double q0 = swap16_add(dot[0], dot[4]), q1 = swap16_add(dot[1], dot[5]);
-            double q2 = swap16_add(dot[2], dot[6]), q3 = swap16_add(dot[3], dot[7]);
-            q0 = swap8_add(q0, q2, lane);
-            q1 = swap8_add(q1, q3, lane);
-            const double d = sum_quad(swap4_add(q0, q1, lane));
-            const int s = ((lane >> 4) & 1) * 4 + ((lane >> 3) & 1) * 2 + ((lane >> 2) & 1);
-            const int i = 32 * s + 2 * wave + half;
-            if ((lane & 3) == 0) sh.p[par][i] = i > jj ? t * d : 0.0;
+            int slot;
+            bool first;
+            const double d = sum_values<32>(dot, lane, slot, first);
+            const int i = RS * (S + slot) + 2 * wave + half;
+            if (first && slot < R - S && i < 32 * C) sh.p[par][i] = i > jj ? t * d : 0.0;
         }
         // The fp64 copies of M are made anew below: kept across the barrier
         // (the compiler's choice) they would not fit the registers.
 #pragma unroll
-        for (int s = S0; s < 8; ++s)
+        for (int s = S; s < R; ++s)
 #pragma unroll
-            for (int c = S0; c < 8; ++c) asm volatile("" : "+v"(M[s][c]));
+            for (int c = C0; c < C; ++c) asm volatile("" : "+v"(M[s][c]));
         lds_barrier();
-        double vc[8], wc[8], pv = 0.0;
+        double vc[C], wc[C], pv = 0.0;
 #pragma unroll
-        for (int c = S0; c < 8; ++c) {
-            vc[c] = sh.v[par][32 * c + cl];
-            wc[c] = sh.p[par][32 * c + cl];
+        for (int c = C0; c < C; ++c) {
+            const int k = 32 * c + cl;
+            vc[c] = sh.v[par][k];
+            // Only the live slots' rows were written this time; v is zero elsewhere.
+            wc[c] = k >= RS * S && k < RS * R ? sh.p[par][k] : 0.0;
             pv += wc[c] * vc[c];
         }
-        if (half) pv = 0.0;
-        const double K = 0.5 * t * wave_sum_d(pv);
+        const double K = 0.5 * t * wave_sum_d(half ? 0.0 : pv);
 #pragma unroll
-        for (int c = S0; c < 8; ++c) wc[c] -= K * vc[c];
+        for (int c = C0; c < C; ++c) wc[c] -= K * vc[c];
 #pragma unroll
-        for (int s = S0; s < 8; ++s) {
-            const int i = 32 * s + 2 * wave + half;
+        for (int s = S; s < R; ++s) {
+            const int i = RS * s + 2 * wave + half;
             const double vi = sh.v[par][i], wi = sh.p[par][i] - K * vi;
 #pragma unroll
-            for (int c = S0; c < 8; ++c) M[s][c] = (float)((double)M[s][c] - vi * wc[c] - wi * vc[c]);
+            for (int c = C0; c < C; ++c) M[s][c] = (float)((double)M[s][c] - vi * wc[c] - wi * vc[c]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    if constexpr (S + 1 < R) tri_reg_cols<NW, R, C, S + 1>(M, sh, par, m, Ag, n, dd, ee, tau);
 }
 
 __global__ void __launch_bounds__(kTriThreads) tri_reg_kernel(float* A, int64_t strideA, int n, int j0,
                                                               const double* vec, int64_t stride_vec, double* dd,
                                                               double* ee, double* tau, int64_t stride_n) {
-    __shared__ TriRegShared sh;
+    __shared__ TriRegShared<8> sh;
     __shared__ double red[kTriThreads / 64];
     const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, cl = lane & 31;
     const int m = n - j0;
     float* Ag = A + (int64_t)z * strideA;
-    float M[8][8];
+    float M[kTriSlots][8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
+    for (int s = 0; s < kTriSlots; ++s)
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            const int i = 32 * s + 2 * wave + half, k = 32 * c + cl;
+            const int i = 2 * kTriWaves * s + 2 * wave + half, k = 32 * c + cl;
             M[s][c] = i < m && k < m ? Ag[(int64_t)(j0 + i) * n + j0 + k] : 0.f;
         }
     if (j0 > 0) {
@@ -480,8 +512,9 @@ __global__ void __launch_bounds__(kTriThreads) tri_reg_kernel(float* A, int64_t 
             wc[c] = sh.p[0][32 * c + cl];
         }
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const double vi = sh.v[0][32 * s + 2 * wave + half], wi = sh.p[0][32 * s + 2 * wave + half];
+        for (int s = 0; s < kTriSlots; ++s) {
+            const int i = 2 * kTriWaves * s + 2 * wave + half;
+            const double vi = sh.v[0][i], wi = sh.p[0][i];
 #pragma unroll
             for (int c = 0; c < 8; ++c) M[s][c] = (float)((double)M[s][c] - vi * wc[c] - wi * vc[c]);
         }
@@ -492,14 +525,7 @@ __global__ void __launch_bounds__(kTriThreads) tri_reg_kernel(float* A, int64_t 
     double* db = dd + (int64_t)z * stride_n + j0;
     double* eb = ee + (int64_t)z * stride_n + j0;
     double* ub = tau + (int64_t)z * stride_n + j0;
-    tri_reg_cols<0>(M, sh, par, m, Ab, n, db, eb, ub);
-    tri_reg_cols<1>(M, sh, par, m, Ab, n, db, eb, ub);
-    tri_reg_cols<2>(M, sh, par, m, Ab, n, db, eb, ub);
-    tri_reg_cols<3>(M, sh, par, m, Ab, n, db, eb, ub);
-    tri_reg_cols<4>(M, sh, par, m, Ab, n, db, eb, ub);
-    tri_reg_cols<5>(M, sh, par, m, Ab, n, db, eb, ub);
-    tri_reg_cols<6>(M, sh, par, m, Ab, n, db, eb, ub);
-    tri_reg_cols<7>(M, sh, par, m, Ab, n, db, eb, ub);
+    tri_reg_cols<kTriWaves, kTriSlots, 8, 0>(M, sh, par, m, Ab, n, db, eb, ub);
 }
 
 // Eigenvalues by multisection, one wave per eigenvalue ((first + t)-th largest
@@ -518,6 +544,80 @@ __global__ void __launch_bounds__(kTriThreads) tri_reg_kernel(float* A, int64_t 
 // with a reciprocal: 1.89 ms).
 constexpr int kBisectWaves = 4;
 constexpr int kSturmRun = 8;
+
+// Sign changes at the P points x of the scaled matrix de = (d_i, e_{i-1}^2),
+// padded to np8.  The signs of a run are collected one bit per step.
+template <int P>
+__device__ __forceinline__ void sturm_changes(const double2* de, int np8, const double (&x)[P], int (&changes)[P]) {
+    double p[P], pp[P];
+    unsigned sg[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        p[k] = 1.0;
+        pp[k] = 0.0;
+        sg[k] = 0;
+        changes[k] = 0;
+    }
+    static_assert(kSturmRun < 32, "sign bits of a run and its start");
+    for (int i = 0; i < np8; i += kSturmRun) {
+        double2 v[kSturmRun];
+#pragma unroll
+        for (int q = 0; q < kSturmRun; ++q) v[q] = de[i + q];
+#pragma unroll
+        for (int q = 0; q < kSturmRun; ++q)
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const double pn = fma(v[q].x - x[k], p[k], -v[q].y * pp[k]);
+                sg[k] = __builtin_amdgcn_alignbit(sg[k], (unsigned)__double2hiint(pn), 31);    // sg << 1 | sign
+                pp[k] = p[k];
+                p[k] = pn;
+            }
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            changes[k] += __popc((sg[k] ^ sg[k] >> 1) & ((1u << kSturmRun) - 1));
+            const int sc = -__builtin_amdgcn_frexp_exp(fmax(fabs(p[k]), fabs(pp[k])));
+            p[k] = ldexp(p[k], sc);
+            pp[k] = ldexp(pp[k], sc);
+        }
+    }
+}
+// Entry i of de for the matrix scaled by 2^-ex.  Past the end: d = 4 > x and no
+// coupling, which adds no sign change.
+__device__ __forceinline__ double2 sturm_entry(const double* d, const double* e, int n, int i, int ex) {
+    const double es = i > 0 && i < n ? ldexp(e[i - 1], -ex) : 0.0;
+    return make_double2(i < n ? ldexp(d[i], -ex) : 4.0, i < n ? fmax(es * es, 0x1p-200) : 0.0);
+}
+// The (idx + 1)-th smallest eigenvalue by the L lanes of a group (`sub` in it,
+// first lane `base`), P points each (lane s takes the points s + 1 + L k),
+// starting from the scaled bracket [lo, hi].
+template <int L, int P>
+__device__ __forceinline__ double multisect(const double2* de, int np8, int idx, double lo, double hi, int sub,
+                                            int base) {
+    constexpr int N = L * P;
+    for (int it = 0; it < 100; ++it) {
+        const double w = hi - lo;
+        if (w <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 0x1p-70) break;
+        auto pt = [&](int k) { return lo + (w * (double)k) * (1.0 / (N + 1)); };
+        double x[P];
+        int c[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) x[k] = pt(sub + 1 + L * k);
+        sturm_changes<P>(de, np8, x, c);
+        // First point whose count exceeds idx (N: none does).
+        int s = N;
+#pragma unroll
+        for (int k = P - 1; k >= 0; --k) {
+            const unsigned long long mask = __ballot(c[k] > idx) >> base & (L == 64 ? ~0ull : (1ull << (L & 63)) - 1);
+            if (mask) s = L * k + __builtin_ctzll(mask);
+        }
+        const double nlo = s > 0 ? pt(s) : lo;
+        const double nhi = s < N ? pt(s + 1) : hi;
+        if (!(nlo > lo) && !(nhi < hi)) break;
+        lo = nlo;
+        hi = nhi;
+    }
+    return 0.5 * (lo + hi);
+}
 
 __global__ void __launch_bounds__(64 * kBisectWaves) tri_bisect_kernel(const double* dd, const double* ee,
                                                                        int64_t stride_n, int n, int first, int nvals,
@@ -558,63 +658,146 @@ __global__ void __launch_bounds__(64 * kBisectWaves) tri_bisect_kernel(const dou
     int ex;
     (void)frexp(span, &ex);             // span = f 2^ex, f in [1/2, 1)
     const int np8 = (n + kSturmRun - 1) / kSturmRun * kSturmRun;
-    for (int i = tid; i < np8; i += 64 * kBisectWaves) {
-        const double es = i > 0 && i < n ? ldexp(e[i - 1], -ex) : 0.0;
-        // Past the end: d = 4 > x and no coupling, which adds no sign change.
-        de[i] = make_double2(i < n ? ldexp(d[i], -ex) : 4.0, i < n ? fmax(es * es, 0x1p-200) : 0.0);
-    }
+    for (int i = tid; i < np8; i += 64 * kBisectWaves) de[i] = sturm_entry(d, e, n, i, ex);
     __syncthreads();
     if (t >= nvals) return;
     lo = ldexp(lo, -ex) - 2.0 * DBL_EPSILON;
     hi = ldexp(hi, -ex) + 2.0 * DBL_EPSILON;
     // smallest x with count(x) > idx, idx counted from the bottom
-    const int idx = n - 1 - (first + t);
-    for (int it = 0; it < 100; ++it) {
-        const double w = hi - lo;
-        if (w <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 0x1p-70) break;
-        auto pt = [&](int k) { return lo + (w * (double)k) * (1.0 / 65.0); };
-        const double x = pt(lane + 1);
-        double p = 1.0, pp = 0.0;
-        int changes = 0;
-        for (int i = 0; i < np8; i += kSturmRun) {
-            double2 v[kSturmRun];
-#pragma unroll
-            for (int q = 0; q < kSturmRun; ++q) v[q] = de[i + q];
-#pragma unroll
-            for (int q = 0; q < kSturmRun; ++q) {
-                const double pn = fma(v[q].x - x, p, -v[q].y * pp);
-                changes += (unsigned)((__double2hiint(pn) ^ __double2hiint(p))) >> 31;
-                pp = p;
-                p = pn;
-            }
-            const int sc = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pp)));
-            p = ldexp(p, sc);
-            pp = ldexp(pp, sc);
-        }
-        const unsigned long long mask = __ballot(changes > idx);
-        // First point whose count exceeds idx (64: none does).
-        const int s = mask ? __builtin_ctzll(mask) : 64;
-        const double nlo = s > 0 ? pt(s) : lo;
-        const double nhi = s < 64 ? pt(s + 1) : hi;
-        if (!(nlo > lo) && !(nhi < hi)) break;
-        lo = nlo;
-        hi = nhi;
-    }
-    if (lane == 0) out[(int64_t)z * stride_out + t] = ldexp(0.5 * (lo + hi), ex);
+    const double x = multisect<64, 1>(de, np8, n - 1 - (first + t), lo, hi, lane, 0);
+    if (lane == 0) out[(int64_t)z * stride_out + t] = ldexp(x, ex);
 }
 
-// Inverse iteration with the factors in LDS, for orders up to kInvLdsMax: one
-// wave per block, `vpb` eigenvalues of one matrix in its first lanes.  The same
-// partially pivoted LU of T - lambda_k I, start vector and solves as
-// tri_inverse_kernel below; the factorization is repeated by each launch (it
-// costs about one solve) instead of being kept in memory.  A step's chain is a
-// few fp64 operations and its operands come from LDS a run of steps ahead,
-// where the global-memory form waits on L2 at every eight steps: 32 vectors of
-// four matrices of order 768 take 0.47 ms for both launches, 256 vectors of
-// order 264 0.18 ms (0.72 ms).  The order limit is the 160 KB of LDS.
-constexpr int kInvLdsMax = 2800;
+// Inverse iteration with the factors in LDS: the partially pivoted LU of
+// T - lambda I and its solves for one eigenvalue per lane.  Row i of the factors
+// (f: multiplier, r: 1 / pivot, m: first superdiagonal, sw: rows swapped; the
+// second superdiagonal is e_{i+1} where they were) is entry i st of each array,
+// the working vector entry i ys of y; de = (d_i, e_i).
 constexpr int kInvRun = 8;
-inline int64_t inv_lds_bytes(int n, int vpb) { return (int64_t)n * (16 + 41 * (int64_t)vpb); }
+struct InvLds {
+    const double2* de;
+    double *f, *r, *m;
+    unsigned char* sw;
+    double* y;
+    int st, ys;
+};
+
+// Factorization and the first solve's forward sweep in one pass; the start
+// vector is the fixed pseudo-random sequence of eigenvalue k when init, else y.
+// Returns the running entry after the sweep.
+__device__ __forceinline__ double inv_factor(const InvLds& a, int n, double lk, double floor_piv, int k, bool init) {
+    auto floored = [&](double g) { return fabs(g) < floor_piv ? (g < 0.0 ? -floor_piv : floor_piv) : g; };
+    uint32_t h = 0x9e3779b9u * (uint32_t)(k + 1);
+    auto draw = [&]() {     // in [-1, 1], distinct per k
+        h ^= h << 13; h ^= h >> 17; h ^= h << 5;
+        return ((double)(h >> 8) * (1.0 / 8388608.0)) - 1.0;
+    };
+    // g, u: the current diagonal and superdiagonal entries of row i (row i + 1
+    // of the matrix is still untouched when step i starts); c: the running
+    // entry of the P L solve.
+    double g = a.de[0].x - lk, u = a.de[0].y, c = init ? draw() : a.y[0];
+    auto step = [&](int i, double l, double dn, double un, double nx) {
+        const int o = i * a.st;
+        const double gn = dn - lk;
+        const bool keep = fabs(g) >= fabs(l);
+        const double r = recip(floored(keep ? g : l));
+        const double f = (keep ? l : g) * r, m = keep ? u : gn;
+        a.f[o] = f;
+        a.r[o] = r;
+        a.m[o] = m;
+        a.sw[o] = !keep;
+        g = (keep ? gn : u) - f * m;
+        u = keep ? un : -f * un;
+        const double top = keep ? c : nx;
+        a.y[i * a.ys] = top;
+        c = (keep ? nx : c) - f * top;
+    };
+    int i0 = 0;
+    for (; i0 + kInvRun < n; i0 += kInvRun) {
+        double2 w[kInvRun + 1];
+        double nx[kInvRun];
+#pragma unroll
+        for (int q = 0; q <= kInvRun; ++q) w[q] = a.de[i0 + q];
+#pragma unroll
+        for (int q = 0; q < kInvRun; ++q) nx[q] = init ? draw() : a.y[(i0 + q + 1) * a.ys];
+#pragma unroll
+        for (int q = 0; q < kInvRun; ++q) step(i0 + q, w[q].y, w[q + 1].x, w[q + 1].y, nx[q]);
+    }
+    for (; i0 + 1 < n; ++i0)
+        step(i0, a.de[i0].y, a.de[i0 + 1].x, a.de[i0 + 1].y, init ? draw() : a.y[(i0 + 1) * a.ys]);
+    a.r[(n - 1) * a.st] = recip(floored(g));
+    return c;
+}
+
+// Forward sweep (P L) of y scaled by `scale`; returns the running entry.
+__device__ __forceinline__ double inv_forward(const InvLds& a, int n, double scale) {
+    double c = a.y[0] * scale;
+    auto step = [&](int i, double nx, double f, bool swap) {
+        const double top = swap ? nx : c;
+        a.y[i * a.ys] = top;
+        c = (swap ? c : nx) - f * top;
+    };
+    int i0 = 0;
+    for (; i0 + kInvRun < n; i0 += kInvRun) {
+        double nx[kInvRun], fl[kInvRun];
+        int pf[kInvRun];
+#pragma unroll
+        for (int q = 0; q < kInvRun; ++q) {
+            nx[q] = a.y[(i0 + q + 1) * a.ys] * scale;
+            fl[q] = a.f[(i0 + q) * a.st];
+            pf[q] = a.sw[(i0 + q) * a.st];
+        }
+#pragma unroll
+        for (int q = 0; q < kInvRun; ++q) step(i0 + q, nx[q], fl[q], pf[q]);
+    }
+    for (; i0 + 1 < n; ++i0) step(i0, a.y[(i0 + 1) * a.ys] * scale, a.f[i0 * a.st], a.sw[i0 * a.st]);
+    return c;
+}
+
+// Backward sweep from the running entry c; returns 1 / max |y_i| (1 for y = 0).
+__device__ __forceinline__ double inv_backward(const InvLds& a, int n, double c) {
+    double y1 = c * a.r[(n - 1) * a.st], y2 = 0.0, mx = fabs(y1);
+    a.y[(n - 1) * a.ys] = y1;
+    auto step = [&](int i, double yv, double m, double e1, double r) {
+        const double y0 = (yv - e1 * y2 - m * y1) * r;
+        a.y[i * a.ys] = y0;
+        mx = fmax(mx, fabs(y0));
+        y2 = y1;
+        y1 = y0;
+    };
+    int i0 = n - 2;
+    for (; i0 >= kInvRun - 1; i0 -= kInvRun) {
+        double yv[kInvRun], m[kInvRun], e1[kInvRun], r[kInvRun];
+#pragma unroll
+        for (int q = 0; q < kInvRun; ++q) {
+            const int i = i0 - q, o = i * a.st;
+            yv[q] = a.y[i * a.ys];
+            m[q] = a.m[o];
+            r[q] = a.r[o];
+            const double ev = a.de[i + 1].y;
+            e1[q] = a.sw[o] ? ev : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < kInvRun; ++q) step(i0 - q, yv[q], m[q], e1[q], r[q]);
+    }
+    for (; i0 >= 0; --i0)
+        step(i0, a.y[i0 * a.ys], a.m[i0 * a.st], a.sw[i0 * a.st] ? a.de[i0 + 1].y : 0.0, a.r[i0 * a.st]);
+    return mx > 0.0 ? recip(mx) : 1.0;
+}
+
+// Pivot floor eps ||T||; the bound keeps its reciprocal finite for T = 0.
+__device__ __forceinline__ double inv_floor(double tnorm) { return fmax(tnorm * DBL_EPSILON, 0x1p-900); }
+
+// Inverse iteration for orders up to kInvLdsMax: one wave per block, `vpb`
+// eigenvalues of one matrix in its first lanes.  The factorization is repeated
+// by each launch (it costs about one solve) instead of being kept in memory.  A
+// step's chain is a few fp64 operations and its operands come from LDS a run
+// of steps ahead, where the global-memory form waits on L2 at every eight
+// steps: 32 vectors of four matrices of order 768 take 0.47 ms for both
+// launches, 256 vectors of order 264 0.18 ms (0.72 ms).  The order limit is the
+// 160 KB of LDS.
+constexpr int kInvLdsMax = 2800;
+inline int64_t inv_lds_bytes(int n, int vpb) { return (int64_t)n * (16 + 33 * (int64_t)vpb); }
 
 __global__ void __launch_bounds__(64) tri_inverse_lds_kernel(const double* dd, const double* ee, int64_t stride_n,
                                                              int n, const double* lam, int64_t stride_lam, int nvals,
@@ -622,14 +805,12 @@ __global__ void __launch_bounds__(64) tri_inverse_lds_kernel(const double* dd, c
     extern __shared__ double sh[];
     const int z = blockIdx.y, lane = threadIdx.x, k0 = blockIdx.x * vpb;
     const int nk = min(vpb, nvals - k0);            // eigenvalues of this block
-        double2* de = reinterpret_cast<double2*>(sh);   // (d_i, e_i)
+    double2* de = reinterpret_cast<double2*>(sh);   // (d_i, e_i)
     double* base = sh + 2 * n;
-    double* dl = base + lane;
-    double* ig = base + (int64_t)n * vpb + lane;
-    double* du = base + 2 * (int64_t)n * vpb + lane;
-    double* du2 = base + 3 * (int64_t)n * vpb + lane;
-    double* yw = base + 4 * (int64_t)n * vpb + lane;
-    unsigned char* pv = reinterpret_cast<unsigned char*>(base + 5 * (int64_t)n * vpb) + lane;
+    const int64_t nv = (int64_t)n * vpb;
+    double* yw = base + 3 * nv;
+    const InvLds a{de, base + lane, base + nv + lane, base + 2 * nv + lane,
+                   reinterpret_cast<unsigned char*>(base + 4 * nv) + lane, yw + lane, vpb, vpb};
     const double* d0 = dd + (int64_t)z * stride_n;
     const double* e0 = ee + (int64_t)z * stride_n;
     double* yz = y + ((int64_t)z * nvals + k0) * (int64_t)n;
@@ -643,113 +824,20 @@ __global__ void __launch_bounds__(64) tri_inverse_lds_kernel(const double* dd, c
     for (int o = 32; o >= 1; o >>= 1) tn = fmax(tn, __shfl_xor(tn, o, 64));
     if (!init)
         for (int k = 0; k < nk; ++k)
-            for (int i = lane; i < n; i += 64) yw[(int64_t)i * vpb + k - lane] = yz[(int64_t)k * n + i];
+            for (int i = lane; i < n; i += 64) yw[(int64_t)i * vpb + k] = yz[(int64_t)k * n + i];
     __syncthreads();
     double scale = 1.0;
     if (lane < nk) {
-        const int k = k0 + lane;
-        const double lk = lam[(int64_t)z * stride_lam + k];
-        // Pivot floor eps ||T||; the bound keeps its reciprocal finite for T = 0.
-        const double floor_piv = fmax(tn * DBL_EPSILON, 0x1p-900);
-        auto floored = [&](double g) { return fabs(g) < floor_piv ? (g < 0.0 ? -floor_piv : floor_piv) : g; };
-        // Start vector: a fixed pseudo-random sequence in [-1, 1], distinct per k.
-        uint32_t h = 0x9e3779b9u * (uint32_t)(k + 1);
-        auto draw = [&]() {
-            h ^= h << 13; h ^= h >> 17; h ^= h << 5;
-            return ((double)(h >> 8) * (1.0 / 8388608.0)) - 1.0;
-        };
-        // Factorization and the first solve's forward sweep in one pass.
-        // g, u: the current diagonal and superdiagonal entries of row i (row
-        // i + 1 of the matrix is still untouched when step i starts); c: the
-        // running entry of P L solve.
-        double g = de[0].x - lk, u = de[0].y, c = init ? draw() : yw[0];
-        auto lu_step = [&](int i, double l, double dn, double un, double nx) {
-            const int o = i * vpb;
-            const double gn = dn - lk;
-            const bool keep = fabs(g) >= fabs(l);
-            const double r = recip(floored(keep ? g : l));
-            const double f = (keep ? l : g) * r, m = keep ? u : gn;
-            dl[o] = f;
-            ig[o] = r;
-            du[o] = m;
-            du2[o] = keep ? 0.0 : un;
-            pv[o] = !keep;
-            g = (keep ? gn : u) - f * m;
-            u = keep ? un : -f * un;
-            const double a = keep ? c : nx;
-            yw[o] = a;
-            c = (keep ? nx : c) - f * a;
-        };
-        int i0 = 0;
-        for (; i0 + kInvRun < n; i0 += kInvRun) {
-            double2 w[kInvRun + 1];
-            double nx[kInvRun];
-#pragma unroll
-            for (int q = 0; q <= kInvRun; ++q) w[q] = de[i0 + q];
-#pragma unroll
-            for (int q = 0; q < kInvRun; ++q) nx[q] = init ? draw() : yw[(i0 + q + 1) * vpb];
-#pragma unroll
-            for (int q = 0; q < kInvRun; ++q) lu_step(i0 + q, w[q].y, w[q + 1].x, w[q + 1].y, nx[q]);
-        }
-        for (; i0 + 1 < n; ++i0)
-            lu_step(i0, de[i0].y, de[i0 + 1].x, de[i0 + 1].y, init ? draw() : yw[(i0 + 1) * vpb]);
-        ig[(n - 1) * vpb] = recip(floored(g));
+        double c = inv_factor(a, n, lam[(int64_t)z * stride_lam + k0 + lane], inv_floor(tn), k0 + lane, init);
         for (int sv = 0; sv < solves; ++sv) {
-            if (sv > 0) {
-                // Forward: P L, the running entry c = y[i] in a register.
-                c = yw[0] * scale;
-                auto fwd = [&](int i, double nx, double f, bool swap) {
-                    const double a = swap ? nx : c;
-                    yw[i * vpb] = a;
-                    c = (swap ? c : nx) - f * a;
-                };
-                i0 = 0;
-                for (; i0 + kInvRun < n; i0 += kInvRun) {
-                    double nx[kInvRun], fl[kInvRun];
-                    int pf[kInvRun];
-#pragma unroll
-                    for (int q = 0; q < kInvRun; ++q) {
-                        const int o = (i0 + q) * vpb;
-                        nx[q] = yw[o + vpb] * scale;
-                        fl[q] = dl[o];
-                        pf[q] = pv[o];
-                    }
-#pragma unroll
-                    for (int q = 0; q < kInvRun; ++q) fwd(i0 + q, nx[q], fl[q], pf[q]);
-                }
-                for (; i0 + 1 < n; ++i0) fwd(i0, yw[(i0 + 1) * vpb] * scale, dl[i0 * vpb], pv[i0 * vpb]);
-            }
-            // Backward: U with two superdiagonals, y[i + 1] and y[i + 2] carried.
-            double y1 = c * ig[(n - 1) * vpb], y2 = 0.0, mx = fabs(y1);
-            yw[(n - 1) * vpb] = y1;
-            auto bwd = [&](int i, double yv, double uu, double u2, double gi) {
-                const double y0 = (yv - u2 * y2 - uu * y1) * gi;
-                yw[i * vpb] = y0;
-                mx = fmax(mx, fabs(y0));
-                y2 = y1;
-                y1 = y0;
-            };
-            for (i0 = n - 2; i0 >= kInvRun - 1; i0 -= kInvRun) {
-                double yv[kInvRun], uu[kInvRun], u2[kInvRun], gi[kInvRun];
-#pragma unroll
-                for (int q = 0; q < kInvRun; ++q) {
-                    const int o = (i0 - q) * vpb;
-                    yv[q] = yw[o];
-                    uu[q] = du[o];
-                    u2[q] = du2[o];
-                    gi[q] = ig[o];
-                }
-#pragma unroll
-                for (int q = 0; q < kInvRun; ++q) bwd(i0 - q, yv[q], uu[q], u2[q], gi[q]);
-            }
-            for (; i0 >= 0; --i0) bwd(i0, yw[i0 * vpb], du[i0 * vpb], du2[i0 * vpb], ig[i0 * vpb]);
-            scale = mx > 0.0 ? recip(mx) : 1.0;
+            if (sv > 0) c = inv_forward(a, n, scale);
+            scale = inv_backward(a, n, c);
         }
     }
     __syncthreads();
     for (int k = 0; k < nk; ++k) {
         const double sk = lane_value(scale, k);
-        for (int i = lane; i < n; i += 64) yz[(int64_t)k * n + i] = yw[(int64_t)i * vpb + k - lane] * sk;
+        for (int i = lane; i < n; i += 64) yz[(int64_t)k * n + i] = yw[(int64_t)i * vpb + k] * sk;
     }
 }
 
@@ -1123,6 +1211,255 @@ __global__ void __launch_bounds__(256) select_k_kernel(const double* lam, int to
     kmat[(int64_t)z * ell_pad * ell_pad + q] = (float)sacc;
 }
 
+// Ritz pairs, selection and K of one l x l problem per workgroup, l <= kRitzMax:
+// the dense solver's steps (reduction in registers, multisection, inverse
+// iteration with one lane per vector, Gram-Schmidt inside clusters,
+// back-transformation) with everything between them in LDS, in one launch.  All
+// of them are chains of l steps whose LDS instructions all waves share (an
+// access of few lanes takes the pipe as long as one of 64), so the workgroup
+// has four waves: with sixteen the same steps took three times as long.
+//   LDS: y (top x n doubles, odd pitch), the LU factors of `batch` vectors, and
+//   the tridiagonal matrix; the reflectors go to K's memory until K is formed.
+// 138 us per launch at l = 40 (48 matrices), 304 at l = 72 (112), 70 at l = 24, a
+// third of it the reduction at 1.0-1.25 us per column; the round-robin fp32
+// Jacobi it replaces took 194, 692 and 99 us (six sweeps of l rounds).
+constexpr int kRitzMax = 80;
+constexpr int kRitzWaves = 4, kRitzThreads = 64 * kRitzWaves;
+constexpr size_t kRitzLds = 156 * 1024;
+
+inline size_t ritz_fixed_lds(int n, int top) {
+    const int np8 = (n + kSturmRun - 1) / kSturmRun * kSturmRun;
+    return (size_t)8 * ((size_t)top * (n | 1) + 3 * n + 1 + 2 * np8 + 2 * n + 2 * top);
+}
+inline size_t ritz_vec_lds(int n) { return (size_t)n * 25; }
+
+template <int R, int C>
+__global__ void __launch_bounds__(kRitzThreads) ritz_kernel(EigArgs a, int batch) {
+    extern __shared__ double dyn[];
+    __shared__ TriRegShared<C> sh;
+    __shared__ double gl[kRitzWaves], gh[kRitzWaves], gt[kRitzWaves];
+    constexpr int NW = kRitzWaves;
+    const int z = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int half = lane >> 5, cl = lane & 31;
+    const int n = a.ell, lp = a.ell_pad, top = min(a.rank, n), ny = n | 1;
+    const int np8 = (n + kSturmRun - 1) / kSturmRun * kSturmRun;
+    double* y = dyn;                                // [t][i], pitch ny
+    double* d = y + (size_t)top * ny;
+    double* e = d + n;
+    double* tau = e + n;
+    double2* ds = reinterpret_cast<double2*>(tau + n + ((top * ny + 3 * n) & 1));     // scaled (d, e^2)
+    double2* de = ds + np8;                         // (d_i, e_i)
+    double* lam = reinterpret_cast<double*>(de + n);
+    double* fc = lam + top;
+    double* lu = fc + top;                          // f, r, m of a batch
+    unsigned char* sw = reinterpret_cast<unsigned char*>(lu + 3 * (size_t)n * batch);
+    float* K = a.kmat + (int64_t)z * lp * lp;
+    float* V = K;                                   // n x n, until K is formed
+    const double* part = a.partial + (int64_t)z * a.chunks * lp * lp;
+    float M[R][C];
+#pragma unroll
+    for (int s = 0; s < R; ++s)
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int i = 2 * NW * s + 2 * wave + half, k = 32 * c + cl;
+            const double v = gram_at(part, lp, min(i, n - 1), min(k, n - 1), a.chunks);
+            M[s][c] = i < n && k < n ? (float)v : 0.f;
+        }
+    int par = 0;
+    tri_reg_cols<NW, R, C, 0>(M, sh, par, n, V, n, d, e, tau);
+    __syncthreads();
+    // Gershgorin interval and the norm for the pivot floor.
+    double lo = DBL_MAX, hi = -DBL_MAX, tn = 0.0;
+    for (int i = tid; i < n; i += kRitzThreads) {
+        const double em = i > 0 ? fabs(e[i - 1]) : 0.0, ei = i + 1 < n ? fabs(e[i]) : 0.0;
+        lo = fmin(lo, d[i] - em - ei);
+        hi = fmax(hi, d[i] + em + ei);
+        tn = fmax(tn, fabs(d[i]) + em + ei);
+        de[i] = make_double2(d[i], i + 1 < n ? e[i] : 0.0);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o, 64));
+        hi = fmax(hi, __shfl_xor(hi, o, 64));
+        tn = fmax(tn, __shfl_xor(tn, o, 64));
+    }
+    if (lane == 0) {
+        gl[wave] = lo;
+        gh[wave] = hi;
+        gt[wave] = tn;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+        lo = fmin(lo, gl[q]);
+        hi = fmax(hi, gh[q]);
+        tn = fmax(tn, gt[q]);
+    }
+    const double span = fmax(fabs(lo), fabs(hi));
+    int ex = 0;
+    if (span > 0.0) (void)frexp(span, &ex);
+    for (int i = tid; i < np8; i += kRitzThreads) ds[i] = sturm_entry(d, e, n, i, ex);
+    __syncthreads();
+    {
+        const double slo = ldexp(lo, -ex) - 2.0 * DBL_EPSILON, shi = ldexp(hi, -ex) + 2.0 * DBL_EPSILON;
+        // As many lanes per eigenvalue as one pass over all of them allows.
+        auto all = [&](auto lanes) {
+            constexpr int L = decltype(lanes)::value, G = 64 / L;
+            for (int t0 = G * wave; t0 < top; t0 += G * NW) {
+                const int t = t0 + lane / L;
+                // Groups past the last eigenvalue repeat it (the ballots need all lanes).
+                const double x = span > 0.0 ? multisect<L, 2>(ds, np8, n - 1 - min(t, top - 1), slo, shi, lane % L,
+                                                              lane / L * L)
+                                            : 0.0;
+                if (lane % L == 0 && t < top) lam[t] = ldexp(x, ex);
+            }
+        };
+        if (top <= 4 * NW) all(std::integral_constant<int, 16>{});
+        else if (top <= 8 * NW) all(std::integral_constant<int, 8>{});
+        else all(std::integral_constant<int, 4>{});
+    }
+    __syncthreads();
+    // After two solves the clusters are orthogonalized and one more solve
+    // follows.
+    constexpr int E = (32 * C + 63) / 64;           // entries of a vector per lane
+    auto orthonormal = [&]() {
+        const double ortol = 1e-9 * fmax(fabs(lam[0]), fabs(lam[top - 1]));
+        for (int k0 = wave; k0 < top; k0 += NW) {
+            if (k0 > 0 && !(lam[k0 - 1] - lam[k0] > ortol)) continue;   // inside a cluster
+            int k1 = k0 + 1;
+            while (k1 < top && !(lam[k1 - 1] - lam[k1] > ortol)) ++k1;
+            for (int k = k0; k < k1; ++k) {
+                double v[E];
+#pragma unroll
+                for (int c = 0; c < E; ++c) v[c] = lane + 64 * c < n ? y[k * ny + lane + 64 * c] : 0.0;
+                for (int q = k0; q < k; ++q) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int c = 0; c < E; ++c) s += lane + 64 * c < n ? v[c] * y[q * ny + lane + 64 * c] : 0.0;
+                    s = wave_sum_d(s);
+#pragma unroll
+                    for (int c = 0; c < E; ++c)
+                        if (lane + 64 * c < n) v[c] -= s * y[q * ny + lane + 64 * c];
+                }
+                double s = 0.0;
+#pragma unroll
+                for (int c = 0; c < E; ++c) s += v[c] * v[c];
+                s = wave_sum_d(s);
+                const double inv = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+#pragma unroll
+                for (int c = 0; c < E; ++c)
+                    if (lane + 64 * c < n) y[k * ny + lane + 64 * c] = v[c] * inv;
+            }
+        }
+    };
+    const double floor_piv = inv_floor(tn);
+    const int per_wave = (batch + NW - 1) / NW;     // lanes of each wave that hold a vector
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int b0 = 0; b0 < top; b0 += batch) {
+            const int v = per_wave * wave + lane, t = b0 + v;
+            if (lane < per_wave && v < batch && t < top) {
+                const size_t nb = (size_t)n * batch;
+                const InvLds w{de, lu + v, lu + nb + v, lu + 2 * nb + v, sw + v, y + (size_t)t * ny, batch, 1};
+                // A single batch keeps its factors for the second pass.
+                const double c = pass == 0 || top > batch ? inv_factor(w, n, lam[t], floor_piv, t, pass == 0)
+                                                          : inv_forward(w, n, 1.0);
+                double sc = inv_backward(w, n, c);
+                if (pass == 0) sc = inv_backward(w, n, inv_forward(w, n, sc));
+                for (int i = 0; i < n; ++i) w.y[i] *= sc;
+            }
+        }
+        __syncthreads();
+        orthonormal();
+        __syncthreads();
+    }
+    // u = H_0 ... H_{n-2} y, a wave per eight vectors.
+    for (int t0 = 8 * wave; t0 < top; t0 += 8 * NW) {
+        double u[8][E], vn[E];
+        auto load_v = [&](int j) {
+#pragma unroll
+            for (int c = 0; c < E; ++c) {
+                const int i = lane + 64 * c;
+                const float x = V[max(j, 0) * n + min(i, n - 1)];
+                vn[c] = i > j && i < n ? (double)x : 0.0;
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int c = 0; c < E; ++c) u[q][c] = lane + 64 * c < n ? y[min(t0 + q, top - 1) * ny + lane + 64 * c] : 0.0;
+        load_v(n - 2);
+        for (int j = n - 2; j >= 0; --j) {
+            double v[E], s[8];
+#pragma unroll
+            for (int c = 0; c < E; ++c) v[c] = vn[c];
+            load_v(j - 1);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                s[q] = 0.0;
+#pragma unroll
+                for (int c = 0; c < E; ++c) s[q] += v[c] * u[q][c];
+            }
+            int slot;
+            bool first;
+            const double sum = tau[j] * sum_values<64>(s, lane, slot, first);
+            // The sum of vector q sits in the lanes with bits 5, 4, 3 = q.
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const double f = lane_value(sum, 8 * q);
+#pragma unroll
+                for (int c = 0; c < E; ++c) u[q][c] -= f * v[c];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int c = 0; c < E; ++c)
+                if (t0 + q < top && lane + 64 * c < n) y[(t0 + q) * ny + lane + 64 * c] = u[q][c];
+    }
+    // Selection (lam is descending, so the selected ones lead) and K = Z_C
+    // diag(lambda^-1/2 - 1) Z_C^T in 4 x 4 blocks.
+    int ns = 0;
+    while (ns < top && lam[ns] > 1.0) ++ns;
+    for (int t = tid; t < top; t += kRitzThreads) {
+        fc[t] = t < ns ? 1.0 / sqrt(lam[t]) - 1.0 : 0.0;
+        a.ritz[(int64_t)z * a.ritz_stride + t] = (float)lam[t];
+    }
+    if (tid == 0) a.nsel[z] = ns;
+    __syncthreads();
+    const int nb = lp / 4;
+    for (int b = tid; b < nb * nb; b += kRitzThreads) {
+        const int c0 = b / nb * 4, d0 = (b - b / nb * nb) * 4;
+        double acc[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
+        if (c0 < n && d0 < n)
+            for (int t = 0; t < ns; ++t) {
+                const double f = fc[t];
+                double zc[4], zd[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    zc[u] = y[t * ny + min(c0 + u, n - 1)] * f;
+                    zd[u] = y[t * ny + min(d0 + u, n - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[u][v] = fma(zc[u], zd[v], acc[u][v]);
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float4 o;
+            o.x = c0 + u < n && d0 < n ? (float)acc[u][0] : 0.f;
+            o.y = c0 + u < n && d0 + 1 < n ? (float)acc[u][1] : 0.f;
+            o.z = c0 + u < n && d0 + 2 < n ? (float)acc[u][2] : 0.f;
+            o.w = c0 + u < n && d0 + 3 < n ? (float)acc[u][3] : 0.f;
+            *(float4*)(K + (int64_t)(c0 + u) * lp + d0) = o;
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t launch_gamma_sym(const float* g, int64_t ldg, int64_t strideg, int n, float* A, int batch,
@@ -1260,6 +1597,30 @@ hipError_t launch_eig_select_dense(const EigArgs& a, const TriWork& w, double* l
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(select_k_kernel, dim3((unsigned)(((int64_t)lp * lp + 255) / 256), batch), dim3(256), 0, s,
                        lam, top, zbuf, n, lp, a.kmat, a.ritz, a.ritz_stride, a.nsel);
+    return hipGetLastError();
+}
+
+// Largest width of the one-workgroup Ritz kernel.
+int ritz_small_max() { return kRitzMax; }
+
+hipError_t launch_eig_select(const EigArgs& a, int batch_mats, hipStream_t s) {
+    const int n = a.ell, top = std::min(a.rank, n);
+    if (n < 1 || n > kRitzMax || n > a.ell_pad || a.ell_pad % 4 || top < 1 || a.chunks < 1 || a.chunks > kGramChunks ||
+        a.chunks % 4)
+        return hipErrorInvalidValue;
+    // All vectors at once where their factors fit, else equal batches.
+    const size_t fixed = ritz_fixed_lds(n, top);
+    const int most = std::min(64 * kRitzWaves, (int)((kRitzLds - fixed) / ritz_vec_lds(n)));
+    const int batches = (top + most - 1) / most, batch = (top + batches - 1) / batches;
+    const size_t lds = fixed + batch * ritz_vec_lds(n);
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(batch_mats), dim3(kRitzThreads), lds, s, a, batch);
+    };
+    if (n <= 16) run(ritz_kernel<2, 1>);
+    else if (n <= 32) run(ritz_kernel<4, 1>);
+    else if (n <= 48) run(ritz_kernel<6, 2>);
+    else if (n <= 64) run(ritz_kernel<8, 2>);
+    else run(ritz_kernel<10, 3>);
     return hipGetLastError();
 }
 

@@ -364,18 +364,17 @@ struct SmallMulArgs {
 };
 hipError_t launch_small_mul(const SmallMulArgs& a, hipStream_t s);
 
-// Jacobi eigensolver of Gamma_Q (summed fp64 partials), selection of the
-// top-min(r, l) Ritz values > 1, K = Z_C diag(lambda^-1/2 - 1) Z_C^T (fp32,
-// l_pad x l_pad).
+// Ritz pairs of Gamma_Q (summed fp64 partials), selection of the top-min(r, l)
+// Ritz values > 1, K = Z_C diag(lambda^-1/2 - 1) Z_C^T (fp32, l_pad x l_pad).
 struct EigArgs {
     const double* partial; int chunks;
     int ell, ell_pad, rank;
-    float* scratch;             // 2 * l_pad * l_pad floats per matrix
     float* kmat;                // l_pad x l_pad per matrix
     float* ritz; int ritz_stride;
     int* nsel;
-    int max_sweeps;
 };
+// One workgroup per matrix, l <= ritz_small_max().
+int ritz_small_max();
 hipError_t launch_eig_select(const EigArgs& a, int batch, hipStream_t s);
 
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t s);
@@ -446,8 +445,7 @@ hipError_t launch_vec_split(const double* y, int nvals, int n, half_t* hi, half_
                             int64_t stride_out, int batch, hipStream_t s);
 // a += 2^-11 b over count floats per matrix (count and stride multiples of 4).
 hipError_t launch_join_split(float* a, const float* b, int64_t count, int64_t stride, int batch, hipStream_t s);
-// Ritz pairs through the dense eigensolver (for l above the Jacobi kernels'
-// sweet spot): Gamma_Q from the summed fp64 Gram partials, its top
+// Ritz pairs through the dense eigensolver's launches (wider l): Gamma_Q from the summed fp64 Gram partials, its top
 // min(r, l) eigenpairs, the selection lambda > 1 and K = Z_C diag(lambda^-1/2
 // - 1) Z_C^T, with the outputs of launch_eig_select.  zbuf: top x l floats
 // per matrix; lam: top doubles per matrix.

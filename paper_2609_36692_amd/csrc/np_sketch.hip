@@ -7,10 +7,7 @@
 //     basis Q = qr(Y) and for the Rayleigh-Ritz matrix Gamma_Q = B B^T),
 //   * Cholesky-QR: Cholesky of the Gram with dropping of numerically
 //     dependent columns, and the triangular inverse,
-//   * small products M^T V with an l x l matrix M,
-//   * a parallel cyclic Jacobi eigensolver for Gamma_Q followed by the
-//     selection of the top-min(r, l) Ritz values above one and the l x l
-//     matrix K = Z_C diag(lambda_C^{-1/2} - 1) Z_C^T.
+//   * small products M^T V with an l x l matrix M.
 #include "np_internal.h"
 
 #include <algorithm>
@@ -248,8 +245,6 @@ __device__ __forceinline__ double rcp_f64(double x) {
     y = fma(y, fma(-x, y, 1.0), y);
     return fma(y, fma(-x, y, 1.0), y);
 }
-
-constexpr int kSmallThreads = 512;
 
 // Cholesky and inverse of one l x l matrix per workgroup, l <= kCholG T, all in
 // registers: elimination of the rows of [G | I] turns G into (scaled) R and I
@@ -609,543 +604,6 @@ __global__ void __launch_bounds__(256) small_mul_kernel(SmallMulArgs args) {
     }
 }
 
-// ------------------------------------------------------ Jacobi + select --
-// Two-sided cyclic Jacobi with the round-robin pairing: every round rotates
-// l/2 disjoint (p, q) pairs at once.  A round is one data-parallel phase: the
-// 2 x 2 block of A on rows (p1, q1) and columns (p2, q2) becomes
-// J1^T block J2 for every pair of pairs, and columns (p, q) of Z become Z J.
-// A and Z live in LDS (row stride l + 1) when they fit, else in a global
-// scratch slice.
-constexpr int kEigLdsMax = 138;
-// Packed mode: the upper triangle of A (rows packed) in LDS, Z^T in a global
-// scratch slice; used above kEigLdsMax while l (l + 1) / 2 floats fit.
-constexpr int kEigPackedMax = 278;
-
-// Stopping rule of every Jacobi kernel, tested on the squared off-diagonal
-// mass `off` against the squared Frobenius norm `tot`: converged below
-// 1e-13 relative, or stalled at the fp32 rounding floor (already below 1e-9
-// relative and less than a 4x drop over the last sweep; the quadratic phase
-// drops it far more per sweep until rounding dominates).
-__device__ __forceinline__ bool jacobi_done(float off, float tot, float prev_off) {
-    return !(off > 1e-13f * tot) || (off <= 1e-9f * tot && off >= 0.25f * prev_off);
-}
-
-__device__ __forceinline__ void rr_pair(int round, int k, int n2, int& p, int& q) {
-    const int n1 = n2 - 1;
-    if (k == 0) { p = n1; q = round; }
-    else { p = (round + k) % n1; q = (round - k + n1) % n1; }
-    if (p > q) { const int t = p; p = q; q = t; }
-}
-
-template <int NT>
-__device__ __forceinline__ float block_sum_f(float v, float* red) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float t = 0.f;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) t += red[w];
-    return t;
-}
-
-template <bool IN_LDS>
-__global__ void __launch_bounds__(kSmallThreads) eig_select_kernel(EigArgs a) {
-    constexpr int NT = kSmallThreads;
-    extern __shared__ float dyn[];
-    const int z = blockIdx.x, tid = threadIdx.x;
-    const int n = a.ell, lp = a.ell_pad;
-    const int ld = IN_LDS ? n + 1 : n;
-    float* A;
-    if constexpr (IN_LDS) A = dyn;
-    else A = a.scratch + (int64_t)z * 2 * lp * lp;
-    float* Z = A + n * ld;
-    __shared__ float cs[192], sn[192];
-    __shared__ int pp[192], qq[192];
-    __shared__ float red[NT / 64];
-    __shared__ float lam[384], fcoef[384];
-    __shared__ int rnk[384];
-    __shared__ int stop_flag;
-    const double* part = a.partial + (int64_t)z * a.chunks * lp * lp;
-    for (int q = tid; q < n * n; q += NT) {
-        const int c = q / n, d = q - (q / n) * n;
-        A[c * ld + d] = (float)gram_at(part, lp, c, d, a.chunks);
-        Z[c * ld + d] = c == d ? 1.f : 0.f;
-    }
-    __syncthreads();
-    const int n2 = n + (n & 1);
-    const int npairs = n2 / 2;
-    const int nblk = npairs * npairs;
-    float prev_off = INFINITY;
-    for (int sweep = 0; sweep < a.max_sweeps; ++sweep) {
-        float off = 0.f, tot = 0.f;
-        for (int q = tid; q < n * n; q += NT) {
-            const int c = q / n, d = q - (q / n) * n;
-            const float v = A[c * ld + d] * A[c * ld + d];
-            tot += v;
-            if (c != d) off += v;
-        }
-        off = block_sum_f<NT>(off, red);
-        tot = block_sum_f<NT>(tot, red);
-        if (tid == 0) stop_flag = jacobi_done(off, tot, prev_off);
-        prev_off = off;
-        __syncthreads();
-        if (stop_flag) break;
-        for (int round = 0; round < n2 - 1; ++round) {
-            for (int k = tid; k < npairs; k += NT) {
-                int p, q;
-                rr_pair(round, k, n2, p, q);
-                float c = 1.f, s = 0.f;
-                if (q < n) {
-                    const float apq = A[p * ld + q];
-                    const float app = A[p * ld + p], aqq = A[q * ld + q];
-                    if (fabsf(apq) > 1e-30f && fabsf(apq) > 1e-9f * sqrtf(fabsf(app * aqq))) {
-                        const float theta = (aqq - app) / (2.f * apq);
-                        float t;
-                        if (fabsf(theta) > 1e15f) t = 0.5f / theta;
-                        else t = copysignf(1.f, theta) / (fabsf(theta) + sqrtf(theta * theta + 1.f));
-                        c = 1.f / sqrtf(t * t + 1.f);
-                        s = t * c;
-                    }
-                }
-                cs[k] = c; sn[k] = s; pp[k] = p; qq[k] = q;
-            }
-            __syncthreads();
-            // A <- J^T A J, one 2 x 2 block per work item.
-            for (int w = tid; w < nblk; w += NT) {
-                const int k1 = w / npairs, k2 = w - k1 * npairs;
-                const int p1 = pp[k1], q1 = qq[k1], p2 = pp[k2], q2 = qq[k2];
-                const float c1 = cs[k1], s1 = sn[k1], c2 = cs[k2], s2 = sn[k2];
-                const bool r1 = q1 < n, r2 = q2 < n;
-                const float a00 = A[p1 * ld + p2];
-                const float a01 = r2 ? A[p1 * ld + q2] : 0.f;
-                const float a10 = r1 ? A[q1 * ld + p2] : 0.f;
-                const float a11 = (r1 && r2) ? A[q1 * ld + q2] : 0.f;
-                // rows: J1^T
-                const float b00 = c1 * a00 - s1 * a10, b01 = c1 * a01 - s1 * a11;
-                const float b10 = s1 * a00 + c1 * a10, b11 = s1 * a01 + c1 * a11;
-                // columns: J2
-                A[p1 * ld + p2] = c2 * b00 - s2 * b01;
-                if (r2) A[p1 * ld + q2] = s2 * b00 + c2 * b01;
-                if (r1) A[q1 * ld + p2] = c2 * b10 - s2 * b11;
-                if (r1 && r2) A[q1 * ld + q2] = s2 * b10 + c2 * b11;
-            }
-            for (int w = tid; w < npairs * n; w += NT) {
-                const int k = w / n, i = w - (w / n) * n;
-                const int p = pp[k], q = qq[k];
-                if (q >= n) continue;
-                const float c = cs[k], s = sn[k];
-                const float zp = Z[i * ld + p], zq = Z[i * ld + q];
-                Z[i * ld + p] = c * zp - s * zq;
-                Z[i * ld + q] = s * zp + c * zq;
-            }
-            __syncthreads();
-        }
-    }
-    // Ritz values, descending order with ties to the lower index.
-    for (int i = tid; i < n; i += NT) lam[i] = A[i * ld + i];
-    __syncthreads();
-    const int top = min(a.rank, n);
-    for (int i = tid; i < n; i += NT) {
-        const float li = lam[i];
-        int r = 0;
-        for (int j = 0; j < n; ++j) r += (lam[j] > li) || (lam[j] == li && j < i);
-        rnk[i] = r;
-        const bool sel = r < top && li > 1.f;
-        fcoef[i] = sel ? (1.f / sqrtf(li) - 1.f) : 0.f;
-        if (r < top) a.ritz[(int64_t)z * a.ritz_stride + r] = li;
-    }
-    __syncthreads();
-    // K = Z diag(f) Z^T over the selected modes.
-    float* K = a.kmat + (int64_t)z * lp * lp;
-    for (int q = tid; q < lp * lp; q += NT) {
-        const int c = q / lp, d = q - (q / lp) * lp;
-        float s = 0.f;
-        if (c < n && d < n)
-            for (int i = 0; i < n; ++i)
-                if (fcoef[i] != 0.f) s = fmaf(Z[c * ld + i] * fcoef[i], Z[d * ld + i], s);
-        K[q] = s;
-    }
-    if (tid == 0) {
-        int cnt = 0;
-        for (int i = 0; i < n; ++i) cnt += (rnk[i] < top && lam[i] > 1.f);
-        a.nsel[z] = cnt;
-    }
-}
-
-// Index of (r, c) in the packed upper triangle of an n x n symmetric matrix.
-__device__ __forceinline__ int pk(int r, int c, int n) {
-    if (r > c) { const int t = r; r = c; c = t; }
-    return r * n - (r * (r - 1)) / 2 + (c - r);
-}
-
-// The same Jacobi sweep, selection and K as eig_select_kernel, with A packed
-// in LDS and Z stored transposed (row i = Ritz vector i) in global memory, so
-// the rotation of columns p, q of Z updates two contiguous rows.  Only the
-// pair-blocks (k1 <= k2) of the upper triangle are rotated; the diagonal
-// block keeps its three distinct entries.
-__global__ void __launch_bounds__(kSmallThreads) eig_select_packed_kernel(EigArgs a) {
-    constexpr int NT = kSmallThreads;
-    extern __shared__ float A[];
-    const int z = blockIdx.x, tid = threadIdx.x;
-    const int n = a.ell, lp = a.ell_pad;
-    float* Zt = a.scratch + (int64_t)z * 2 * lp * lp;
-    __shared__ float cs[192], sn[192];
-    __shared__ int pp[192], qq[192];
-    __shared__ float red[NT / 64];
-    __shared__ float lam[384], fcoef[384];
-    __shared__ int rnk[384];
-    __shared__ int stop_flag;
-    const double* part = a.partial + (int64_t)z * a.chunks * lp * lp;
-    for (int q = tid; q < n * n; q += NT) {
-        const int c = q / n, d = q - (q / n) * n;
-        if (c <= d) A[pk(c, d, n)] = (float)gram_at(part, lp, c, d, a.chunks);
-        Zt[(int64_t)c * lp + d] = c == d ? 1.f : 0.f;
-    }
-    __syncthreads();
-    const int n2 = n + (n & 1);
-    const int npairs = n2 / 2;
-    float prev_off = INFINITY;
-    for (int sweep = 0; sweep < a.max_sweeps; ++sweep) {
-        float off = 0.f, tot = 0.f;
-        for (int q = tid; q < n * n; q += NT) {
-            const int c = q / n, d = q - (q / n) * n;
-            if (c > d) continue;
-            const float v = A[pk(c, d, n)] * A[pk(c, d, n)];
-            tot += c == d ? v : 2.f * v;
-            if (c != d) off += 2.f * v;
-        }
-        off = block_sum_f<NT>(off, red);
-        tot = block_sum_f<NT>(tot, red);
-        if (tid == 0) stop_flag = jacobi_done(off, tot, prev_off);
-        prev_off = off;
-        __syncthreads();
-        if (stop_flag) break;
-        for (int round = 0; round < n2 - 1; ++round) {
-            for (int k = tid; k < npairs; k += NT) {
-                int p, q;
-                rr_pair(round, k, n2, p, q);
-                float c = 1.f, s = 0.f;
-                if (q < n) {
-                    const float apq = A[pk(p, q, n)];
-                    const float app = A[pk(p, p, n)], aqq = A[pk(q, q, n)];
-                    if (fabsf(apq) > 1e-30f && fabsf(apq) > 1e-9f * sqrtf(fabsf(app * aqq))) {
-                        const float theta = (aqq - app) / (2.f * apq);
-                        float t;
-                        if (fabsf(theta) > 1e15f) t = 0.5f / theta;
-                        else t = copysignf(1.f, theta) / (fabsf(theta) + sqrtf(theta * theta + 1.f));
-                        c = 1.f / sqrtf(t * t + 1.f);
-                        s = t * c;
-                    }
-                }
-                cs[k] = c; sn[k] = s; pp[k] = p; qq[k] = q;
-            }
-            __syncthreads();
-            for (int w = tid; w < npairs * npairs; w += NT) {
-                const int k1 = w / npairs, k2 = w - k1 * npairs;
-                if (k1 > k2) continue;
-                const int p1 = pp[k1], q1 = qq[k1], p2 = pp[k2], q2 = qq[k2];
-                const float c1 = cs[k1], s1 = sn[k1], c2 = cs[k2], s2 = sn[k2];
-                const bool r1 = q1 < n, r2 = q2 < n;
-                const float a00 = A[pk(p1, p2, n)];
-                const float a01 = r2 ? A[pk(p1, q2, n)] : 0.f;
-                const float a10 = r1 ? A[pk(q1, p2, n)] : 0.f;
-                const float a11 = (r1 && r2) ? A[pk(q1, q2, n)] : 0.f;
-                const float b00 = c1 * a00 - s1 * a10, b01 = c1 * a01 - s1 * a11;
-                const float b10 = s1 * a00 + c1 * a10, b11 = s1 * a01 + c1 * a11;
-                A[pk(p1, p2, n)] = c2 * b00 - s2 * b01;
-                if (r2) A[pk(p1, q2, n)] = s2 * b00 + c2 * b01;
-                // (q1, p2) is the same stored entry as (p1, q2) on the diagonal block
-                if (r1 && k1 != k2) A[pk(q1, p2, n)] = c2 * b10 - s2 * b11;
-                if (r1 && r2) A[pk(q1, q2, n)] = s2 * b10 + c2 * b11;
-            }
-            // Z^T rows p, q <- rotated; ZB items per thread per batch keep
-            // several global loads in flight.
-            constexpr int ZB = 8;
-            const int zitems = npairs * n;
-            for (int w0 = tid; w0 < zitems; w0 += NT * ZB) {
-                float vp[ZB], vq[ZB];
-                int64_t op[ZB], oq[ZB];
-                float cz[ZB], sz[ZB];
-#pragma unroll
-                for (int b = 0; b < ZB; ++b) {
-                    const int w = w0 + b * NT;
-                    op[b] = -1;
-                    if (w < zitems) {
-                        const int k = w / n, i = w - (w / n) * n;
-                        if (qq[k] < n) {
-                            op[b] = (int64_t)pp[k] * lp + i;
-                            oq[b] = (int64_t)qq[k] * lp + i;
-                            cz[b] = cs[k];
-                            sz[b] = sn[k];
-                            vp[b] = Zt[op[b]];
-                            vq[b] = Zt[oq[b]];
-                        }
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < ZB; ++b) {
-                    if (op[b] < 0) continue;
-                    Zt[op[b]] = cz[b] * vp[b] - sz[b] * vq[b];
-                    Zt[oq[b]] = sz[b] * vp[b] + cz[b] * vq[b];
-                }
-            }
-            __syncthreads();
-        }
-    }
-    for (int i = tid; i < n; i += NT) lam[i] = A[pk(i, i, n)];
-    __syncthreads();
-    const int top = min(a.rank, n);
-    for (int i = tid; i < n; i += NT) {
-        const float li = lam[i];
-        int r = 0;
-        for (int j = 0; j < n; ++j) r += (lam[j] > li) || (lam[j] == li && j < i);
-        rnk[i] = r;
-        const bool sel = r < top && li > 1.f;
-        fcoef[i] = sel ? (1.f / sqrtf(li) - 1.f) : 0.f;
-        if (r < top) a.ritz[(int64_t)z * a.ritz_stride + r] = li;
-    }
-    __syncthreads();
-    // K = sum_i f_i z_i z_i^T, with the rows of Z^T staged through the LDS that
-    // held A, CH rows at a time (K accumulated in place across chunks).
-    float* K = a.kmat + (int64_t)z * lp * lp;
-    const int CH = (n + 1) / 2;
-    for (int i0 = 0; i0 < n; i0 += CH) {
-        const int cnt = min(CH, n - i0);
-        for (int q = tid; q < cnt * n; q += NT) {
-            const int i = q / n, c = q - (q / n) * n;
-            A[q] = Zt[(int64_t)(i0 + i) * lp + c];
-        }
-        __syncthreads();
-        for (int q = tid; q < lp * lp; q += NT) {
-            const int c = q / lp, d = q - (q / lp) * lp;
-            float s = i0 == 0 ? 0.f : K[q];
-            if (c < n && d < n)
-                for (int i = 0; i < cnt; ++i) {
-                    const float f = fcoef[i0 + i];
-                    if (f != 0.f) s = fmaf(A[i * n + c] * f, A[i * n + d], s);
-                }
-            K[q] = s;
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        int cnt = 0;
-        for (int i = 0; i < n; ++i) cnt += (rnk[i] < top && lam[i] > 1.f);
-        a.nsel[z] = cnt;
-    }
-}
-
-// Round-robin Jacobi for l <= kEigRRMax with A double-buffered in LDS: a
-// round reads the current A and writes J^T A J into the other buffer, and
-// each thread derives the rotations of its own pair-blocks from the current
-// A with the same arithmetic the pair's diagonal block uses, so a round
-// needs one barrier instead of two.  The columns of Z take round r's
-// rotations during round r + 1 (published by the diagonal blocks, double
-// buffered by round parity).  The off-diagonal mass is summed while the last
-// round of a sweep is written, so the stopping test costs no extra pass.
-// Arithmetic per rotation, the stopping rule, selection and K are those of
-// eig_select_kernel.
-constexpr int kEigRRMax = 104;
-
-__device__ __forceinline__ void rr_pair_fast(int round, int k, int n1, int& p, int& q) {
-    if (k == 0) {
-        p = n1; q = round;
-    } else {
-        p = round + k;
-        if (p >= n1) p -= n1;
-        q = round - k;
-        if (q < 0) q += n1;
-    }
-    if (p > q) { const int t = p; p = q; q = t; }
-}
-
-// Rotation (c, s) that zeroes a_pq (Rutishauser's tangent form), or the
-// identity below the same threshold as the other Jacobi kernels.  Hardware
-// reciprocal / square-root approximations: the rotation only has to be
-// orthogonal to fp32 precision, which rsq keeps (c^2 + s^2 = 1 to ~1 ulp),
-// and every thread that needs a pair's rotation computes it with the same
-// instructions from the same operands.
-__device__ __forceinline__ void jacobi_rotation_fast(float app, float aqq, float apq, bool real, float& c, float& s) {
-    const float aa = fabsf(apq);
-    const bool rot = real && aa > 1e-30f && aa > 1e-9f * __builtin_amdgcn_sqrtf(fabsf(app * aqq));
-    const float theta = (aqq - app) * 0.5f * __builtin_amdgcn_rcpf(apq);
-    const float at = fabsf(theta);
-    const float t = copysignf(__builtin_amdgcn_rcpf(at + __builtin_amdgcn_sqrtf(fmaf(at, at, 1.f))), theta);
-    const float cc = __builtin_amdgcn_rsqf(fmaf(t, t, 1.f));
-    c = rot ? cc : 1.f;
-    s = rot ? t * cc : 0.f;
-}
-
-template <int NT, int NB, int NZ>
-__global__ void __launch_bounds__(NT) eig_select_rr_kernel(EigArgs a) {
-    extern __shared__ float dyn[];
-    const int z = blockIdx.x, tid = threadIdx.x;
-    const int n = a.ell, lp = a.ell_pad, ld = n + 1;
-    // Two n x (n + 1) buffers for A and one for Z; the padding column n
-    // absorbs the phantom index of odd n (reads there are masked, writes
-    // are identity rotations).
-    float* Ac = dyn;
-    float* An = dyn + n * ld;
-    float* Z = dyn + 2 * n * ld;
-    // Rotation of each pair, published by its diagonal block: (c, s, p, q).
-    __shared__ float4 rec[2][kEigRRMax / 2 + 1];
-    __shared__ float red[2][2][NT / 64];
-    __shared__ float lam[kEigRRMax], fcoef[kEigRRMax];
-    __shared__ int rnk[kEigRRMax];
-    const double* part = a.partial + (int64_t)z * a.chunks * lp * lp;
-    for (int q = tid; q < n * ld; q += NT) {
-        const int c = q / ld, d = q - (q / ld) * ld;
-        Ac[q] = d < n ? (float)gram_at(part, lp, c, d, a.chunks) : 0.f;
-        Z[q] = c == d ? 1.f : 0.f;
-    }
-    const int n2 = n + (n & 1), n1 = n2 - 1, npairs = n2 / 2;
-    const int ub = npairs * (npairs + 1) / 2;
-    // This thread's pair-blocks (k1 <= k2) and Z items (pair k, row i).
-    int bk1[NB], bk2[NB], zk[NZ], zi[NZ];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        int w = tid + j * NT, k1 = -1, k2 = -1;
-        if (w < ub) {
-            k1 = 0;
-            while (w >= npairs - k1) { w -= npairs - k1; ++k1; }
-            k2 = k1 + w;
-        }
-        bk1[j] = k1;
-        bk2[j] = k2;
-    }
-#pragma unroll
-    for (int j = 0; j < NZ; ++j) {
-        const int w = tid + j * NT;
-        zk[j] = w < npairs * n ? w / n : -1;
-        zi[j] = w < npairs * n ? w - (w / n) * n : 0;
-    }
-    __syncthreads();
-    int gr = 0;             // rounds done (parity of the published rotations)
-    const int lane = tid & 63, wave = tid >> 6;
-    // Columns p, q of Z take the rotations published in round gr - 1.
-    auto rotate_z = [&](int par) {
-#pragma unroll
-        for (int j = 0; j < NZ; ++j) {
-            if (zk[j] < 0) break;
-            const float4 r = rec[par][zk[j]];
-            const int p = __float_as_int(r.z), q = __float_as_int(r.w), i = zi[j];
-            const float za = Z[i * ld + p], zb = Z[i * ld + q];
-            Z[i * ld + p] = r.x * za - r.y * zb;
-            Z[i * ld + q] = r.y * za + r.x * zb;
-        }
-    };
-    float prev_off = INFINITY;
-    for (int sweep = 0; sweep < a.max_sweeps; ++sweep) {
-        float off = 0.f, tot = 0.f;
-        for (int round = 0; round < n1; ++round, ++gr) {
-            const bool last = round == n1 - 1;
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int k1 = bk1[j], k2 = bk2[j];
-                if (k1 < 0) break;
-                int p1, q1, p2, q2;
-                rr_pair_fast(round, k1, n1, p1, q1);
-                rr_pair_fast(round, k2, n1, p2, q2);
-                const bool r1 = q1 < n, r2 = q2 < n;
-                const int u1 = min(q1, n - 1), u2 = min(q2, n - 1);
-                // Every read of the block first, then the rotations.
-                const float x0 = Ac[p1 * ld + p1], x1 = Ac[u1 * ld + u1], x2 = Ac[p1 * ld + u1];
-                const float x3 = Ac[p2 * ld + p2], x4 = Ac[u2 * ld + u2], x5 = Ac[p2 * ld + u2];
-                const float x6 = Ac[p1 * ld + p2], x7 = Ac[p1 * ld + u2];
-                const float x8 = Ac[u1 * ld + p2], x9 = Ac[u1 * ld + u2];
-                if (j == 0 && gr > 0) rotate_z((gr - 1) & 1);
-                float c1, s1, c2, s2;
-                jacobi_rotation_fast(x0, x1, x2, r1, c1, s1);
-                jacobi_rotation_fast(x3, x4, x5, r2, c2, s2);
-                if (k2 == k1) rec[gr & 1][k1] = make_float4(c1, s1, __int_as_float(p1), __int_as_float(q1));
-                const float a00 = x6, a01 = r2 ? x7 : 0.f;
-                const float a10 = r1 ? x8 : 0.f, a11 = (r1 && r2) ? x9 : 0.f;
-                const float b00 = c1 * a00 - s1 * a10, b01 = c1 * a01 - s1 * a11;
-                const float b10 = s1 * a00 + c1 * a10, b11 = s1 * a01 + c1 * a11;
-                const float d00 = c2 * b00 - s2 * b01, d01 = s2 * b00 + c2 * b01;
-                const float d10 = c2 * b10 - s2 * b11, d11 = s2 * b10 + c2 * b11;
-                An[p1 * ld + p2] = d00;
-                if (r2) An[p1 * ld + q2] = d01;
-                if (r1) An[q1 * ld + p2] = d10;
-                if (r1 && r2) An[q1 * ld + q2] = d11;
-                if (k2 != k1) {
-                    An[p2 * ld + p1] = d00;
-                    if (r2) An[q2 * ld + p1] = d01;
-                    if (r1) An[p2 * ld + q1] = d10;
-                    if (r1 && r2) An[q2 * ld + q1] = d11;
-                }
-                if (last) {
-                    const float e00 = d00 * d00, e01 = r2 ? d01 * d01 : 0.f;
-                    const float e10 = r1 ? d10 * d10 : 0.f, e11 = (r1 && r2) ? d11 * d11 : 0.f;
-                    if (k2 != k1) {
-                        const float m = 2.f * (e00 + e01 + e10 + e11);
-                        off += m;
-                        tot += m;
-                    } else {
-                        off += e01 + e10;
-                        tot += e00 + e01 + e10 + e11;
-                    }
-                }
-            }
-            // Threads without a pair-block still rotate their Z items.
-            if (bk1[0] < 0 && gr > 0) rotate_z((gr - 1) & 1);
-            if (last) {
-#pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) {
-                    off += __shfl_xor(off, o, 64);
-                    tot += __shfl_xor(tot, o, 64);
-                }
-                if (lane == 0) {
-                    red[sweep & 1][0][wave] = off;
-                    red[sweep & 1][1][wave] = tot;
-                }
-            }
-            __syncthreads();
-            float* t = Ac; Ac = An; An = t;
-        }
-        float so = 0.f, st = 0.f;
-#pragma unroll
-        for (int w = 0; w < NT / 64; ++w) {
-            so += red[sweep & 1][0][w];
-            st += red[sweep & 1][1][w];
-        }
-        if (jacobi_done(so, st, prev_off)) break;
-        prev_off = so;
-    }
-    if (gr > 0) rotate_z((gr - 1) & 1);
-    // Ritz values, descending order with ties to the lower index.
-    for (int i = tid; i < n; i += NT) lam[i] = Ac[i * ld + i];
-    __syncthreads();
-    const int top = min(a.rank, n);
-    for (int i = tid; i < n; i += NT) {
-        const float li = lam[i];
-        int r = 0;
-        for (int j = 0; j < n; ++j) r += (lam[j] > li) || (lam[j] == li && j < i);
-        rnk[i] = r;
-        const bool sel = r < top && li > 1.f;
-        fcoef[i] = sel ? (1.f / sqrtf(li) - 1.f) : 0.f;
-        if (r < top) a.ritz[(int64_t)z * a.ritz_stride + r] = li;
-    }
-    __syncthreads();
-    // K = Z diag(f) Z^T over the selected modes.
-    float* K = a.kmat + (int64_t)z * lp * lp;
-    for (int q = tid; q < lp * lp; q += NT) {
-        const int c = q / lp, d = q - (q / lp) * lp;
-        float s = 0.f;
-        if (c < n && d < n)
-            for (int i = 0; i < n; ++i)
-                if (fcoef[i] != 0.f) s = fmaf(Z[c * ld + i] * fcoef[i], Z[d * ld + i], s);
-        K[q] = s;
-    }
-    if (tid == 0) {
-        int cnt = 0;
-        for (int i = 0; i < n; ++i) cnt += (rnk[i] < top && lam[i] > 1.f);
-        a.nsel[z] = cnt;
-    }
-}
-
 }  // namespace
 
 hipError_t launch_omega_f16(const OmegaArgs& a, int batch, hipStream_t s) {
@@ -1288,26 +746,6 @@ hipError_t launch_small_mul(const SmallMulArgs& a, hipStream_t s) {
     }
     dim3 grid((unsigned)(len_pad / kSmBN), (unsigned)(a.ell_pad / kSmBM), a.zbeg[a.n]);
     hipLaunchKernelGGL(small_mul_kernel, grid, dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_eig_select(const EigArgs& a, int batch, hipStream_t s) {
-    if (a.ell > 384 || a.ell_pad > 384 || a.chunks < 1 || a.chunks > kGramChunks) return hipErrorInvalidValue;
-    if (a.ell <= kEigRRMax) {
-        const size_t lds = (size_t)3 * a.ell * (a.ell + 1) * sizeof(float);
-        if (a.ell <= 64)
-            hipLaunchKernelGGL((eig_select_rr_kernel<1024, 1, 2>), dim3(batch), dim3(1024), lds, s, a);
-        else
-            hipLaunchKernelGGL((eig_select_rr_kernel<1024, 2, 6>), dim3(batch), dim3(1024), lds, s, a);
-    } else if (a.ell <= kEigLdsMax) {
-        const size_t lds = (size_t)2 * a.ell * (a.ell + 1) * sizeof(float);
-        hipLaunchKernelGGL((eig_select_kernel<true>), dim3(batch), dim3(kSmallThreads), lds, s, a);
-    } else if (a.ell <= kEigPackedMax) {
-        const size_t lds = (size_t)a.ell * (a.ell + 1) / 2 * sizeof(float);
-        hipLaunchKernelGGL(eig_select_packed_kernel, dim3(batch), dim3(kSmallThreads), lds, s, a);
-    } else {
-        hipLaunchKernelGGL((eig_select_kernel<false>), dim3(batch), dim3(kSmallThreads), 0, s, a);
-    }
     return hipGetLastError();
 }
 

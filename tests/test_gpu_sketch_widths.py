@@ -1,7 +1,9 @@
 """NormPre-L over sketch widths l at the edges of the l x l kernels: the
-Cholesky's tiles of 16, the summed Gram above 64, the two-level factorization
-above 192 (with its uneven halves), and rank-deficient sketches whose dependent
-columns are dropped in either half."""
+Cholesky's tiles of 16, the summed Gram above 96, the two-level factorization
+above 192 (with its uneven halves), the one-workgroup Ritz kernel up to 80 and
+the dense solver above (its workspace shared up to 104); rank-deficient
+sketches whose dependent columns are dropped in either half; and equal Ritz
+values, whose vectors come out of one cluster."""
 import math
 
 import numpy as np
@@ -44,7 +46,7 @@ def _step(ctx, mats, t, rank, oversample):
         print(f"  l={ref['ell']} |C|={ref['n_selected']} update err {err:.2e}", flush=True)
 
 
-@pytest.mark.parametrize("ell", [1, 2, 3, 15, 16, 17, 32, 33, 48, 49, 63, 64, 65, 96, 97, 104, 105, 128, 129, 160,
+@pytest.mark.parametrize("ell", [1, 2, 3, 15, 16, 17, 32, 33, 48, 49, 63, 64, 65, 80, 81, 96, 97, 104, 105, 128, 129, 160,
                                  161, 192, 193, 208, 209, 256, 257, 383, 384])
 def test_widths(ctx, ell):
     print(f"L width {ell}", flush=True)
@@ -61,3 +63,15 @@ def test_rank_deficient(ctx, ell, true_rank, t):
     m = torch.randn(300, true_rank, generator=g) @ torch.randn(true_rank, 410, generator=g)
     w = 0.02 * torch.randn(300, 410, generator=g)
     _step(ctx, [(w, m, torch.zeros_like(m))], t, ell - 8, 8)
+
+
+@pytest.mark.parametrize("groups,rank,oversample", [(16, 32, 8), (5, 8, 0), (40, 64, 8), (60, 96, 8)])
+def test_equal_ritz_values(ctx, groups, rank, oversample):
+    print(f"L equal Ritz values, {groups} groups r={rank}", flush=True)
+    # Rows in `groups` sets of equal unit vectors: Gamma has the eigenvalue
+    # 8 that many times and zeros, and the projector on the cluster is unique.
+    a = 8 * groups
+    m = torch.zeros(a, 410)
+    m[torch.arange(a), torch.arange(a) % groups] = 2.0
+    w = torch.zeros_like(m)
+    _step(ctx, [(w, m, torch.zeros_like(m))], 0, rank, oversample)
