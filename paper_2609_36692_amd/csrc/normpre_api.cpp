@@ -35,9 +35,6 @@ constexpr int kEigAliasMax = 104;
 constexpr int64_t kMaxExactRows = 8192;
 constexpr int kColRowChunk = 128;   // rows per block in the column-active pass
 constexpr int kMaxSplits = 16;
-// NormPre-L: largest share of ||Psi||_F^2 in the selected modes for which
-// ||T||_F^2 is taken in closed form (see sketch_back).
-constexpr float kClosedNormFrac = 0.25f;
 constexpr size_t kGroupBudget = size_t(24) << 30;  // workspace bytes per item
 constexpr size_t kRoundBudget = size_t(48) << 30;  // workspace bytes per round
 // Static scratch of normpre_step_noalloc(): the whole workspace of that entry
@@ -787,12 +784,14 @@ int run_normalize(const StepCtx& sc, const Dims& d, const GWork& w, const std::v
                    "non-finite counts");
         }
     }
-    NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
-                 [&] {
-                     return launch_psi_scale(w.psisq, d.lp_, both ? (int)d.n : (int)d.a, sc.hp->ns_eps, w.scale,
-                                             count, sc.s);
-                 }),
-           "psi scale");
+    // (NormPre-L takes ||Psi||_F^2 from psisq itself.)
+    if (sc.variant != NORMPRE_VARIANT_L)
+        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
+                     [&] {
+                         return launch_psi_scale(w.psisq, d.lp_, both ? (int)d.n : (int)d.a, sc.hp->ns_eps, w.scale,
+                                                 count, sc.s);
+                     }),
+               "psi scale");
     if (w.xs) {
         // Interaction source X: X_s = sqrt(a / ||X||_F^2) D Psi, so that
         // X_s X_s^T is the trace-matched Gram of the active rows.
@@ -1519,32 +1518,43 @@ float pow2_at_most_inv_sqrt(int64_t a) {
     return std::ldexp(1.f, -e);
 }
 
-int sketch_front(const StepCtx& sc, const Item& it, DebugMat* dbg) {
-    const Dims& d = it.d;
-    const GWork& w = it.w;
-    const std::vector<int>& idx = (*sc.groups)[it.g].idx;
-    const int first = it.first, count = it.count;
-    int rc = run_normalize(sc, d, w, idx, first, count, dbg);
-    if (rc) return rc;
-    const normpre_hparams& hp = *sc.hp;
-    const int64_t lp = d.ellp, maxpad = d.lp_;
-    // Omega^T (ell_pad x b_pad), one counter per matrix: its index in the list.
-    for (int c0 = 0; c0 < count; c0 += kChunk) {
-        const int cnt = std::min(kChunk, count - c0);
-        OmegaArgs o{};
-        o.seed = hp.seed;
-        o.step = hp.step;
-        for (int i = 0; i < cnt; ++i) o.ids[i] = idx[first + c0 + i];
-        o.b = (int)d.b;
+// Omega^T (ell_pad x b_pad) of the sketched items of a pool run, one counter per
+// matrix: its index in the list.  kOmegaIds matrices per launch (an item may
+// be split over launches).
+int omega_run(const StepCtx& sc, const std::vector<const Item*>& its) {
+    OmegaArgs o{};
+    o.seed = sc.hp->seed;
+    o.step = sc.hp->step;
+    auto flush = [&]() -> int {
+        if (o.n == 0) return NORMPRE_OK;
+        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0, [&] { return launch_omega_f16(o, sc.s); }), "omega");
+        o.n = 0;
+        return NORMPRE_OK;
+    };
+    for (const Item* it : its) {
+        const Dims& d = it->d;
+        const std::vector<int>& idx = (*sc.groups)[it->g].idx;
+        const int64_t stride = (int64_t)d.ellp * d.lp_;
         o.ell = d.ell;
-        o.ell_pad = (int)lp;
-        o.ld = d.b_pad;
-        o.out = w.omega + (int64_t)c0 * lp * maxpad;
-        o.stride = lp * maxpad;
-        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0, [&] { return launch_omega_f16(o, cnt, sc.s); }),
-               "omega");
+        o.ell_pad = d.ellp;
+        for (int c0 = 0; c0 < it->count;) {
+            const int used = o.n > 0 ? o.zbeg[o.n] : 0, cnt = std::min(kOmegaIds - used, it->count - c0);
+            if (cnt == 0 || o.n == kMaxItems) {
+                if (int rc = flush()) return rc;
+                continue;
+            }
+            const int g = o.n++;
+            o.zbeg[g] = used;
+            o.zbeg[g + 1] = used + cnt;
+            o.b[g] = (int)d.b;
+            o.ld[g] = d.b_pad;
+            o.out[g] = it->w.omega + c0 * stride;
+            o.stride[g] = stride;
+            for (int i = 0; i < cnt; ++i) o.ids[used + i] = idx[it->first + c0 + i];
+            c0 += cnt;
+        }
     }
-    return NORMPRE_OK;
+    return flush();
 }
 
 // Alg. 2: Y = Psi Omega; p times Y <- Psi (Psi^T Y), each product one grouped
@@ -1678,7 +1688,8 @@ bool closed_norm(const Item& it) { return !it.d.xl && !it.w.xs; }
 // groups per launch (see LNormGroups).
 int closed_norm_launches(const StepCtx& sc, const std::vector<Item>& items, const std::vector<Pool>& pools) {
     LNormGroups g{};
-    g.frac = kClosedNormFrac;
+    const bool both = sc.hp->orientation == NORMPRE_ORIENT_BOTH;
+    g.unit_rows = !both;
     int total = 0;
     auto flush = [&]() -> int {
         if (g.n == 0) return NORMPRE_OK;
@@ -1694,7 +1705,9 @@ int closed_norm_launches(const StepCtx& sc, const std::vector<Item>& items, cons
         const Pool& pl = pools[it.pool];
         const int i = g.n++;
         g.zbeg[i] = total;
-        g.psi2[i] = it.w.scale + 1;
+        g.psisq[i] = it.w.psisq;
+        g.stride[i] = it.d.lp_;
+        g.count[i] = both ? (int)it.d.n : (int)it.d.a;
         g.ritz[i] = pl.ritz + (int64_t)it.pool_off * pl.top;
         g.ritz_stride[i] = pl.top;
         g.nsel[i] = pl.nsel + it.pool_off;
@@ -1719,15 +1732,13 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
     const half_t* R = d.k == 0 ? w.flen : w.qlen;
     const int64_t l_stride = (d.k == 0 ? d.a_pad : d.b_pad) * lp;
     const int64_t r_stride = (d.k == 0 ? d.b_pad : d.a_pad) * lp;
-    // ||T||_F^2: in closed form, ||Psi||_F^2 - sum_C (lambda_i - 1), where the
-    // selected modes hold at most a quarter of ||Psi||_F^2; there its error
-    // is a few 1e-4 of ||T||^2 (fp16 Q and B) while a norm pass over T would
-    // stream Psi once more.  Where they hold more, the subtraction cancels,
-    // and those matrices take the norm pass: the same product as the update,
-    // reduced to per-tile sums of T^2.  (The closed form needs the Ritz
-    // values of Psi itself: not with the interaction source X, nor for the
-    // dense eigensolver's exact variant.)
-    // (closed_norm_launches ran the closed form for these matrices.)
+    // ||T||_F^2: in closed form, ||Psi||_F^2 - sum_C (lambda_i - 1), where that is
+    // accurate (closed_norm_launches decided it on the device), which saves
+    // streaming Psi once more; the other matrices take the norm pass: the
+    // same product as the update, reduced to per-tile sums of T^2, which the
+    // update's blocks add up.  (The closed form needs the Ritz values of Psi
+    // itself: not with the interaction source X, nor for the dense
+    // eigensolver's exact variant.)
     const bool closed = closed_norm(it);
     {
         Operand A{L, lp, l_stride};
@@ -1741,12 +1752,13 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
         NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_L_APPLY, 2.0 * d.ell * (double)d.m * d.n * count, 2.0 * d.m * d.n * count,
                      [&] { return launch_gemm_apply_norm(A, B, sh, count, e, sc.s); }),
                "apply norm");
-        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
-                     [&] {
-                         return launch_sum_partials(w.sumsq, apply_tiles(d), w.tn2, count, sc.s,
-                                                    closed ? w.lneed : nullptr);
-                     }),
-               "t norm");
+        if (!closed || dbg)
+            NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
+                         [&] {
+                             return launch_sum_partials(w.sumsq, apply_tiles(d), w.tn2, count, sc.s,
+                                                        closed ? w.lneed : nullptr);
+                         }),
+                   "t norm");
     }
     for (int c0 = 0; c0 < count; c0 += kChunk) {
         const int cnt = std::min(kChunk, count - c0);
@@ -1756,6 +1768,8 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
         EpiApplyUpdate e{};
         e.psi = w.psi + (int64_t)c0 * mn; e.ld_psi = d.np_; e.stride_psi = mn;
         e.tnorm2 = w.tn2 + c0;
+        if (closed) e.need = w.lneed + c0;
+        e.sumsq = w.sumsq + (int64_t)c0 * apply_tiles(d); e.tiles_per_mat = apply_tiles(d);
         e.rows = (int)d.m; e.cols = (int)d.n;
         e.lr = hp.lr; e.wd = hp.weight_decay; e.target_rms = hp.target_rms;
         e.ptrs = make_chunk(sc, idx, first + c0, cnt);
@@ -1780,7 +1794,8 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
 
 int run_round_l(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& pools, DebugMat* dbg) {
     for (const Item& it : items) {
-        int rc = it.d.xl ? exact_front(sc, it, pools[it.pool], dbg) : sketch_front(sc, it, dbg);
+        int rc = it.d.xl ? exact_front(sc, it, pools[it.pool], dbg)
+                         : run_normalize(sc, it.d, it.w, (*sc.groups)[it.g].idx, it.first, it.count, dbg);
         if (rc) return rc;
     }
     for (const Pool& pl : pools)
@@ -1794,6 +1809,7 @@ int run_round_l(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
         std::vector<const Item*> sketched;
         for (const Item* it : run)
             if (!it->d.xl) sketched.push_back(it);
+        if (int rc = omega_run(sc, sketched)) return rc;
         if (int rc = sketch_power_run(sc, sketched)) return rc;
     }
     // Q = qr(Y) by two Cholesky-QR passes (fp64 Gram and factorization).

@@ -221,7 +221,7 @@ template <int MF> struct AccSel { using type = f32x4; };
 template <> struct AccSel<32> { using type = f32x16; };
 
 template <int BM, int BN, int WM, int WN, int LAYOUT, class Epi, int MF>
-__global__ void __launch_bounds__(WM * WN * 64, 2)
+__global__ void __launch_bounds__(WM * WN * 64, Epi::kind == EpiKind::ApplyNorm ? 3 : 2)
 gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM, TN = BN / WN, FM = TM / MF, FN = TN / MF;
@@ -276,9 +276,6 @@ gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
         tiles_n = epi.cg.N[cgi] / BN;
         if (bx >= (sh.M / BM) * tiles_n) return;   // whole block, before any barrier
     }
-    int tm, tn;
-    decode_tile(bx, tiles_n, sh.sym, tm, tn);
-    const int m0 = tm * BM, n0 = tn * BN;
     const int kbeg = split * k_chunk;
     int kend = min(K, kbeg + k_chunk);
 
@@ -348,6 +345,13 @@ gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
     // the tiles up to 128 x 128 have the registers for it, and so has the
     // 64 x 512 one (eight waves: the same loads per thread as 64 x 256).
     constexpr bool DEEP = MF == 32 && (BM * BN <= 128 * 128 || (BM == 64 && BN == 512));
+    // One tile per block, except the norm pass, whose blocks walk tiles.
+    constexpr bool WALK = Epi::kind == EpiKind::ApplyNorm;
+    bool more = false;
+    do {
+    int tm, tn;
+    decode_tile(bx, tiles_n, sh.sym, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
     u32x4 ra[LA::N], rb[LB::N];
     u32x4 ra2[LA::N], rb2[LB::N];
 
@@ -575,7 +579,19 @@ gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
         } else {
             psi = epi.psi + (int64_t)z * epi.stride_psi;
             if constexpr (Epi::kind == EpiKind::Apply) {
-                const float t2 = epi.tnorm2[z];
+                float t2;
+                if (epi.need && epi.need[z]) {
+                    // The norm pass's partial sums, in a fixed order.
+                    float p = 0.f;
+                    for (int i = tid; i < epi.tiles_per_mat; i += NT) p += epi.sumsq[(int64_t)z * epi.tiles_per_mat + i];
+                    p = wave_sum(p);
+                    if (lane == 0) red[wave] = p;
+                    lds_barrier();
+                    t2 = 0.f;
+                    for (int q = 0; q < NT / 64; ++q) t2 += red[q];
+                } else {
+                    t2 = epi.tnorm2[z];
+                }
                 scale = t2 > 0.f ? epi.target_rms * sqrtf((float)epi.rows * (float)epi.cols) / sqrtf(t2) : 0.f;
                 w = epi.ptrs.w[z];
             }
@@ -770,6 +786,12 @@ gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
             }
         }
     }
+    if constexpr (WALK) {
+        bx += gridDim.x;
+        more = bx < (sh.M / BM) * tiles_n;
+        if (more) lds_barrier();        // the next tile's staging reuses this one's LDS
+    }
+    } while (WALK && more);
 }
 
 struct EAff : EpiAffine { static constexpr EpiKind kind = EpiKind::Affine; };
@@ -800,7 +822,7 @@ bool take_launch_events(hipEvent_t& start, hipEvent_t& stop) {
 }
 
 template <int BM, int BN, int WM, int WN, int LAYOUT, class E, int MF = 32>
-hipError_t run(Operand A, Operand B, GemmShape sh, int batch, const E& e, hipStream_t s) {
+hipError_t run(Operand A, Operand B, GemmShape sh, int batch, const E& e, hipStream_t s, int max_blocks = 1 << 30) {
     if (sh.M % BM || sh.N % BN || sh.K % BK || sh.k_chunk % BK || batch < 1) return hipErrorInvalidValue;
     const int tm = sh.M / BM, tn = sh.N / BN;
     int tiles = tm * tn;
@@ -808,7 +830,7 @@ hipError_t run(Operand A, Operand B, GemmShape sh, int batch, const E& e, hipStr
         if (tm != tn) return hipErrorInvalidValue;
         tiles = tn * (tn + 1) / 2;
     }
-    dim3 grid(tiles, sh.k_split, batch);
+    dim3 grid(std::min(tiles, max_blocks), sh.k_split, batch);
     hipEvent_t ev0, ev1;
     if (take_launch_events(ev0, ev1))
         hipExtLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, LAYOUT, E, MF>), grid, dim3(WM * WN * 64), 0, s, ev0, ev1, 0,
@@ -991,7 +1013,7 @@ hipError_t launch_gemm_apply_norm(Operand A, Operand B, GemmShape sh, int batch,
                                   const EpiApplyNorm& e, hipStream_t s) {
     EAppN ee;
     static_cast<EpiApplyNorm&>(ee) = e;
-    return run<64, 128, 1, 4, 0>(A, B, sh, batch, ee, s);
+    return run<64, 128, 1, 4, 0>(A, B, sh, batch, ee, s, std::max(16, kNormBlocks / std::max(batch, 1)));
 }
 
 }  // namespace np

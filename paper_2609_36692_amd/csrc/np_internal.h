@@ -72,7 +72,11 @@ struct EpiPartial {
 // weight update W <- W - lr (s T + wd W) with s = rms sqrt(mn) / ||T||_F.
 struct EpiApplyUpdate {
     const half_t* psi; int64_t ld_psi; int64_t stride_psi;
-    const float* tnorm2;                // per matrix ||T||_F^2 (from the norm pass)
+    const float* tnorm2;                // per matrix ||T||_F^2, except where need[z]
+    // need[z] != 0: ||T||_F^2 is the sum of the norm pass's tiles_per_mat
+    // partial sums of matrix z (need null: tnorm2 holds every matrix's).
+    const int* need;
+    const float* sumsq; int tiles_per_mat;
     int rows, cols;                     // real sizes of W
     float lr, wd, target_rms;
     int vec_ok;                         // W rows 16-byte aligned (cols % 4 == 0)
@@ -142,6 +146,9 @@ hipError_t launch_gemm_combine_grouped(TileCfg cfg, int s_dim, const CombineGrou
                                        hipStream_t s);
 hipError_t launch_gemm_apply(Operand A, Operand B, GemmShape sh, int batch,
                              const EpiApplyUpdate& e, hipStream_t s);
+// Up to kNormBlocks blocks, each walking tiles: where no matrix of the launch
+// needs the pass, few blocks start only to leave.
+constexpr int kNormBlocks = 2048;
 hipError_t launch_gemm_apply_norm(Operand A, Operand B, GemmShape sh, int batch,
                                   const EpiApplyNorm& e, hipStream_t s);
 // Grouped symmetric Gram (X X^T with layout 0, Y^T Y with layout 2): shape
@@ -227,22 +234,22 @@ hipError_t launch_psi_col_normalize(const NormArgs& a, int batch, float* part, i
 hipError_t launch_sum_partials(const float* in, int n, float* out, int batch, hipStream_t s,
                                const int* need = nullptr);
 // NormPre-L ||T||_F^2 in closed form (App. B), for several shape groups in
-// one launch: matrix z of the launch is matrix z - zbeg[g] of group g.  With
+// one launch, a block per matrix: matrix z of the launch is matrix z - zbeg[g] of group g.  With
 // the selected Ritz values the first nsel[i] of the descending list ritz[i]
 // (stride ritz_stride), ||T||_F^2 = ||Psi||_F^2 - sum_C (lambda_i - 1),
-// psi2[i * 2] being ||Psi||_F^2.  It is written to tn2[i] unless the selected
-// modes hold more than `frac` of ||Psi||_F^2 (or the result is not
-// positive); need[i] = 1 marks those matrices, whose norm the norm pass over
-// T supplies instead.
+// ||Psi||_F^2 being the sum of the `count` values of psisq[i * stride].  It is
+// written to tn2[i] where the fp16 rounding of Q moves it by little (see the
+// kernel); need[i] = 1 marks the other matrices, whose norm the norm pass
+// over T supplies instead.
 struct LNormGroups {
     int n;
     int zbeg[kMaxItems + 1];
-    const float* psi2[kMaxItems];
+    const float* psisq[kMaxItems]; int64_t stride[kMaxItems]; int count[kMaxItems];
     const float* ritz[kMaxItems]; int64_t ritz_stride[kMaxItems];
     const int* nsel[kMaxItems];
     float* tn2[kMaxItems];
     int* need[kMaxItems];
-    float frac;
+    int unit_rows;              // the active rows of Psi have unit norm (or are zero)
 };
 hipError_t launch_l_norm_closed(const LNormGroups& g, hipStream_t s);
 
@@ -273,14 +280,21 @@ hipError_t launch_momentum_sumsq(const NormArgs& a, int batch, float* part, int6
 hipError_t launch_scaled_cast(const NormArgs& a, int batch, const float* scale, hipStream_t s);
 
 // ------------------------------------------------------ sketch kernels ---
-// Omega^T (l x b) in fp16, zero padded to (l_pad x b_pad), ld = b_pad.
+// Omega^T (l x b) in fp16, zero padded to (l_pad x b_pad), ld = b_pad, for
+// several shape groups of one l in one launch: group g covers launch matrices
+// [zbeg[g], zbeg[g + 1]).
+constexpr int kOmegaIds = 128;
 struct OmegaArgs {
     uint64_t seed; int64_t step;
-    int ids[kChunk];            // matrix id (index in the caller's list)
-    int b, ell, ell_pad; int64_t ld;
-    half_t* out; int64_t stride;
+    int ell, ell_pad;
+    int n;
+    int zbeg[kMaxItems + 1];
+    int b[kMaxItems];
+    int64_t ld[kMaxItems];
+    half_t* out[kMaxItems]; int64_t stride[kMaxItems];
+    int ids[kOmegaIds];         // matrix id (index in the caller's list) per launch matrix
 };
-hipError_t launch_omega_f16(const OmegaArgs& a, int batch, hipStream_t s);
+hipError_t launch_omega_f16(const OmegaArgs& a, hipStream_t s);
 hipError_t launch_omega_f32(uint64_t seed, int64_t step, int id, int64_t b,
                             int ell, float* out, hipStream_t s);
 

@@ -28,33 +28,65 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
     return c;
 }
 
-// Normal variate number e of the stream keyed by (seed, step, id).
-__device__ __forceinline__ float omega_value(uint64_t seed, int64_t step, uint32_t id, int64_t e) {
-    const uint4 ctr = make_uint4((uint32_t)(e >> 2), id, (uint32_t)((uint64_t)step & 0xffffffffu),
+__device__ __forceinline__ uint4 omega_bits(uint64_t seed, int64_t step, uint32_t id, int64_t blk) {
+    const uint4 ctr = make_uint4((uint32_t)blk, id, (uint32_t)((uint64_t)step & 0xffffffffu),
                                  (uint32_t)((uint64_t)step >> 32));
-    const uint4 x = philox4x32_10(ctr, (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32));
-    const int lane = (int)(e & 3);
-    const uint32_t a = lane < 2 ? x.x : x.z;
-    const uint32_t b = lane < 2 ? x.y : x.w;
+    return philox4x32_10(ctr, (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32));
+}
+// Box-Muller: the cosine and the sine normal of one pair of words.
+__device__ __forceinline__ void omega_pair(uint32_t a, uint32_t b, float& zc, float& zs) {
     const float u1 = (float)((a >> 8) + 1u) * 0x1p-24f;
     const float u2 = (float)(b >> 8) * 0x1p-24f;
     const float rad = sqrtf(-2.f * logf(u1));
     float s, c;
     sincospif(2.f * u2, &s, &c);
-    return (lane & 1) ? rad * s : rad * c;
+    zc = rad * c;
+    zs = rad * s;
+}
+// The four normal variates of block blk of the stream keyed by (seed, step, id).
+__device__ __forceinline__ void omega_block(uint64_t seed, int64_t step, uint32_t id, int64_t blk, float (&v)[4]) {
+    const uint4 x = omega_bits(seed, step, id, blk);
+    omega_pair(x.x, x.y, v[0], v[1]);
+    omega_pair(x.z, x.w, v[2], v[3]);
 }
 
-__global__ void omega_f16_kernel(OmegaArgs a) {
+// Normal variate number e of the stream keyed by (seed, step, id).
+__device__ __forceinline__ float omega_value(uint64_t seed, int64_t step, uint32_t id, int64_t e) {
+    const uint4 x = omega_bits(seed, step, id, e >> 2);
+    const int lane = (int)(e & 3);
+    float zc, zs;
+    omega_pair(lane < 2 ? x.x : x.z, lane < 2 ? x.y : x.w, zc, zs);
+    return (lane & 1) ? zs : zc;
+}
+
+__global__ void __launch_bounds__(256) omega_f16_kernel(OmegaArgs a) {
     const int z = blockIdx.y;
-    const int64_t total = (int64_t)a.ell_pad * a.ld;
-    half_t* out = a.out + (int64_t)z * a.stride;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int c = (int)(idx / a.ld);
-        const int64_t i = idx - (int64_t)c * a.ld;
-        float v = 0.f;
-        if (c < a.ell && i < a.b) v = omega_value(a.seed, a.step, (uint32_t)a.ids[z], (int64_t)c * a.b + i);
-        out[idx] = (half_t)v;
+    int g = 0;
+    while (g + 1 < a.n && z >= a.zbeg[g + 1]) ++g;
+    const int64_t ld = a.ld[g], b = a.b[g], total4 = (int64_t)a.ell_pad * ld / 4;
+    half_t* out = a.out[g] + (int64_t)(z - a.zbeg[g]) * a.stride[g];
+    const uint32_t id = (uint32_t)a.ids[z];
+    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < total4; q += (int64_t)gridDim.x * 256) {
+        const int c = (int)(4 * q / ld);
+        const int64_t i = 4 * q - (int64_t)c * ld;
+        half_t v[4] = {(half_t)0.f, (half_t)0.f, (half_t)0.f, (half_t)0.f};
+        if (c < a.ell) {
+            // Four consecutive entries are one generator block when b % 4 == 0.
+            if ((b & 3) == 0) {
+                if (i < b) {
+                    float x[4];
+                    omega_block(a.seed, a.step, id, ((int64_t)c * b + i) >> 2, x);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = (half_t)x[e];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < b) v[e] = (half_t)omega_value(a.seed, a.step, id, (int64_t)c * b + i + e);
+            }
+        }
+        typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+        *(f16x4*)(out + 4 * q) = f16x4{v[0], v[1], v[2], v[3]};
     }
 }
 
@@ -606,10 +638,15 @@ __global__ void __launch_bounds__(256) small_mul_kernel(SmallMulArgs args) {
 
 }  // namespace
 
-hipError_t launch_omega_f16(const OmegaArgs& a, int batch, hipStream_t s) {
-    const int64_t total = (int64_t)a.ell_pad * a.ld;
-    const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 4096);
-    hipLaunchKernelGGL(omega_f16_kernel, dim3(blocks, batch), dim3(256), 0, s, a);
+hipError_t launch_omega_f16(const OmegaArgs& a, hipStream_t s) {
+    if (a.n < 1 || a.n > kMaxItems || a.zbeg[0] != 0 || a.zbeg[a.n] > kOmegaIds) return hipErrorInvalidValue;
+    int64_t most = 0;
+    for (int g = 0; g < a.n; ++g) {
+        if (a.zbeg[g + 1] <= a.zbeg[g] || a.ld[g] % 4 || a.stride[g] % 4) return hipErrorInvalidValue;
+        most = std::max(most, (int64_t)a.ell_pad * a.ld[g] / 4);
+    }
+    const unsigned blocks = (unsigned)std::min<int64_t>((most + 255) / 256, 1024);
+    hipLaunchKernelGGL(omega_f16_kernel, dim3(blocks, a.zbeg[a.n]), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

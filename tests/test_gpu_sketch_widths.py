@@ -75,3 +75,34 @@ def test_equal_ritz_values(ctx, groups, rank, oversample):
     m[torch.arange(a), torch.arange(a) % groups] = 2.0
     w = torch.zeros_like(m)
     _step(ctx, [(w, m, torch.zeros_like(m))], 0, rank, oversample)
+
+
+# ||T||_F in closed form and by the norm pass on both sides of the rule: rank-8
+# signal plus noise of falling size (the selected modes hold more and more of
+# ||Psi||^2, down to exact low rank), spread over all entries or on few columns
+# (eigenvectors with large entries).  The update's RMS is the target up to the
+# norm that was used: 1.25e-4 rms by the rule, four times that allowed.
+@pytest.mark.parametrize("noise", [0.5, 0.1, 0.01, 0.001, 0.0])
+@pytest.mark.parametrize("spread", ["dense", "columns"])
+@pytest.mark.parametrize("t", [0, 1])
+def test_update_rms_of_low_rank_signals(ctx, noise, spread, t):
+    print(f"L update RMS noise={noise} {spread} t={t}", flush=True)
+    g = torch.Generator().manual_seed(11)
+    m, n = (512, 700) if t == 0 else (700, 512)
+    sig = torch.randn(m, 8, generator=g) @ torch.randn(8, n, generator=g)
+    if spread == "columns":
+        keep = torch.zeros(m, n)
+        keep[:, :12] = 1.0
+        keep[:12, :] = 1.0
+        sig = sig * keep
+    grad = sig + noise * torch.randn(m, n, generator=g)
+    w = 0.02 * torch.randn(m, n, generator=g)
+    mat = (w, grad, torch.zeros_like(w))
+    W, G, M = (x.cuda().clone() for x in mat)
+    hp = N.normpre_default_hparams(lr=1.0, weight_decay=0.0, step=t, rank=32)
+    N.normpre_step(ctx, N.NORMPRE_VARIANT_L, [W], [G], [M], hp)
+    torch.cuda.synchronize()
+    u = w.double() - W.cpu().double()
+    rms = float(torch.linalg.vector_norm(u)) / math.sqrt(m * n)
+    print(f"  rms {rms:.6f}", flush=True)
+    assert abs(rms / 0.2 - 1.0) < 5e-4
