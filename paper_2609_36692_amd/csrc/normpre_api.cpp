@@ -403,6 +403,7 @@ bool gram_space_ns(int variant, const Dims& d, const normpre_hparams& hp) {
 int ns_tiles(const Dims& d) { return (int)((d.mp / 128) * (d.np_ / 128)); }
 // Tiles of the NormPre-L apply passes (64 x 128).
 int apply_tiles(const Dims& d) { return (int)((d.mp / 64) * (d.np_ / 128)); }
+int small_tiles(const Dims& d) { return (int)((d.mp / 64) * (d.np_ / 64)); }
 int combine_tiles(const Dims& d, TileCfg cfg) {
     const int64_t t = cfg == TileCfg::Big256 ? 256 : 128;
     return (int)((d.mp / t) * (d.np_ / t));
@@ -431,6 +432,8 @@ struct Item {
     int pool_off = 0;     // its first matrix inside the pool
     TileCfg ccfg = TileCfg::Big;   // tile of its Newton-Schulz combines
     bool gns = false;     // Newton-Schulz iterations carried in Gram space
+    bool small = false;   // Newton-Schulz by the grouped 64 x 64 tile launches
+    int q_off = 0;        // its first Q and R slot of the pool (gns)
     int eig = -1;         // eigenproblem group of its pool (d.xl)
     int eig_off = 0;      // its first matrix inside the group
 };
@@ -458,8 +461,12 @@ struct Pool {
     half_t* amat = nullptr;
     half_t* bmat = nullptr;
     // Gram-space Newton-Schulz: its items hold pool slots [0, gns_count);
-    // Q (double buffered, qcur the current one) and the product R.
+    // Q (double buffered, qcur the current one) and the product R.  The small
+    // items hold the last slots, from small_off on (and, in Gram space, slots of
+    // Q and R behind the others': qslots in all).
     int gns_count = 0;
+    int qslots = 0;
+    int small_off = 0;
     half_t* qmat[2] = {nullptr, nullptr};
     half_t* rmat = nullptr;
     int qcur = 0;
@@ -504,7 +511,7 @@ void carve_item(Arena& ar, Item& it, int variant, int opts) {
     w.psisq = ar.take<float>(count * d.lp_);
     w.scale = ar.take<float>(count * 2);
     w.colpart = ar.take<double>(count * normalize_cols_partials((int)d.m, (int)d.np_, kColRowChunk));
-    w.sumsq = ar.take<float>(count * std::max(ns_tiles(d), apply_tiles(d)));
+    w.sumsq = ar.take<float>(count * (it.small ? small_tiles(d) : std::max(ns_tiles(d), apply_tiles(d))));
     w.tn2 = ar.take<float>(count);
     if (opts & kOptCheck) w.nfin = ar.take<int>(count * nfin_stride(d));
     if (variant == NORMPRE_VARIANT_G || variant == NORMPRE_VARIANT_MUON) {
@@ -550,8 +557,8 @@ void carve_pool(Arena& ar, Pool& p, int variant) {
     if (variant == NORMPRE_VARIANT_G || variant == NORMPRE_VARIANT_MUON) {
         p.amat = ar.take<half_t>(c * p.sp * p.sp);
         p.bmat = ar.take<half_t>(c * p.sp * p.sp);
-        if (p.gns_count > 0) {
-            const int64_t gc = p.gns_count;
+        if (p.qslots > 0) {
+            const int64_t gc = p.qslots;
             p.qmat[0] = ar.take<half_t>(gc * p.sp * p.sp);
             p.qmat[1] = ar.take<half_t>(gc * p.sp * p.sp);
             p.rmat = ar.take<half_t>(gc * p.sp * p.sp);
@@ -626,13 +633,18 @@ std::vector<Pool> make_pools(std::vector<Item>& items, int variant) {
     }
     // Gram-space items take the first slots of their pool, so their s x s
     // matrices form one contiguous range (one launch per Gram-space product).
-    for (int pass = 0; pass < 2; ++pass)
+    for (int pass = 0; pass < 3; ++pass)
         for (Item& it : items) {
-            if (it.gns != (pass == 0)) continue;
+            if ((it.small ? 2 : it.gns ? 0 : 1) != pass) continue;
             Pool& p = pools[it.pool];
             it.pool_off = p.count;
             p.count += it.count;
-            if (it.gns) p.gns_count += it.count;
+            if (!it.small) p.small_off = p.count;
+            if (it.gns) {
+                it.q_off = p.qslots;
+                p.qslots += it.count;
+                if (!it.small) p.gns_count += it.count;
+            }
             if (variant != NORMPRE_VARIANT_L || !it.d.xl) continue;
             it.eig = -1;
             for (size_t q = 0; q < p.eig.size(); ++q)
@@ -665,7 +677,44 @@ size_t carve_round(Arena& ar, std::vector<Item>& items, std::vector<Pool>& pools
     return ar.off + 256;
 }
 
-size_t round_bytes(std::vector<Item> items, int variant, int opts) {
+// Newton-Schulz items of a round whose products are too small to fill the chip
+// for longer than their launches take share grouped launches on 64 x 64 tiles, one
+// per stage of the iteration for all of them: the smallest first, within
+// kSmallFlops nominal FLOPs per iteration (4 s^2 L + 2 s^3 of the padded sizes)
+// and within 256 + 256 tiles per item (1536 per Gram-space item, whose s x s
+// products have far fewer tiles than its combines).  NormPre-G steps in us,
+// launches per pool and item against grouped ones: one 256^2 matrix 123 / 109, one
+// 1024^2 216 / 184, one 1280^2 (400 tiles) 255 / 219, eight of 512^2 (512 tiles)
+// 161 / 154, four of 768^2 (576 tiles) 199 / 220; Gram-space: one 512 x 2048 214 /
+// 161, four of 256 x 8192 301 / 239, two of 1024 x 2048 303 / 298, eight of
+// 512 x 2048 (2048 tiles) 263 / 259; five shapes of three matrices 596 / 254.
+constexpr double kSmallFlops = 22e9;
+void mark_small(std::vector<Item>& items, int variant, const normpre_hparams& hp, bool allow = true) {
+    for (Item& it : items) {
+        it.small = false;
+        it.gns = gram_space_ns(variant, it.d, hp);
+    }
+    if (!allow || (variant != NORMPRE_VARIANT_G && variant != NORMPRE_VARIANT_MUON)) return;
+    auto work = [](const Item* it) {
+        const double s = (double)it->d.sp, l = (double)it->d.lp_;
+        return it->count * (4.0 * s * s * l + 2.0 * s * s * s);
+    };
+    std::vector<Item*> by;
+    for (Item& it : items) by.push_back(&it);
+    std::stable_sort(by.begin(), by.end(), [&](const Item* a, const Item* b) { return work(a) < work(b); });
+    double sum = 0.0;
+    int64_t tiles = 0, most = 256;
+    for (Item* it : by) {
+        sum += work(it);
+        tiles += it->count * (int64_t)small_tiles(it->d);
+        most += it->gns ? 1536 : 256;
+        if (sum > kSmallFlops || tiles > most) break;
+        it->small = true;
+    }
+}
+
+size_t round_bytes(std::vector<Item> items, int variant, int opts, const normpre_hparams& hp, bool allow_small = true) {
+    mark_small(items, variant, hp, allow_small);
     std::vector<Pool> pools = make_pools(items, variant);
     Arena ar{nullptr, 0, 0};
     return carve_round(ar, items, pools, variant, opts);
@@ -784,14 +833,6 @@ int run_normalize(const StepCtx& sc, const Dims& d, const GWork& w, const std::v
                    "non-finite counts");
         }
     }
-    // (NormPre-L takes ||Psi||_F^2 from psisq itself.)
-    if (sc.variant != NORMPRE_VARIANT_L)
-        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
-                     [&] {
-                         return launch_psi_scale(w.psisq, d.lp_, both ? (int)d.n : (int)d.a, sc.hp->ns_eps, w.scale,
-                                                 count, sc.s);
-                     }),
-               "psi scale");
     if (w.xs) {
         // Interaction source X: X_s = sqrt(a / ||X||_F^2) D Psi, so that
         // X_s X_s^T is the trace-matched Gram of the active rows.
@@ -931,7 +972,7 @@ int gram_launches(const StepCtx& sc, const std::vector<Item>& items, const std::
         for (int tall = 0; tall < 2; ++tall) {
             std::vector<const Item*> its;
             for (const Item& it : items)
-                if (it.pool == (int)pi && (int)it.d.tall == tall &&
+                if (it.pool == (int)pi && !it.small && (int)it.d.tall == tall &&
                     (!it.gns || iter == 0 || iter == kGnsRestart)) {
                     its.push_back(&it);
                     if ((int)its.size() == kMaxGramGroups) {
@@ -1011,7 +1052,7 @@ std::vector<std::vector<Item*>> wide_combine_chunks(std::vector<Item>& items, si
     for (size_t pi = 0; pi < npools; ++pi) {
         std::vector<Item*> cur;
         for (Item& it : items) {
-            if (it.pool != (int)pi || it.d.tall || it.gns) continue;
+            if (it.pool != (int)pi || it.small || it.d.tall || it.gns) continue;
             cur.push_back(&it);
             if ((int)cur.size() == kMaxItems) {
                 chunks.push_back(cur);
@@ -1104,7 +1145,7 @@ int gns_iteration(const StepCtx& sc, const std::vector<Item>& items, Pool& pl, i
     const bool seg_end = iter == kGnsRestart - 1 || iter == q - 1;
     double flops = 0.0;
     for (const Item& it : items)
-        if (it.pool == pi && it.gns) {
+        if (it.pool == pi && it.gns && !it.small) {
             const double s_ = (double)std::min(it.d.m, it.d.n);
             flops += 2.0 * s_ * s_ * s_ * it.count;
         }
@@ -1126,11 +1167,39 @@ int gns_iteration(const StepCtx& sc, const std::vector<Item>& items, Pool& pl, i
     }
     const bool first_seg = iter < kGnsRestart;
     for (const Item& it : items) {
-        if (it.pool != pi || !it.gns) continue;
+        if (it.pool != pi || !it.gns || it.small) continue;
         half_t* x = first_seg ? it.w.psi : it.w.xb;
         half_t* xn = first_seg ? it.w.xb : it.w.psi;
         if (int rc = combine_launch(sc, it, pl.qmat[pl.qcur], x, xn, first_seg && fold_scale, iter == q - 1, 0.f))
             return rc;
+    }
+    return NORMPRE_OK;
+}
+
+// One sum per matrix of every item, kMaxItems items per launch: ||T||_F^2 from the
+// last combine's per-tile sums, or (psi) ||Psi||_F^2 and the pre-scale from the
+// active rows' squared norms.
+int sum_launches(const StepCtx& sc, const std::vector<Item>& items, bool psi) {
+    const bool both = sc.hp->orientation == NORMPRE_ORIENT_BOTH;
+    for (size_t i0 = 0; i0 < items.size(); i0 += kMaxItems) {
+        SumGroups g{};
+        g.scaled = psi;
+        g.eps = sc.hp->ns_eps;
+        for (size_t i = i0; i < std::min(items.size(), i0 + kMaxItems); ++i) {
+            const Item& it = items[i];
+            const int k = g.n++;
+            g.zbeg[k + 1] = g.zbeg[k] + it.count;
+            if (psi) {
+                g.in[k] = it.w.psisq; g.stride[k] = it.d.lp_; g.len[k] = both ? (int)it.d.n : (int)it.d.a;
+                g.out[k] = it.w.scale;
+            } else {
+                g.len[k] = it.small ? small_tiles(it.d) : combine_tiles(it.d, it.ccfg);
+                g.in[k] = it.w.sumsq; g.stride[k] = g.len[k];
+                g.out[k] = it.w.tn2;
+            }
+        }
+        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0, [&] { return launch_sum_groups(g, sc.s); }),
+               psi ? "psi scale" : "t norm");
     }
     return NORMPRE_OK;
 }
@@ -1146,15 +1215,10 @@ int g_update_launch(const StepCtx& sc, const Item& it, const half_t* t, DebugMat
     const float* tn2 = it.w.tn2;
     int64_t tn2_stride = 1;
     float fixed_scale = 0.f;
-    if (sc.variant == NORMPRE_VARIANT_G) {
-        const int t_tiles = combine_tiles(d, it.ccfg);
-        NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
-                     [&] { return launch_sum_partials(it.w.sumsq, t_tiles, it.w.tn2, count, sc.s); }),
-               "t norm");
-    } else if (sc.variant == NORMPRE_VARIANT_NORMALIZE_ONLY) {
+    if (sc.variant == NORMPRE_VARIANT_NORMALIZE_ONLY) {
         tn2 = it.w.scale + 1;
         tn2_stride = 2;
-    } else {
+    } else if (sc.variant == NORMPRE_VARIANT_MUON) {
         fixed_scale = hp.target_rms * std::sqrt((float)std::max(d.m, d.n));
     }
     for (int c0 = 0; c0 < count; c0 += kChunk) {
@@ -1202,6 +1266,147 @@ int g_update_launch(const StepCtx& sc, const Item& it, const half_t* t, DebugMat
     return NORMPRE_OK;
 }
 
+// The Newton-Schulz iterations of the small items.  Each item is a list of
+// stages, the products of one stage being independent (the plain iteration:
+// A = X X^T or X^T X, B = b A + c A^2, X <- a X + B X or a X + X B; or the
+// Gram-space one, with Q and R's products of an iteration in one stage); launch k
+// holds stage k of every item, up to kMaxItems products.
+struct SmallProduct {
+    const Item* it;
+    int kclass;
+    const half_t *a, *b, *src;
+    half_t* out;
+    int M, N, K, lda, ldb, layout;      // out's rows are N long
+    int64_t a_stride, b_stride, out_stride;
+    bool sym, scaled, sums;
+    float ca, cs, diag;
+};
+
+std::vector<std::vector<SmallProduct>> small_stages(const StepCtx& sc, const Item& it, const Pool& pl, int q,
+                                                    bool fold_scale) {
+    const Dims& d = it.d;
+    const float a = sc.hp->ns_coeffs[0], b = sc.hp->ns_coeffs[1], c = sc.hp->ns_coeffs[2];
+    const int np = (int)d.np_, mp = (int)d.mp, sp = (int)d.sp;
+    const int64_t mn = d.mp * d.np_, ss = d.sp * d.sp;
+    half_t* am = pl.amat + it.pool_off * ss;
+    half_t* bm = pl.bmat + it.pool_off * ss;
+    std::vector<std::vector<SmallProduct>> st;
+    auto gram = [&](const half_t* x, bool first) {
+        st.push_back({{&it, NORMPRE_KCLASS_NS_GRAM, x, x, nullptr, am, sp, sp, (int)d.lp_, np, np, d.tall ? 2 : 0, mn,
+                       mn, ss, true, first, false, 1.f, 0.f, 0.f}});
+    };
+    // out = ca L R + cs src on the s x s matrices (diag: + diag I).
+    auto square = [&](const half_t* l, const half_t* r, const half_t* src, half_t* out, float ca, float cs, float diag) {
+        return SmallProduct{&it, NORMPRE_KCLASS_NS_POLY, l, r, src, out, sp, sp, sp, sp, sp, 0, ss, ss, ss,
+                            true, false, false, ca, cs, diag};
+    };
+    auto combine = [&](const half_t* s, const half_t* x, half_t* xn, float cs, bool first, bool last) {
+        SmallProduct p{&it, NORMPRE_KCLASS_NS_COMBINE, s, x, cs != 0.f ? x : nullptr, xn, mp, np, sp, sp, np, 1, ss,
+                       mn, mn, false, first, last, 1.f, cs, 0.f};
+        if (d.tall) {
+            std::swap(p.a, p.b); std::swap(p.lda, p.ldb); std::swap(p.a_stride, p.b_stride);
+            p.layout = 0;
+        }
+        st.push_back({p});
+    };
+    if (!it.gns) {
+        for (int i = 0; i < q; ++i) {
+            half_t* x = (i & 1) ? it.w.xb : it.w.psi;
+            half_t* xn = (i & 1) ? it.w.psi : it.w.xb;
+            gram(x, i == 0 && fold_scale);
+            st.push_back({square(am, am, am, bm, c, b, 0.f)});
+            combine(bm, x, xn, a, i == 0 && fold_scale, i == q - 1);
+        }
+        return st;
+    }
+    half_t* qm[2] = {pl.qmat[0] + it.q_off * ss, pl.qmat[1] + it.q_off * ss};
+    half_t* rm = pl.rmat + it.q_off * ss;
+    int cur = 0;
+    for (int i = 0; i < q; ++i) {
+        const bool seg_start = i == 0 || i == kGnsRestart, seg_end = i == kGnsRestart - 1 || i == q - 1;
+        half_t* x = i < kGnsRestart ? it.w.psi : it.w.xb;
+        half_t* xn = i < kGnsRestart ? it.w.xb : it.w.psi;
+        const bool first = i < kGnsRestart && fold_scale;
+        if (seg_start) {
+            gram(x, first);
+            st.push_back({square(am, am, am, qm[0], c, b, a)});
+            cur = 0;
+        } else {
+            st.push_back({square(am, am, am, bm, c, b, 0.f)});
+            st.push_back({square(bm, qm[cur], qm[cur], qm[1 - cur], 1.f, a, 0.f)});
+            cur = 1 - cur;
+        }
+        if (seg_end) {
+            combine(qm[cur], x, xn, 0.f, first, i == q - 1);
+            continue;
+        }
+        const half_t* left = seg_start ? qm[0] : bm;
+        const float cs = seg_start ? 0.f : a;
+        const SmallProduct r = square(left, am, seg_start ? nullptr : am, rm, 1.f, cs, 0.f);
+        if (seg_start) st.push_back({r});
+        else st.back().push_back(r);
+        st.push_back({square(left, rm, seg_start ? nullptr : rm, am, 1.f, cs, 0.f)});
+    }
+    return st;
+}
+
+int small_launch(const StepCtx& sc, const std::vector<SmallProduct>& ps) {
+    SmallJobs j{};
+    double flops = 0.0, issued = 0.0, bytes = 0.0, most = -1.0;
+    int kclass = NORMPRE_KCLASS_NS_POLY;        // the largest product's
+    for (const SmallProduct& p : ps) {
+        const Item& it = *p.it;
+        const int g = j.n++;
+        j.zbeg[g + 1] = j.zbeg[g] + it.count;
+        SmallJob& o = j.job[g];
+        o.a = p.a; o.lda = p.lda; o.a_stride = p.a_stride;
+        o.b = p.b; o.ldb = p.ldb; o.b_stride = p.b_stride;
+        o.src = p.src; o.out = p.out; o.ld_out = p.N; o.out_stride = p.out_stride;
+        o.M = p.M; o.N = p.N; o.K = p.K; o.layout = p.layout; o.sym = p.sym;
+        o.mul = p.scaled ? it.w.scale : nullptr;
+        o.mul_pow = p.scaled ? (p.kclass == NORMPRE_KCLASS_NS_GRAM ? 2 : 1) : 0;
+        o.sumsq = p.sums ? it.w.sumsq : nullptr;
+        o.ca = p.ca; o.cs = p.cs; o.diag = p.diag;
+        const double s_ = (double)std::min(it.d.m, it.d.n), l_ = (double)std::max(it.d.m, it.d.n);
+        const bool poly = p.kclass == NORMPRE_KCLASS_NS_POLY, comb = p.kclass == NORMPRE_KCLASS_NS_COMBINE;
+        const double f = 2.0 * s_ * s_ * (poly ? s_ : l_) * it.count;
+        flops += f;
+        bytes += (poly ? (p.src == p.a ? 4.0 : 6.0) * s_ * s_ : 2.0 * ((comb ? 2.0 : 1.0) * s_ * l_ + s_ * s_)) * it.count;
+        const double tn = p.N / 64, tiles = p.sym ? tn * (tn + 1) / 2 : (p.M / 64) * tn;
+        issued += tiles * 8192.0 * p.K * it.count;
+        if (f > most) {
+            most = f;
+            kclass = p.kclass;
+        }
+    }
+    NP_TRY(timed(sc.ctx, kclass, flops, bytes, [&] { return launch_small_jobs(j, sc.s); }, issued), "ns small products");
+    return NORMPRE_OK;
+}
+
+int small_iterations(const StepCtx& sc, const std::vector<Item>& items, const std::vector<Pool>& pools, int q,
+                     bool fold_scale) {
+    std::vector<std::vector<std::vector<SmallProduct>>> lists;
+    size_t stages = 0;
+    for (const Item& it : items)
+        if (it.small) {
+            lists.push_back(small_stages(sc, it, pools[it.pool], q, fold_scale));
+            stages = std::max(stages, lists.back().size());
+        }
+    for (size_t k = 0; k < stages; ++k) {
+        std::vector<SmallProduct> ps;
+        for (const auto& l : lists) {
+            if (k >= l.size()) continue;
+            if (ps.size() + l[k].size() > (size_t)kMaxItems) {
+                if (int rc = small_launch(sc, ps)) return rc;
+                ps.clear();
+            }
+            ps.insert(ps.end(), l[k].begin(), l[k].end());
+        }
+        if (int rc = small_launch(sc, ps)) return rc;
+    }
+    return NORMPRE_OK;
+}
+
 // NormPre-G, and the Muon and normalize-only reference steps, which share
 // its stages: input (normalize, or Muon's momentum + Frobenius scaling),
 // q Newton-Schulz iterations (none for normalize-only), update.
@@ -1212,6 +1417,8 @@ int run_round_g(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
                      : run_normalize(sc, it.d, it.w, (*sc.groups)[it.g].idx, it.first, it.count, dbg);
         if (rc) return rc;
     }
+    if (sc.variant != NORMPRE_VARIANT_MUON)
+        if (int rc = sum_launches(sc, items, true)) return rc;
     // Muon's X0 is scaled when it is written; NormPre-G folds 1/||Psi||_F
     // into the first iteration's epilogues.
     const bool fold_scale = sc.variant == NORMPRE_VARIANT_G;
@@ -1221,15 +1428,17 @@ int run_round_g(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
     for (Item& it : items)
         if (it.d.tall || it.gns) it.ccfg = ns_cfg(it.d.mp, it.d.np_, it.d.sp, false, it.count);
     const auto wide = wide_combine_chunks(items, pools.size());
+    if (int rc = small_iterations(sc, items, pools, q, fold_scale)) return rc;
     for (int iter = 0; iter < q; ++iter) {
         const bool first_it = iter == 0 && fold_scale, last_it = iter == q - 1;
         int rc = gram_launches(sc, items, pools, iter, first_it);
         if (rc) return rc;
         for (size_t pi = 0; pi < pools.size(); ++pi) {
             Pool& pl = pools[pi];
+            if (pl.small_off == 0) continue;
             double fg = 0.0, fs = 0.0;
             for (const Item& it : items)
-                if (it.pool == (int)pi) {
+                if (it.pool == (int)pi && !it.small) {
                     const double s_ = (double)std::min(it.d.m, it.d.n);
                     (it.gns ? fg : fs) += 2.0 * s_ * s_ * s_ * it.count;
                 }
@@ -1237,9 +1446,9 @@ int run_round_g(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
             // straight into Q's first buffer (Q_{k+1} = B_k + a I).
             const bool split = pl.gns_count > 0 && (iter == 0 || iter == kGnsRestart);
             int rc = split ? poly_launch(sc, pl, 0, pl.gns_count, pl.qmat[0], fg)
-                           : poly_launch(sc, pl, 0, pl.count, pl.bmat, fg + fs);
-            if (!rc && split && pl.count > pl.gns_count)
-                rc = poly_launch(sc, pl, pl.gns_count, pl.count - pl.gns_count,
+                           : poly_launch(sc, pl, 0, pl.small_off, pl.bmat, fg + fs);
+            if (!rc && split && pl.small_off > pl.gns_count)
+                rc = poly_launch(sc, pl, pl.gns_count, pl.small_off - pl.gns_count,
                                  pl.bmat + (int64_t)pl.gns_count * pl.sp * pl.sp, fs);
             if (rc) return rc;
         }
@@ -1254,7 +1463,7 @@ int run_round_g(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
             if (rc) return rc;
         }
         for (const Item& it : items) {
-            if (!it.d.tall || it.gns) continue;
+            if (!it.d.tall || it.gns || it.small) continue;
             half_t* x = (iter & 1) ? it.w.xb : it.w.psi;
             half_t* xn = (iter & 1) ? it.w.psi : it.w.xb;
             int rc = combine_launch(sc, it, pools[it.pool].bmat, x, xn, first_it, last_it, sc.hp->ns_coeffs[0]);
@@ -1265,6 +1474,8 @@ int run_round_g(const StepCtx& sc, std::vector<Item>& items, std::vector<Pool>& 
             if (int rc = gns_iteration(sc, items, pools[pi], (int)pi, iter, q, fold_scale)) return rc;
         }
     }
+    if (sc.variant == NORMPRE_VARIANT_G)
+        if (int rc = sum_launches(sc, items, false)) return rc;
     for (const Item& it : items) {
         // Gram-space items end with T in psi (their second segment writes it).
         const half_t* t = it.gns ? it.w.psi : (q & 1) ? it.w.xb : it.w.psi;
@@ -2017,8 +2228,9 @@ Plan plan_step(int variant, int num_mats, const int64_t* shapes, const normpre_h
         one.g = (int)g;
         one.count = 1;
         one.d = d;
-        one.gns = gram_space_ns(variant, d, hp);
-        const size_t per = round_bytes({one}, variant, opts);
+        // Whichever way the batch will run (the whole item decides, not one
+        // matrix of it).
+        const size_t per = std::max(round_bytes({one}, variant, opts, hp), round_bytes({one}, variant, opts, hp, false));
         pl.one_matrix = std::max(pl.one_matrix, per);
         const int b = (int)std::max<size_t>(1, std::min<size_t>((size_t)cnt, item_budget / std::max<size_t>(per, 1)));
         for (int first = 0; first < cnt; first += b) {
@@ -2027,7 +2239,6 @@ Plan plan_step(int variant, int num_mats, const int64_t* shapes, const normpre_h
             it.first = first;
             it.count = std::min(b, cnt - first);
             it.d = d;
-            it.gns = one.gns;
             all.push_back(it);
         }
     }
@@ -2037,7 +2248,7 @@ Plan plan_step(int variant, int num_mats, const int64_t* shapes, const normpre_h
         if (!pl.rounds.empty()) {
             std::vector<Item> trial = pl.rounds.back();
             trial.push_back(it);
-            const size_t bytes = round_bytes(trial, variant, opts);
+            const size_t bytes = round_bytes(trial, variant, opts, hp);
             if (bytes <= round_budget) {
                 pl.rounds.back().push_back(it);
                 pl.need = std::max(pl.need, bytes);
@@ -2045,7 +2256,7 @@ Plan plan_step(int variant, int num_mats, const int64_t* shapes, const normpre_h
             }
         }
         pl.rounds.push_back({it});
-        pl.need = std::max(pl.need, round_bytes(pl.rounds.back(), variant, opts));
+        pl.need = std::max(pl.need, round_bytes(pl.rounds.back(), variant, opts, hp));
     }
     if (opts & kOptCheck) pl.need += status_bytes(num_mats);
     return pl;
@@ -2095,6 +2306,7 @@ int run_plan(normpre_ctx* ctx, int variant, Plan& plan, float* const* params, co
     ctx->stream = s;
     StepCtx sc{ctx, s, hp, params, grads, momentum, variant, debug, &plan.groups, status};
     for (std::vector<Item>& items : plan.rounds) {
+        mark_small(items, variant, *hp);
         std::vector<Pool> pools = make_pools(items, variant);
         Arena ar{static_cast<char*>(ws) + front, 0, ws_bytes - front};
         carve_round(ar, items, pools, variant, opts);

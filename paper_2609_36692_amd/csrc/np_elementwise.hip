@@ -799,6 +799,28 @@ __global__ void __launch_bounds__(256) sum_partials_kernel(const float* in, int 
     if (threadIdx.x == 0) out[z] = red[0] + red[1] + red[2] + red[3];
 }
 
+__global__ void __launch_bounds__(256) sum_groups_kernel(SumGroups g) {
+    int gi = 0;
+    while (gi + 1 < g.n && (int)blockIdx.x >= g.zbeg[gi + 1]) ++gi;
+    const int z = blockIdx.x - g.zbeg[gi];
+    const float* p = g.in[gi] + (int64_t)z * g.stride[gi];
+    float s = 0.f;
+    for (int i = threadIdx.x; i < g.len[gi]; i += 256) s += p[i];
+    s = wave_sum_f(s);
+    __shared__ float red[4];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const float tot = red[0] + red[1] + red[2] + red[3];
+        if (g.scaled) {
+            g.out[gi][2 * z] = 1.f / (sqrtf(tot) + g.eps);
+            g.out[gi][2 * z + 1] = tot;
+        } else {
+            g.out[gi][z] = tot;
+        }
+    }
+}
+
 // One block per matrix: the closed-form ||T||_F^2 of NormPre-L and whether the
 // norm pass has to supply it (see LNormGroups).  Sums in fp64.
 // What the closed form leaves out is that the apply uses Q rounded to fp16:
@@ -1211,6 +1233,14 @@ hipError_t launch_g_update(const GUpdateArgs& a, int batch, hipStream_t s) {
 
 hipError_t launch_sum_partials(const float* in, int n, float* out, int batch, hipStream_t s, const int* need) {
     hipLaunchKernelGGL(sum_partials_kernel, dim3(batch), dim3(256), 0, s, in, n, out, need);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_groups(const SumGroups& g, hipStream_t s) {
+    if (g.n < 1 || g.n > kMaxItems || g.zbeg[0] != 0) return hipErrorInvalidValue;
+    for (int i = 0; i < g.n; ++i)
+        if (g.zbeg[i + 1] <= g.zbeg[i] || !g.in[i] || !g.out[i]) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sum_groups_kernel, dim3(g.zbeg[g.n]), dim3(256), 0, s, g);
     return hipGetLastError();
 }
 

@@ -17,6 +17,8 @@
 // All sizes are multiples of the tile sizes (the workspace is zero padded).
 #include "np_internal.h"
 
+#include <climits>
+
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -87,7 +89,7 @@ struct MNMajorLoader {
     static constexpr bool kTrans = true;
     static constexpr int CH = R / 8;                 // 16-byte chunks per row
     static constexpr int N = R * BK / 8 / NT;
-    static_assert(R >= 128 && N >= 1 && R * BK / 8 % NT == 0 && NT % CH == 0, "unsupported MN-major tile");
+    static_assert(R >= 64 && N >= 1 && R * BK / 8 % NT == 0 && NT % CH == 0, "unsupported MN-major tile");
     static __device__ __forceinline__ int mswz(int k) { return (4 * (k & 3)) & (CH - 1); }
     static __device__ __forceinline__ void load_item(u32x4 (&r)[N], const half_t* base, int64_t ld, int row0, int k0,
                                                      int tid, int i) {
@@ -794,6 +796,143 @@ gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
     } while (WALK && more);
 }
 
+// ---------------------------------------------- small Newton-Schulz jobs ---
+// One 64 x 64 tile per block of four waves (32 x 32 each), whatever the job's
+// layout: the products of a stage of all small matrices of a step are one
+// launch, since at these sizes a launch costs more (5 to 8 us each in a chain of
+// dependent launches) than its products, and 64-wide tiles give a 256 x 256
+// matrix sixteen CUs.  Bound by the chain of launches: 5.9 us each at 256 x 256
+// (the fifteen of five iterations 88 us; with 128-wide tiles 98).  Operands are
+// staged as in gemm_kernel (two LDS stages, global loads three K-steps ahead);
+// results are stored from the accumulators.
+template <int LAYOUT>
+__device__ __forceinline__ void small_tile(const half_t* Ab, int lda, const half_t* Bb, int ldb, int m0, int n0,
+                                           int K, half_t* sbase, f32x16& acc) {
+    constexpr int NT = 256;
+    using LA = typename LoaderSel<(LAYOUT == 2), 64, NT>::type;
+    using LB = typename LoaderSel<(LAYOUT >= 1), 64, NT>::type;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    constexpr int kStage = 2 * 64 * BK;     // halves
+    u32x4 ra[LA::N], rb[LB::N], ra2[LA::N], rb2[LB::N];
+    const int nk = K / BK;
+    auto kat = [&](int j) { return min(j, nk - 1) * BK; };
+    auto kstep = [&](int stage, bool store, bool load, int k_load, auto& rA, auto& rB) {
+        const half_t* ca = sbase + stage * kStage;
+        const half_t* cb = ca + 64 * BK;
+        half_t* sa = sbase + (stage ^ 1) * kStage;
+        f16x8 af[BK / 16], bf[BK / 16];
+#pragma unroll
+        for (int s = 0; s < BK / 16; ++s) {
+            af[s] = LA::frag(ca, 32 * wm, s, lane);
+            bf[s] = LB::frag(cb, 32 * wn, s, lane);
+        }
+        if (store) {
+            LA::store(rA, sa, tid);
+            LB::store(rB, sa + 64 * BK, tid);
+            if (load) {
+                LA::load(rA, Ab, lda, m0, k_load, tid);
+                LB::load(rB, Bb, ldb, n0, k_load, tid);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < BK / 16; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[s], bf[s], acc, 0, 0, 0);
+    };
+    LA::load(ra, Ab, lda, m0, 0, tid);
+    LB::load(rb, Bb, ldb, n0, 0, tid);
+    LA::load(ra2, Ab, lda, m0, kat(1), tid);
+    LB::load(rb2, Bb, ldb, n0, kat(1), tid);
+    LA::store(ra, sbase, tid);
+    LB::store(rb, sbase + 64 * BK, tid);
+    LA::load(ra, Ab, lda, m0, kat(2), tid);
+    LB::load(rb, Bb, ldb, n0, kat(2), tid);
+    // Step j computes LDS stage j & 1 and stores step j + 1's data (set ra2 for
+    // even j) into the other; the set is refilled with step j + 3's.
+    int j = 0;
+    for (; j + 2 < nk; j += 2) {
+        lds_barrier();
+        kstep(0, true, true, kat(j + 3), ra2, rb2);
+        lds_barrier();
+        kstep(1, true, true, kat(j + 4), ra, rb);
+    }
+    if (j + 1 < nk) {
+        lds_barrier();
+        kstep(0, true, false, 0, ra2, rb2);
+        ++j;
+    }
+    lds_barrier();
+    kstep(j & 1, false, false, 0, ra, rb);
+}
+
+__global__ void __launch_bounds__(256, 2) small_jobs_kernel(SmallJobs p) {
+    __shared__ __attribute__((aligned(16))) half_t smem[2 * 2 * 64 * BK];
+    __shared__ float red[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    int bx = blockIdx.x, by = 0, bz = 0;
+    xcd_remap<false>(bx, by, bz);       // neighbouring tiles of a matrix on one XCD
+    // The job's fields are one run of scalar loads, all before the K loop: a
+    // load of one field later costs its full latency (0.7 us of a launch).
+    int g = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxItems - 1; ++i) g += bx >= p.tend[i];
+    const SmallJob& J = p.job[g];
+    const float j_ca = J.ca, j_cs = J.cs, diag = J.diag;
+    float* sumsq = J.sumsq;
+    asm volatile("" ::"s"(j_ca), "s"(j_cs), "s"(diag), "s"(sumsq));
+    const bool sym = J.sym;
+    const int tiles_n = J.N / 64;
+    const int tiles = sym ? tiles_n * (tiles_n + 1) / 2 : (J.M / 64) * tiles_n;
+    const int z = (bx - J.first) / tiles, tile = bx - J.first - z * tiles;
+    int tm, tn;
+    decode_tile(tile, tiles_n, sym, tm, tn);
+    const int m0 = 64 * tm, n0 = 64 * tn;
+    const half_t* A = J.a + (int64_t)z * J.a_stride;
+    const half_t* Bm = J.b + (int64_t)z * J.b_stride;
+    const int ldo = J.ld_out;
+    const half_t* src = J.src ? J.src + (int64_t)z * J.out_stride : nullptr;
+    half_t* out = J.out + (int64_t)z * J.out_stride;
+    // Register r of a lane: row 8 (r / 4) + 4 (lane / 32) + r % 4, column lane % 32.
+    const int row0 = m0 + 32 * wm + 4 * (lane >> 5), col = n0 + 32 * wn + (lane & 31);
+    half_t sv[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sv[r] = src ? src[(int64_t)(row0 + 8 * (r / 4) + r % 4) * ldo + col] : (half_t)0.f;
+    float mul = 1.f;
+    if (J.mul && J.mul_pow > 0) {
+        const float f = J.mul[2 * z];
+        mul = J.mul_pow == 1 ? f : f * f;
+    }
+    f32x16 acc = f32x16{};
+    if (J.layout == 0) small_tile<0>(A, J.lda, Bm, J.ldb, m0, n0, J.K, smem, acc);
+    else if (J.layout == 1) small_tile<1>(A, J.lda, Bm, J.ldb, m0, n0, J.K, smem, acc);
+    else small_tile<2>(A, J.lda, Bm, J.ldb, m0, n0, J.K, smem, acc);
+    const float ca = j_ca * mul, cs = j_cs * mul;
+    const bool mirror = sym && tm != tn;
+    float ss = 0.f;
+    typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f16x4 h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float x = ca * acc[4 * q + r];
+            if (src) x += cs * (float)sv[4 * q + r];
+            h[r] = (half_t)x;
+            if (diag != 0.f && row0 + 8 * q + r == col) h[r] = (half_t)((float)h[r] + diag);
+            const float f = (float)h[r];
+            ss += f * f;
+            out[(int64_t)(row0 + 8 * q + r) * ldo + col] = h[r];
+        }
+        // src is symmetric wherever the result is, so the mirror is the
+        // transpose: four consecutive entries of row `col`.
+        if (mirror) *(f16x4*)(out + (int64_t)col * ldo + row0 + 8 * q) = h;
+    }
+    if (sumsq) {
+        ss = wave_sum(ss);
+        if (lane == 0) red[wave] = ss;
+        lds_barrier();
+        if (tid == 0) sumsq[(int64_t)z * tiles + tile] = red[0] + red[1] + red[2] + red[3];
+    }
+}
+
 struct EAff : EpiAffine { static constexpr EpiKind kind = EpiKind::Affine; };
 struct EAffG : EpiAffine {
     static constexpr EpiKind kind = EpiKind::Affine;
@@ -991,6 +1130,32 @@ hipError_t launch_gemm_combine_grouped(TileCfg cfg, int s_dim, const CombineGrou
     GemmShape sh{s_dim, maxN, s_dim, 1, s_dim, 0};
     if (cfg == TileCfg::Big) return run<128, 128, 2, 2, 1>(dummy, dummy, sh, g.zbeg[g.n], ee, s);
     return run<256, 256, 2, 4, 1, EAffC, 32>(dummy, dummy, sh, g.zbeg[g.n], ee, s);
+}
+
+hipError_t launch_small_jobs(SmallJobs& j, hipStream_t s) {
+    if (j.n < 1 || j.n > kMaxItems || j.zbeg[0] != 0) return hipErrorInvalidValue;
+    int64_t blocks = 0;
+    for (int i = 0; i < kMaxItems; ++i) {
+        if (i >= j.n) {
+            j.tend[i] = INT_MAX;
+            continue;
+        }
+        SmallJob& p = j.job[i];
+        const int64_t tm = p.M / 64, tn = p.N / 64;
+        if (j.zbeg[i + 1] <= j.zbeg[i] || p.M < 64 || p.N < 64 || p.K < BK || p.M % 64 || p.N % 64 || p.K % BK ||
+            p.layout < 0 || p.layout > 2 || (p.sym && (tm != tn || p.sumsq)))
+            return hipErrorInvalidValue;
+        p.first = (int)blocks;
+        blocks += (p.sym ? tn * (tn + 1) / 2 : tm * tn) * (j.zbeg[i + 1] - j.zbeg[i]);
+        if (blocks > (1 << 30)) return hipErrorInvalidValue;
+        j.tend[i] = (int)blocks;
+    }
+    hipEvent_t ev0, ev1;
+    if (take_launch_events(ev0, ev1))
+        hipExtLaunchKernelGGL(small_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, s, ev0, ev1, 0, j);
+    else
+        hipLaunchKernelGGL(small_jobs_kernel, dim3((unsigned)blocks), dim3(256), 0, s, j);
+    return hipGetLastError();
 }
 
 hipError_t launch_gemm_gram_f32(int layout, Operand A, Operand B, GemmShape sh, int batch, const EpiPartial& e,

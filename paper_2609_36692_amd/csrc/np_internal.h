@@ -170,6 +170,33 @@ struct GramGroups {
 };
 hipError_t launch_gemm_gram_grouped(TileCfg cfg, int layout, const GramGroups& g, int sp, const EpiAffine& e,
                                     hipStream_t s);
+// Newton-Schulz products of small matrices: jobs of any shape and operand
+// layout in one launch, 64 x 64 tiles.  Job g has
+// zbeg[g + 1] - zbeg[g] matrices:
+//   out = mul^p (ca A B + cs src), fp16, then + diag on its diagonal, with out's
+// per-tile sums of squares
+// (tiles (M / 64)(N / 64) per matrix) where sumsq is set; sym: the product is
+// symmetric, tiles on and above the diagonal are computed and mirrored.
+// layout as in the launchers above; M, N multiples of 64, K of 64.
+struct SmallJob {
+    const half_t* a; const half_t* b;
+    const half_t* src;              // ld_out, out_stride; null: none
+    half_t* out;
+    int64_t a_stride, b_stride, out_stride;
+    const float* mul;               // mul[2 z]; null: 1
+    float* sumsq;
+    int lda, ldb, ld_out;
+    int M, N, K, layout, sym, mul_pow;
+    float ca, cs, diag;
+    int first;                      // its first block (launch_small_jobs)
+};
+struct SmallJobs {
+    int n;
+    int zbeg[kMaxItems + 1];
+    int tend[kMaxItems];            // past its last block (launch_small_jobs)
+    SmallJob job[kMaxItems];
+};
+hipError_t launch_small_jobs(SmallJobs& j, hipStream_t s);
 int gemm_tile_m(TileCfg cfg);
 // Kernel timing hand-off (instrumented steps only): while a start/stop event
 // pair is armed on this thread, the next GEMM launch records it at its own
@@ -228,6 +255,18 @@ hipError_t launch_source_x(const half_t* psi, int64_t ld, int64_t stride, int ro
 hipError_t launch_psi_col_normalize(const NormArgs& a, int batch, float* part, int64_t part_floats, int row_chunk,
                                     hipStream_t s);
 
+// Grouped forms of the two sums below: group g covers launch matrices
+// [zbeg[g], zbeg[g + 1]), whose n[g] values start at in[g] + i * stride[g]; the
+// results go to out[g] as launch_sum_partials (scaled: launch_psi_scale) writes
+// them.
+struct SumGroups {
+    int n;
+    int zbeg[kMaxItems + 1];
+    const float* in[kMaxItems]; int64_t stride[kMaxItems]; int len[kMaxItems];
+    float* out[kMaxItems];
+    int scaled; float eps;
+};
+hipError_t launch_sum_groups(const SumGroups& g, hipStream_t s);
 // out[z] = sum_i in[z*n + i] in a fixed order (per-matrix ||T||_F^2 from
 // per-tile partial sums); with `need`, only for the matrices with
 // need[z] != 0.

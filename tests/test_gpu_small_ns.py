@@ -1,0 +1,55 @@
+"""Newton-Schulz of small matrices by grouped launches: tile edges on both
+sides, one row, one column, wide and tall; more shape groups than one launch
+takes; and steps that mix the grouped items with tiled and Gram-space ones of
+the same pool (equal padded short side)."""
+import pytest
+import torch
+
+from oracle import normpre_oracle as O
+from paper_2609_36692_amd import normpre as N
+from paper_2609_36692_amd import workloads as WL
+from parity_util import check_update
+
+pytestmark = pytest.mark.gpu
+
+# fp16 Newton-Schulz operands through five iterations.
+TOL = 2e-2
+
+SETS = {
+    "one": [(1, 1)],
+    "edges": [(64, 63), (65, 64), (1, 300), (300, 1), (255, 256), (257, 256), (129, 511)],
+    # ten groups: two launches per stage
+    "ten": [(40 + 60 * i, 500 - 45 * i) for i in range(10)],
+    # (300, 330) grouped; the others take tiles, (256, 2048) in Gram space
+    "mixed": [(300, 330)] + [(256, 2048)] * 10 + [(200, 256)] + [(250, 256)] * 50 + [(1024, 1500)] * 3,
+}
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    c = N.normpre_init(0)
+    yield c
+    N.normpre_destroy(c)
+
+
+@pytest.mark.parametrize("variant", ["G", "MUON"])
+@pytest.mark.parametrize("t", [0, 1])
+@pytest.mark.parametrize("name", list(SETS))
+def test_small_ns(ctx, name, t, variant):
+    print(f"small Newton-Schulz {name} {variant} t={t}", flush=True)
+    shapes = SETS[name]
+    wl = WL.Workload("t", 90, shapes, "lowrank", 1.0, rank=8)
+    mats = [WL.make_matrix(wl, i, "cpu", shape=s) for i, s in enumerate(shapes)]
+    Ws, Gs, Ms = ([m[i].cuda().clone() for m in mats] for i in range(3))
+    hp = N.normpre_default_hparams(lr=1.0, weight_decay=0.0, step=t)
+    N.normpre_step(ctx, N.VARIANTS[variant], Ws, Gs, Ms, hp)
+    torch.cuda.synchronize()
+    ohp = O.HParams(lr=1.0, weight_decay=0.0)
+    for i in sorted({shapes.index(s) for s in shapes} | {len(shapes) - 1}):
+        w, g, m = (x.numpy() for x in mats[i])
+        ref = (O.muon_step(w, g, m, ohp) if variant == "MUON"
+               else O.normpre_step(w, g, m, t, ohp, variant, matrix_id=i))
+        check_update(f"{variant} small {shapes[i]} t={t}",
+                     mats[i][0].double().numpy() - Ws[i].cpu().double().numpy(), ref["update"], TOL)
