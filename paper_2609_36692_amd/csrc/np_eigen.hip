@@ -17,6 +17,7 @@
 // and by the spectral diagnostics of the normalized and unnormalized Grams
 // (App. A, spectral dynamics).  Matrices of one launch share n (grid y).
 #include "np_internal.h"
+#include "np_lanes.h"
 
 #include <algorithm>
 #include <cfloat>
@@ -96,11 +97,11 @@ __device__ __forceinline__ void lds_barrier() {
 constexpr int kDppBit3 = 0x128, kDppBit2 = 0x141, kDppBit1 = 0x4e, kDppBit0 = 0xb1;
 
 // N values per lane summed over the 32 lanes of each half wave (W = 32) or over
-// the wave (W = 64): every exchange halves the values a lane carries.  The
-// lanes end with the sum of value `slot` (none where slot >= N); of the lanes
-// that share one, `first` is set in the first.
-template <int W, int BIT, int N>
-__device__ __forceinline__ double sum_values(const double (&v)[N], int lane, int& slot, bool& first) {
+// the wave (W = 64): every exchange halves the values a lane carries.  Returns
+// the sum of value `slot` to the lanes where lane_sum says so; of the lanes that
+// share one, `first` is set in one, and never in a lane left with padding.
+template <int BIT, int N>
+__device__ __forceinline__ double halve_values(const double (&v)[N], int lane) {
     constexpr int H = (N + 1) / 2;
     const bool up = lane & BIT;
     if constexpr (BIT == 0) {
@@ -110,8 +111,7 @@ __device__ __forceinline__ double sum_values(const double (&v)[N], int lane, int
         if constexpr (BIT == 32) r[0] = swap32_add(v[0], v[0]);
         else if constexpr (BIT == 16) r[0] = swap16_add(v[0], v[0]);
         else r[0] = v[0] + dpp_take<BIT == 8 ? kDppBit3 : BIT == 4 ? kDppBit2 : BIT == 2 ? kDppBit1 : kDppBit0, 0xf>(v[0]);
-        first = first && !up;
-        return sum_values<W, BIT / 2, 1>(r, lane, slot, first);
+        return halve_values<BIT / 2, 1>(r, lane);
     } else {
         double r[H];
 #pragma unroll
@@ -121,15 +121,16 @@ __device__ __forceinline__ double sum_values(const double (&v)[N], int lane, int
             else if constexpr (BIT == 16) r[i] = swap16_add(a, b);
             else r[i] = swap_dpp_add<BIT == 8 ? kDppBit3 : BIT == 4 ? kDppBit2 : BIT == 2 ? kDppBit1 : kDppBit0>(a, b, up);
         }
-        slot += up ? H : 0;
-        return sum_values<W, BIT / 2, H>(r, lane, slot, first);
+        return halve_values<BIT / 2, H>(r, lane);
     }
 }
 template <int W, int N>
 __device__ __forceinline__ double sum_values(const double (&v)[N], int lane, int& slot, bool& first) {
-    slot = 0;
-    first = true;
-    return sum_values<W, W / 2, N>(v, lane, slot, first);
+    static_assert(N <= W && lane_sum_complete(W, N), "every value stored by one lane");
+    const LaneSum o = lane_sum(W, N, lane & (W - 1));
+    slot = o.slot;
+    first = o.first;
+    return halve_values<W / 2, N>(v, lane);
 }
 
 // Sum over the block in a fixed order (every thread returns the same value).
@@ -438,7 +439,7 @@ __device__ __forceinline__ void tri_reg_cols(float (&M)[R][C], TriRegShared<C>& 
             bool first;
             const double d = sum_values<32>(dot, lane, slot, first);
             const int i = RS * (S + slot) + 2 * wave + half;
-            if (first && slot < R - S && i < 32 * C) sh.p[par][i] = i > jj ? t * d : 0.0;
+            if (first && i < 32 * C) sh.p[par][i] = i > jj ? t * d : 0.0;
         }
         // The fp64 copies of M are made anew below: kept across the barrier
         // (the compiler's choice) they would not fit the registers.
