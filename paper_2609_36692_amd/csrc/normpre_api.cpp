@@ -2598,7 +2598,11 @@ int normpre_spectrum(normpre_ctx* ctx, int which, int64_t rows, int64_t cols, co
     NP_TRY(launch_tri_eigvals(tw, (int)eo, 0, (int)eo, lam, eo, 1, s), "bisection");
     NP_TRY(hipMemcpyAsync(eigs, lam, (size_t)eo * sizeof(double), hipMemcpyDeviceToHost, s), "copy eigenvalues");
     NP_TRY(hipStreamSynchronize(s), "hipStreamSynchronize");
-    std::fill(eigs + eo, eigs + d.a, 0.0);
+    // The zeros go before computed eigenvalues of rounding size that came out
+    // negative, so that the list stays descending.
+    double* neg = std::find_if(eigs, eigs + eo, [](double v) { return v < 0.0; });
+    std::move_backward(neg, eigs + eo, eigs + d.a);
+    std::fill(neg, neg + (d.a - eo), 0.0);
     ctx->last_stream = s;
     ctx->have_stream = true;
     return NORMPRE_OK;

@@ -44,6 +44,9 @@ def _momentum(kind, shape):
         return m
     if kind == "zero":
         return torch.zeros(shape)
+    if kind == "rank4":             # computed eigenvalues of rounding size, of either sign
+        gen = torch.Generator().manual_seed(5)
+        return torch.randn(shape[0], 4, generator=gen) @ torch.randn(4, shape[1], generator=gen)
     w, g, mp = _inputs(shape, kind, seed=13)
     return (0.95 * mp + g) * torch.linspace(0.3, 3.0, shape[0])[:, None]
 
@@ -53,7 +56,8 @@ def _momentum(kind, shape):
     ((256, 400), 0, "lowrank"), ((257, 400), 0, "lowrank"), ((511, 600), 0, "lowrank"), ((577, 600), 0, "lowrank"),
     ((770, 900), 1, "lowrank"), ((1090, 1200), 0, "student_t"), ((2113, 2200), 0, "student_t"),
     ((900, 257), 0, "lowrank"), ((300, 1100), 1, "lowrank"), ((700, 1), 0, "lowrank"),
-    ((300, 600), 0, "identity"), ((300, 600), 0, "repeated"), ((290, 310), 0, "zero")])
+    ((300, 600), 0, "identity"), ((300, 600), 0, "repeated"), ((290, 310), 0, "zero"),
+    ((700, 300), 0, "rank4"), ((260, 800), 1, "rank4"), ((600, 290), 0, "repeated"), ((310, 290), 0, "zero")])
 def test_spectrum_of_the_rounded_psi(ctx, shape, t, kind):
     print(f"spectrum shape={shape} t={t} {kind}", flush=True)
     m = _momentum(kind, shape)
