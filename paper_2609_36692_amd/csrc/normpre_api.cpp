@@ -1900,7 +1900,6 @@ bool closed_norm(const Item& it) { return !it.d.xl && !it.w.xs; }
 int closed_norm_launches(const StepCtx& sc, const std::vector<Item>& items, const std::vector<Pool>& pools) {
     LNormGroups g{};
     const bool both = sc.hp->orientation == NORMPRE_ORIENT_BOTH;
-    g.unit_rows = !both;
     int total = 0;
     auto flush = [&]() -> int {
         if (g.n == 0) return NORMPRE_OK;

@@ -823,19 +823,16 @@ __global__ void __launch_bounds__(256) sum_groups_kernel(SumGroups g) {
 
 // One block per matrix: the closed-form ||T||_F^2 of NormPre-L and whether the
 // norm pass has to supply it (see LNormGroups).  Sums in fp64.
-// What the closed form leaves out is that the apply uses Q rounded to fp16:
-// with E = Q16^T Q16 - I it is off by <E, Z diag((1 - sqrt lambda)^2) Z^T>.  An
-// entry of a selected eigenvector u = Psi v / sqrt lambda is at most |psi_i| /
-// sqrt lambda = 1 / sqrt lambda, so a mode's term has rms at most (1 - sqrt
-// lambda)^2 2 d / sqrt lambda for a relative rounding error of rms d = 1.4e-4
-// (for eigenvectors spread over their entries, far less).  Accepted while the
-// root of the summed squares is within 2.5e-4 of the result, i.e. 1.25e-4 in the
-// update's scale, a quarter of what fp16 operands do to the update; also, as
-// for rows that are not unit vectors, while the selected modes hold at most a
-// quarter of ||Psi||^2.  (With that second rule alone the low-rank and power-law
-// stacks took the norm pass: 0.09 of 1.20 ms on GPT-2 Small, 0.66 of 7.9 ms on the
-// LLaMA-1B-shaped stack.)
-constexpr double kClosedShare = 0.25, kRoundRms2 = 2.8e-4, kClosedRel = 2.5e-4;
+// The closed form holds for an orthonormal Q and the unrounded Psi; the update
+// uses both in fp16.  With E = Q16^T Q16 - I it is off by <E, Z diag((sqrt lambda -
+// 1)^2) Z^T>, up to 2^-10 sum_C (sqrt lambda - 1)^2 where the rounding errors of a
+// mode's entries have one sign (equal entries: rows that share one direction),
+// and by up to 2^-10 sum_C lambda from Psi's rounding.  While the selected modes
+// hold at most a quarter of ||Psi||^2, each is below 3.3e-4 of the result (1.6e-4
+// of the update's scale).  A bound on the rms of independent rounding errors
+// would admit most other matrices, but equal entries then left the scale off by
+// up to 8.5e-3 (1500 rows, share 0.97; by the norm pass 1e-7).
+constexpr double kClosedShare = 0.25;
 
 __global__ void __launch_bounds__(256) l_norm_closed_kernel(LNormGroups g) {
     const int zl = blockIdx.x, tid = threadIdx.x;
@@ -845,17 +842,16 @@ __global__ void __launch_bounds__(256) l_norm_closed_kernel(LNormGroups g) {
     const int n = g.nsel[gi][z];
     const float* r = g.ritz[gi] + (int64_t)z * g.ritz_stride[gi];
     const float* p = g.psisq[gi] + (int64_t)z * g.stride[gi];
-    double v[4] = {0.0, 0.0, 0.0, 0.0};         // ||Psi||^2, sum lambda, sum lambda - 1, error terms
+    double v[3] = {0.0, 0.0, 0.0};              // ||Psi||^2, sum lambda, sum lambda - 1
     for (int i = tid; i < g.count[gi]; i += 256) v[0] += p[i];
     for (int i = tid; i < n; i += 256) {
-        const double l = r[i], k = sqrt(l) - 1.0;
+        const double l = r[i];
         v[1] += l;
         v[2] += l - 1.0;
-        v[3] += k * k * k * k / l;
     }
-    __shared__ double red[4][4];
+    __shared__ double red[4][3];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 3; ++q) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
         if ((tid & 63) == 0) red[tid >> 6][q] = v[q];
@@ -863,10 +859,9 @@ __global__ void __launch_bounds__(256) l_norm_closed_kernel(LNormGroups g) {
     __syncthreads();
     if (tid != 0) return;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = red[0][q] + red[1][q] + red[2][q] + red[3][q];
+    for (int q = 0; q < 3; ++q) v[q] = red[0][q] + red[1][q] + red[2][q] + red[3][q];
     const double t2 = v[0] - v[2];
-    const bool closed = t2 > 0.0 && (v[1] <= kClosedShare * v[0] ||
-                                     (g.unit_rows && kRoundRms2 * sqrt(v[3]) <= kClosedRel * t2));
+    const bool closed = t2 > 0.0 && v[1] <= kClosedShare * v[0];
     g.need[gi][z] = closed ? 0 : 1;
     if (closed) g.tn2[gi][z] = (float)t2;
 }

@@ -277,8 +277,8 @@ hipError_t launch_sum_partials(const float* in, int n, float* out, int batch, hi
 // the selected Ritz values the first nsel[i] of the descending list ritz[i]
 // (stride ritz_stride), ||T||_F^2 = ||Psi||_F^2 - sum_C (lambda_i - 1),
 // ||Psi||_F^2 being the sum of the `count` values of psisq[i * stride].  It is
-// written to tn2[i] where the fp16 rounding of Q moves it by little (see the
-// kernel); need[i] = 1 marks the other matrices, whose norm the norm pass
+// written to tn2[i] where the fp16 rounding of Q and Psi moves it by little (see
+// the kernel); need[i] = 1 marks the other matrices, whose norm the norm pass
 // over T supplies instead.
 struct LNormGroups {
     int n;
@@ -288,7 +288,6 @@ struct LNormGroups {
     const int* nsel[kMaxItems];
     float* tn2[kMaxItems];
     int* need[kMaxItems];
-    int unit_rows;              // the active rows of Psi have unit norm (or are zero)
 };
 hipError_t launch_l_norm_closed(const LNormGroups& g, hipStream_t s);
 
