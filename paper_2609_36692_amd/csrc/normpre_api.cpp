@@ -35,6 +35,13 @@ constexpr int kEigAliasMax = 104;
 constexpr int64_t kMaxExactRows = 8192;
 constexpr int kColRowChunk = 128;   // rows per block in the column-active pass
 constexpr int kMaxSplits = 16;
+// NormPre-L: up to this many tiles of the norm pass per matrix (two partial sums
+// per thread) every block of the update adds them up; above, one launch does,
+// since the blocks together read their square.  Steps in us, added up in the
+// update / by a launch: twelve 768^2 (72 tiles) 319.9 / 320.9, eight 1024^2 (128)
+// 336.6 / 337.4, one 2048^2 (512) 313.8 / 314.1, eight 2048 x 5632 (1408) 1043 /
+// 1022, one 8192^2 (8192) 910 / 834, one 16384 x 32768 (65536) 9670 / 4600.
+constexpr int kUpdateSums = 512;
 constexpr size_t kGroupBudget = size_t(24) << 30;  // workspace bytes per item
 constexpr size_t kRoundBudget = size_t(48) << 30;  // workspace bytes per round
 // Static scratch of normpre_step_noalloc(): the whole workspace of that entry
@@ -1946,10 +1953,10 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
     // accurate (closed_norm_launches decided it on the device), which saves
     // streaming Psi once more; the other matrices take the norm pass: the
     // same product as the update, reduced to per-tile sums of T^2, which the
-    // update's blocks add up.  (The closed form needs the Ritz values of Psi
-    // itself: not with the interaction source X, nor for the dense
-    // eigensolver's exact variant.)
-    const bool closed = closed_norm(it);
+    // update's blocks (kUpdateSums) or a launch add up.  (The closed form needs
+    // the Ritz values of Psi itself: not with the interaction source X, nor for
+    // the dense eigensolver's exact variant.)
+    const bool closed = closed_norm(it), sums_in_update = closed && apply_tiles(d) <= kUpdateSums;
     {
         Operand A{L, lp, l_stride};
         Operand B{R, lp, r_stride};
@@ -1962,7 +1969,7 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
         NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_L_APPLY, 2.0 * d.ell * (double)d.m * d.n * count, 2.0 * d.m * d.n * count,
                      [&] { return launch_gemm_apply_norm(A, B, sh, count, e, sc.s); }),
                "apply norm");
-        if (!closed || dbg)
+        if (!sums_in_update || dbg)
             NP_TRY(timed(sc.ctx, NORMPRE_KCLASS_SK_SMALL, 0.0, 0.0,
                          [&] {
                              return launch_sum_partials(w.sumsq, apply_tiles(d), w.tn2, count, sc.s,
@@ -1978,7 +1985,7 @@ int sketch_back(const StepCtx& sc, const Item& it, const Pool& pl, DebugMat* dbg
         EpiApplyUpdate e{};
         e.psi = w.psi + (int64_t)c0 * mn; e.ld_psi = d.np_; e.stride_psi = mn;
         e.tnorm2 = w.tn2 + c0;
-        if (closed) e.need = w.lneed + c0;
+        if (sums_in_update) e.need = w.lneed + c0;
         e.sumsq = w.sumsq + (int64_t)c0 * apply_tiles(d); e.tiles_per_mat = apply_tiles(d);
         e.rows = (int)d.m; e.cols = (int)d.n;
         e.lr = hp.lr; e.wd = hp.weight_decay; e.target_rms = hp.target_rms;

@@ -129,3 +129,39 @@ def test_update_rms_of_equal_rows(ctx, a, groups, share, t):
     rms = float(W.double().square().mean().sqrt())
     print(f"  rms {rms:.6f}", flush=True)
     assert abs(rms / 0.2 - 1.0) < 3.3e-4
+
+
+# Both sides of the number of tiles up to which the update adds the norm pass's
+# partial sums itself (512: 2048 x 2048).
+@pytest.mark.parametrize("shape", [(2048, 2048), (2048, 2050)])
+def test_update_rms_around_the_sum_launch(ctx, shape):
+    g = torch.Generator().manual_seed(17)
+    grad = torch.randn(shape[0], 4, generator=g) @ torch.randn(4, shape[1], generator=g)
+    W = [torch.zeros(shape, device="cuda") for _ in range(3)]
+    hp = N.normpre_default_hparams(lr=1.0, weight_decay=0.0, step=0, rank=32)
+    N.normpre_step(ctx, N.NORMPRE_VARIANT_L, W, [grad.cuda().clone() for _ in W],
+                   [torch.zeros_like(w) for w in W], hp)
+    for w in W:
+        rms = float(w.double().square().mean().sqrt())
+        print(f"L update RMS {shape} {rms:.7f}", flush=True)
+        assert abs(rms / 0.2 - 1.0) < 1e-5      # fp32 sums of the T that is applied
+
+
+# The norm pass reads Psi once (2 B per element beside the update's 10), however
+# many tiles the matrix has: 16384^2 has 32768, and blocks that each added all
+# their partial sums took 3.7 times the time of a step without the pass.
+def test_norm_pass_time_is_linear(ctx):
+    n, ms = 16384, {}
+    g = torch.Generator(device="cuda").manual_seed(23)
+    noise = torch.randn(n, n, generator=g, device="cuda")
+    low = torch.randn(n, 4, generator=g, device="cuda") @ torch.randn(4, n, generator=g, device="cuda")
+    W, M = torch.zeros(n, n, device="cuda"), torch.zeros(n, n, device="cuda")
+    for name, grad in (("closed", noise), ("pass", low)):
+        hp = N.normpre_default_hparams(lr=1e-3, step=0, flags=N.NORMPRE_FLAG_TIME_KERNELS)
+        M.zero_()
+        for _ in range(2):
+            N.normpre_kernel_stats(ctx, N.NORMPRE_KCLASS_L_APPLY, reset=True)
+            N.normpre_step(ctx, N.NORMPRE_VARIANT_L, [W], [grad], [M], hp)
+        ms[name] = N.normpre_kernel_stats(ctx, N.NORMPRE_KCLASS_L_APPLY)["ms"]
+    print(f"L apply {ms}", flush=True)
+    assert ms["pass"] < 2.0 * ms["closed"]
