@@ -695,6 +695,13 @@ size_t carve_round(Arena& ar, std::vector<Item>& items, std::vector<Pool>& pools
 // 161 / 154, four of 768^2 (576 tiles) 199 / 220; Gram-space: one 512 x 2048 214 /
 // 161, four of 256 x 8192 301 / 239, two of 1024 x 2048 303 / 298, eight of
 // 512 x 2048 (2048 tiles) 263 / 259; five shapes of three matrices 596 / 254.
+// An item stays with its pool (equal padded s) unless all of the pool is grouped:
+// the pool's launches take it along for little or nothing, a chain of its own
+// runs before them.  Beside the rest of the pool, grouped / with the pool: 512^2
+// and eight of 512 x 700 296 / 198, 512 x 2048 and 24 of 512 x 4096 816 / 684, 1024^2
+// and twelve of 1024 x 2048 910 / 878, 256^2 and sixteen of 256 x 8192 604 / 580;
+// the other way at most 672 / 702 (768^2 and twelve of 3072 x 768), which per-pool
+// launches took 707 for.
 constexpr double kSmallFlops = 22e9;
 void mark_small(std::vector<Item>& items, int variant, const normpre_hparams& hp, bool allow = true) {
     for (Item& it : items) {
@@ -718,6 +725,10 @@ void mark_small(std::vector<Item>& items, int variant, const normpre_hparams& hp
         if (sum > kSmallFlops || tiles > most) break;
         it->small = true;
     }
+    for (Item& it : items)
+        it.small = it.small && std::none_of(by.begin(), by.end(), [&](const Item* o) {
+            return !o->small && o->d.sp == it.d.sp;
+        });
 }
 
 size_t round_bytes(std::vector<Item> items, int variant, int opts, const normpre_hparams& hp, bool allow_small = true) {

@@ -53,3 +53,22 @@ def test_small_ns(ctx, name, t, variant):
                else O.normpre_step(w, g, m, t, ohp, variant, matrix_id=i))
         check_update(f"{variant} small {shapes[i]} t={t}",
                      mats[i][0].double().numpy() - Ws[i].cpu().double().numpy(), ref["update"], TOL)
+
+
+# A small item beside tiled ones of its pool shares their launches; only the
+# combines of Gram-space (two) and of tall items (one per iteration) are launched
+# per item.  A chain of its own would be 15 launches.
+@pytest.mark.parametrize("small,tiled,own", [((512, 512), [(512, 700)] * 8, 0), ((512, 2048), [(512, 4096)] * 24, 2),
+                                             ((700, 500), [(700, 512)] * 8, 5)])
+def test_small_item_stays_with_its_pool(ctx, small, tiled, own):
+    classes = (N.NORMPRE_KCLASS_NS_GRAM, N.NORMPRE_KCLASS_NS_POLY, N.NORMPRE_KCLASS_NS_COMBINE)
+    hp = N.normpre_default_hparams(step=0, flags=N.NORMPRE_FLAG_TIME_KERNELS)
+    count = []
+    for shapes in (tiled, [small] + tiled):
+        Ws, Gs, Ms = ([torch.randn(s, device="cuda") for s in shapes] for _ in range(3))
+        for c in classes:
+            N.normpre_kernel_stats(ctx, c, reset=True)
+        N.normpre_step(ctx, N.NORMPRE_VARIANT_G, Ws, Gs, Ms, hp)
+        count.append(sum(N.normpre_kernel_stats(ctx, c)["launches"] for c in classes))
+    print(f"Newton-Schulz launches {small} beside {tiled[0]}: {count}", flush=True)
+    assert count[1] - count[0] <= own
