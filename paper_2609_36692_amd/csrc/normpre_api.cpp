@@ -26,8 +26,8 @@ constexpr int64_t kMaxDim = int64_t(1) << 20;
 constexpr int64_t kMaxElems = int64_t(1) << 31;
 constexpr int kMaxRowLen = 32768;   // row-active register kernel limit
 constexpr int kMaxEll = 384;
-// Up to this width the dense eigensolver's workspace for Gamma_Q fits buffers
-// of the pool that are idle by then.
+// Up to this width the dense eigensolver's workspace for Gamma_Q fits two idle
+// buffers of the pool (`eigs`, the Cholesky scratch).
 constexpr int kEigAliasMax = 104;
 // Exact NormPre-L above kMaxEll active rows: dense fp64 eigensolver on the
 // a x a interaction matrix (tridiagonal reduction, bisection, inverse
@@ -327,8 +327,6 @@ struct GWork {
     double* colpart;
     // G
     half_t* xb;
-    half_t* amat;
-    half_t* bmat;
     float* sumsq;           // per-tile partial sums of T^2 (both variants)
     int* nfin;              // finite check: non-finite count slots
     float* tn2;             // per-matrix ||T||_F^2
@@ -337,15 +335,8 @@ struct GWork {
     half_t* v16[2];
     float* v32[2];
     float* part;
-    double* gpart;
-    double* chol;
-    float* rinv;
-    float* kmat;
     half_t* qlen;
     half_t* flen;
-    float* eigs;
-    float* ritz;
-    int* nsel;
     int* lneed;             // NormPre-L: 1 where ||T||_F needs the norm pass
 };
 
@@ -479,6 +470,7 @@ struct Pool {
     int qcur = 0;
     double* gpart = nullptr;
     int gslots = kGramChunks;   // slots of its Gram partial sums
+    int64_t gslots_all = 0;     // most slots it or a part of it takes in all
     double* chol = nullptr;
     float* rinv = nullptr;
     float* kmat = nullptr;
@@ -572,16 +564,17 @@ void carve_pool(Arena& ar, Pool& p, int variant) {
         }
     } else if (variant == NORMPRE_VARIANT_L) {
         const int64_t lp = p.ellp;
-        p.gpart = ar.take<double>(c * kGramChunks * lp * lp);
+        p.gpart = ar.take<double>(p.gslots_all * lp * lp);
         p.chol = ar.take<double>(c * 2 * lp * lp);
         p.rinv = ar.take<float>(c * lp * lp);
         p.kmat = ar.take<float>(c * lp * lp);
-        p.eigs = ar.take<float>(c * 2 * lp * lp);
+        const bool alias = p.ell > ritz_small_max() && p.ell <= kEigAliasMax;
+        if (alias) p.eigs = ar.take<float>(c * 2 * lp * lp);
         p.ritz = ar.take<float>(c * (int64_t)p.top);
         p.nsel = ar.take<int>(c);
         if (p.ell > ritz_small_max()) {
             const int64_t n = p.ell, top = p.top;
-            if (p.ell <= kEigAliasMax) {
+            if (alias) {
                 // The matrix and the small vectors in `eigs` (2 l_pad^2 floats
                 // per matrix), the eigenvectors after the WY factors in the
                 // Cholesky scratch: l_pad = 128 holds n = 104 of both.
@@ -673,6 +666,7 @@ std::vector<Pool> make_pools(std::vector<Item>& items, int variant) {
             for (const Item& it : items)
                 if (it.pool == (int)q) len = std::max(len, it.d.lp_);
             pools[q].gslots = gram64_slots(pools[q].ell, pools[q].count, len);
+            pools[q].gslots_all = gram64_slots_all(pools[q].ell, pools[q].count, len);
         }
     return pools;
 }

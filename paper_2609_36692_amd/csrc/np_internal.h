@@ -376,6 +376,9 @@ struct Gram64Items {
 };
 hipError_t launch_gram64(const Gram64Items& t, int ell_pad, double* partial, hipStream_t s);
 int gram64_slots(int ell, int count, int64_t max_len);
+// The most slots that `count` matrices or fewer take together, so that a
+// workspace sized for a list also holds every part of it.
+int64_t gram64_slots_all(int ell, int count, int64_t max_len);
 // Element (c, d) of the summed Gram (full symmetric view of the upper tiles
 // gram64 writes), added in slot order with four slots' loads in flight.
 __device__ __forceinline__ double gram_at(const double* p, int ell_pad, int c, int d, int chunks) {

@@ -691,6 +691,12 @@ int gram64_slots(int ell, int count, int64_t max_len) {
     return (int64_t)count * gram_groups(ell) * 4 * kGramWaves < 1024 && max_len > 4096 ? kGramChunks : 4;
 }
 
+int64_t gram64_slots_all(int ell, int count, int64_t max_len) {
+    const int64_t few = std::min<int64_t>(count, 1023 / (gram_groups(ell) * 4 * kGramWaves));
+    return std::max((int64_t)count * gram64_slots(ell, count, max_len),
+                    few > 0 ? few * gram64_slots(ell, (int)few, max_len) : 0);
+}
+
 hipError_t launch_gram64(const Gram64Items& t, int ell_pad, double* partial, hipStream_t s) {
     if (ell_pad % 64 || t.ell < 1 || t.ell > ell_pad || t.n < 1 || t.n > kMaxItems || t.zbeg[0] != 0 ||
         t.chunks < 1 || t.chunks > kGramChunks)

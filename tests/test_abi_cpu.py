@@ -187,6 +187,24 @@ def test_energy_split_host_matches_oracle(N):
         N.normpre_energy_split(lam, -1, 3)
 
 
+def test_sketch_workspace_holds_what_is_used_and_every_part_of_a_list(N):
+    def need(shapes, rank):
+        return N.normpre_workspace_size(N.NORMPRE_VARIANT_L, shapes, N.normpre_default_hparams(rank=rank))
+    # Per matrix of 768 x 1024, l = 72 (both sides and l padded, 1024 and 128): Psi;
+    # Omega, V (two fp16, two fp32 copies), Q and F; the split sums (at most 16);
+    # l_pad^2 entries of 4 fp64 Gram slots, 2 fp64 of the Cholesky and 2 fp32
+    # small matrices; statistics.  With 16 Gram slots it was 15.0 MB.
+    lp, side = 128, 1024
+    psi = 2 * 768 * side
+    most = psi + lp * side * (2 + 2 * 2 + 2 * 4 + 2 + 2 + 16 * 4) + lp * lp * (4 * 8 + 2 * 8 + 2 * 4) + (1 << 18)
+    assert need([(768, 1024)] * 96, 64) <= 96 * most
+    # The number of slots falls as matrices are added (4 from 16 on here), the
+    # workspace does not.
+    for rank in (8, 32, 64, 80, 120):
+        sizes = [need([(768, 6000)] * k, rank) for k in range(1, 40)]
+        assert sizes == sorted(sizes)
+
+
 def test_workspace_size_is_host_only_and_covers_both_orientations(N):
     hp = N.normpre_default_hparams()
     shapes = [(768, 2304), (3072, 768), (768, 768)]
