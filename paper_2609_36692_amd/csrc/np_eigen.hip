@@ -652,7 +652,7 @@ __global__ void __launch_bounds__(64 * kBisectWaves) tri_bisect_kernel(const dou
     }
     const double span = fmax(fabs(lo), fabs(hi));
     const int t = blockIdx.x * kBisectWaves + wave;
-    if (!(span > 0.0)) {                // T = 0 (or not a number: the bound says so)
+    if (!(span > 0.0)) {                // T = 0 (fmin and fmax drop NaN: an all-NaN T ends at 0 below)
         if (t < nvals && lane == 0) out[(int64_t)z * stride_out + t] = span;
         return;
     }

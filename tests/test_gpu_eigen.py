@@ -1,7 +1,7 @@
 """The dense eigensolver (spectra, exact NormPre-L) at the sizes where its
 kernels change: orders around the one-workgroup block of the reduction (256),
 around each change of threads and columns per thread of the per-column
-launches, active sides longer and shorter than the other, and spectra with
+launches up to the largest order, active sides longer and shorter than the other, and spectra with
 clusters, zeros and no coupling at all."""
 import math
 
@@ -75,6 +75,28 @@ def test_spectrum_of_the_rounded_psi(ctx, shape, t, kind):
     tol = (2.0 * n + 256.0) * U24 * max(ref[0], 1e-300)
     err = float(np.max(np.abs(eig - ref)))
     print(f"  max error {err:.2e} (tol {tol:.1e}) lambda_max {ref[0]:.3f}", flush=True)
+    assert err <= tol
+
+
+# The largest orders (above 4096 the per-column launches have 1024 threads, and the
+# multisection's matrix takes more than 64 KB of LDS): rows 0.8 e_i + 0.6 e_{i+1} in
+# random order, whose Gamma is a permuted tridiagonal Toeplitz matrix of known
+# eigenvalues d + 2 o cos(k pi / (n + 1)), d and o from the rounded entries.
+@pytest.mark.parametrize("n", [4097, 5000, 8192])
+def test_spectrum_of_large_orders(ctx, n):
+    print(f"spectrum order {n}", flush=True)
+    i = torch.arange(n, device="cuda")
+    r = torch.randperm(n, generator=torch.Generator().manual_seed(3)).cuda()
+    m = torch.zeros(n, (n + 4) // 4 * 4, device="cuda")
+    m[r, i] = 0.8
+    m[r, i + 1] = 0.6
+    eig = N.normpre_spectrum(ctx, N.NORMPRE_SPECTRUM_GAMMA, torch.zeros_like(m), m, N.normpre_default_hparams(step=0))
+    a, b = (float(np.float16(v)) for v in (0.8, 0.6))
+    ref = a * a + b * b + 2.0 * a * b * np.cos(np.arange(1, n + 1) * math.pi / (n + 1))
+    assert eig.shape == ref.shape and np.all(np.diff(eig) <= 1e-12)
+    tol = (2.0 * n + 256.0) * U24 * ref[0]
+    err = float(np.max(np.abs(eig - ref)))
+    print(f"  max error {err:.2e} (tol {tol:.1e})", flush=True)
     assert err <= tol
 
 
