@@ -1290,7 +1290,8 @@ struct SmallProduct {
     half_t* out;
     int M, N, K, lda, ldb, layout;      // out's rows are N long
     int64_t a_stride, b_stride, out_stride;
-    bool sym, scaled, sums;
+    int sym;
+    bool scaled, sums;
     float ca, cs, diag;
 };
 
@@ -1305,16 +1306,18 @@ std::vector<std::vector<SmallProduct>> small_stages(const StepCtx& sc, const Ite
     std::vector<std::vector<SmallProduct>> st;
     auto gram = [&](const half_t* x, bool first) {
         st.push_back({{&it, NORMPRE_KCLASS_NS_GRAM, x, x, nullptr, am, sp, sp, (int)d.lp_, np, np, d.tall ? 2 : 0, mn,
-                       mn, ss, true, first, false, 1.f, 0.f, 0.f}});
+                       mn, ss, 1, first, false, 1.f, 0.f, 0.f}});
     };
-    // out = ca L R + cs src on the s x s matrices (diag: + diag I).
-    auto square = [&](const half_t* l, const half_t* r, const half_t* src, half_t* out, float ca, float cs, float diag) {
+    // out = ca L R + cs src on the s x s matrices (diag: + diag I); sym 1 for the
+    // square of a fresh Gram, 2 where a factor is itself such a product.
+    auto square = [&](int sym, const half_t* l, const half_t* r, const half_t* src, half_t* out, float ca, float cs,
+                      float diag) {
         return SmallProduct{&it, NORMPRE_KCLASS_NS_POLY, l, r, src, out, sp, sp, sp, sp, sp, 0, ss, ss, ss,
-                            true, false, false, ca, cs, diag};
+                            sym, false, false, ca, cs, diag};
     };
     auto combine = [&](const half_t* s, const half_t* x, half_t* xn, float cs, bool first, bool last) {
         SmallProduct p{&it, NORMPRE_KCLASS_NS_COMBINE, s, x, cs != 0.f ? x : nullptr, xn, mp, np, sp, sp, np, 1, ss,
-                       mn, mn, false, first, last, 1.f, cs, 0.f};
+                       mn, mn, 0, first, last, 1.f, cs, 0.f};
         if (d.tall) {
             std::swap(p.a, p.b); std::swap(p.lda, p.ldb); std::swap(p.a_stride, p.b_stride);
             p.layout = 0;
@@ -1326,7 +1329,7 @@ std::vector<std::vector<SmallProduct>> small_stages(const StepCtx& sc, const Ite
             half_t* x = (i & 1) ? it.w.xb : it.w.psi;
             half_t* xn = (i & 1) ? it.w.psi : it.w.xb;
             gram(x, i == 0 && fold_scale);
-            st.push_back({square(am, am, am, bm, c, b, 0.f)});
+            st.push_back({square(1, am, am, am, bm, c, b, 0.f)});
             combine(bm, x, xn, a, i == 0 && fold_scale, i == q - 1);
         }
         return st;
@@ -1341,11 +1344,11 @@ std::vector<std::vector<SmallProduct>> small_stages(const StepCtx& sc, const Ite
         const bool first = i < kGnsRestart && fold_scale;
         if (seg_start) {
             gram(x, first);
-            st.push_back({square(am, am, am, qm[0], c, b, a)});
+            st.push_back({square(1, am, am, am, qm[0], c, b, a)});
             cur = 0;
         } else {
-            st.push_back({square(am, am, am, bm, c, b, 0.f)});
-            st.push_back({square(bm, qm[cur], qm[cur], qm[1 - cur], 1.f, a, 0.f)});
+            st.push_back({square(2, am, am, am, bm, c, b, 0.f)});
+            st.push_back({square(2, bm, qm[cur], qm[cur], qm[1 - cur], 1.f, a, 0.f)});
             cur = 1 - cur;
         }
         if (seg_end) {
@@ -1354,10 +1357,10 @@ std::vector<std::vector<SmallProduct>> small_stages(const StepCtx& sc, const Ite
         }
         const half_t* left = seg_start ? qm[0] : bm;
         const float cs = seg_start ? 0.f : a;
-        const SmallProduct r = square(left, am, seg_start ? nullptr : am, rm, 1.f, cs, 0.f);
+        const SmallProduct r = square(2, left, am, seg_start ? nullptr : am, rm, 1.f, cs, 0.f);
         if (seg_start) st.push_back({r});
         else st.back().push_back(r);
-        st.push_back({square(left, rm, seg_start ? nullptr : rm, am, 1.f, cs, 0.f)});
+        st.push_back({square(2, left, rm, seg_start ? nullptr : rm, am, 1.f, cs, 0.f)});
     }
     return st;
 }
@@ -1384,8 +1387,7 @@ int small_launch(const StepCtx& sc, const std::vector<SmallProduct>& ps) {
         const double f = 2.0 * s_ * s_ * (poly ? s_ : l_) * it.count;
         flops += f;
         bytes += (poly ? (p.src == p.a ? 4.0 : 6.0) * s_ * s_ : 2.0 * ((comb ? 2.0 : 1.0) * s_ * l_ + s_ * s_)) * it.count;
-        const double tn = p.N / 64, tiles = p.sym ? tn * (tn + 1) / 2 : (p.M / 64) * tn;
-        issued += tiles * 8192.0 * p.K * it.count;
+        issued += (double)small_tile_count(p.M, p.N, p.sym) * 8192.0 * p.K * it.count;
         if (f > most) {
             most = f;
             kclass = p.kclass;

@@ -878,12 +878,18 @@ __global__ void __launch_bounds__(256, 2) small_jobs_kernel(SmallJobs p) {
     const float j_ca = J.ca, j_cs = J.cs, diag = J.diag;
     float* sumsq = J.sumsq;
     asm volatile("" ::"s"(j_ca), "s"(j_cs), "s"(diag), "s"(sumsq));
-    const bool sym = J.sym;
+    const int sym = J.sym;
     const int tiles_n = J.N / 64;
-    const int tiles = sym ? tiles_n * (tiles_n + 1) / 2 : (J.M / 64) * tiles_n;
+    const int tiles = J.tiles;
     const int z = (bx - J.first) / tiles, tile = bx - J.first - z * tiles;
     int tm, tn;
-    decode_tile(tile, tiles_n, sym, tm, tn);
+    if (sym == 2) {
+        decode_tile(tile >> 2, tiles_n / 2, 1, tm, tn);
+        tm = 2 * tm + (tile >> 1 & 1);
+        tn = 2 * tn + (tile & 1);
+    } else {
+        decode_tile(tile, tiles_n, sym, tm, tn);
+    }
     const int m0 = 64 * tm, n0 = 64 * tn;
     const half_t* A = J.a + (int64_t)z * J.a_stride;
     const half_t* Bm = J.b + (int64_t)z * J.b_stride;
@@ -905,7 +911,7 @@ __global__ void __launch_bounds__(256, 2) small_jobs_kernel(SmallJobs p) {
     else if (J.layout == 1) small_tile<1>(A, J.lda, Bm, J.ldb, m0, n0, J.K, smem, acc);
     else small_tile<2>(A, J.lda, Bm, J.ldb, m0, n0, J.K, smem, acc);
     const float ca = j_ca * mul, cs = j_cs * mul;
-    const bool mirror = sym && tm != tn;
+    const bool mirror = sym == 2 ? tm >> 1 != tn >> 1 : sym && tm != tn;
     float ss = 0.f;
     typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -1143,10 +1149,12 @@ hipError_t launch_small_jobs(SmallJobs& j, hipStream_t s) {
         SmallJob& p = j.job[i];
         const int64_t tm = p.M / 64, tn = p.N / 64;
         if (j.zbeg[i + 1] <= j.zbeg[i] || p.M < 64 || p.N < 64 || p.K < BK || p.M % 64 || p.N % 64 || p.K % BK ||
-            p.layout < 0 || p.layout > 2 || (p.sym && (tm != tn || p.sumsq)))
+            p.layout < 0 || p.layout > 2 || p.sym < 0 || p.sym > 2 || (p.sym && (tm != tn || p.sumsq)) ||
+            (p.sym == 2 && tn % 2))
             return hipErrorInvalidValue;
         p.first = (int)blocks;
-        blocks += (p.sym ? tn * (tn + 1) / 2 : tm * tn) * (j.zbeg[i + 1] - j.zbeg[i]);
+        p.tiles = small_tile_count(p.M, p.N, p.sym);
+        blocks += (int64_t)p.tiles * (j.zbeg[i + 1] - j.zbeg[i]);
         if (blocks > (1 << 30)) return hipErrorInvalidValue;
         j.tend[i] = (int)blocks;
     }

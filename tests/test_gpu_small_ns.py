@@ -72,3 +72,20 @@ def test_small_item_stays_with_its_pool(ctx, small, tiled, own):
         count.append(sum(N.normpre_kernel_stats(ctx, c)["launches"] for c in classes))
     print(f"Newton-Schulz launches {small} beside {tiled[0]}: {count}", flush=True)
     assert count[1] - count[0] <= own
+
+
+# The grouped launches compute what the tiled ones do, bit by bit (the Muon
+# step has no sum of its output): a matrix alone, and beside large ones of its
+# pool, with which it takes the tiled launches.
+@pytest.mark.parametrize("shape", [(100, 300), (129, 300), (300, 330), (512, 2048), (2048, 300), (768, 2000)])
+def test_grouped_equals_tiled(ctx, shape):
+    print(f"grouped against tiled {shape}", flush=True)
+    wl = WL.Workload("t", 91, [shape], "lowrank", 1.0, rank=8)
+    mat = [x.cuda() for x in WL.make_matrix(wl, 0, "cpu", shape=shape)]
+    s = (min(shape) + 255) // 256 * 256
+    out = []
+    for beside in ([], [(s, 16384)] * 6):
+        Ws, Gs, Ms = ([x.clone()] + [torch.randn(b, device="cuda") for b in beside] for x in mat)
+        N.normpre_step(ctx, N.NORMPRE_VARIANT_MUON, Ws, Gs, Ms, N.normpre_default_hparams(lr=1.0, weight_decay=0.0))
+        out.append(Ws[0].cpu())
+    assert torch.equal(out[0], out[1])
