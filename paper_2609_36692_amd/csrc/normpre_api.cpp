@@ -684,11 +684,11 @@ size_t carve_round(Arena& ar, std::vector<Item>& items, std::vector<Pool>& pools
 // kSmallFlops nominal FLOPs per iteration (4 s^2 L + 2 s^3 of the padded sizes)
 // and within 256 + 256 tiles per item (1536 per Gram-space item, whose s x s
 // products have far fewer tiles than its combines).  NormPre-G steps in us,
-// launches per pool and item against grouped ones: one 256^2 matrix 123 / 109, one
-// 1024^2 216 / 184, one 1280^2 (400 tiles) 255 / 219, eight of 512^2 (512 tiles)
-// 161 / 154, four of 768^2 (576 tiles) 199 / 220; Gram-space: one 512 x 2048 214 /
-// 161, four of 256 x 8192 301 / 239, two of 1024 x 2048 303 / 298, eight of
-// 512 x 2048 (2048 tiles) 263 / 259; five shapes of three matrices 596 / 254.
+// launches per pool and item against grouped ones: one 256^2 matrix 121 / 103, one
+// 1024^2 214 / 180, one 1280^2 (400 tiles) 253 / 214, eight of 512^2 (512 tiles)
+// 160 / 146, four of 768^2 (576 tiles) 198 / 208; Gram-space: one 512 x 2048 215 /
+// 160, four of 256 x 8192 301 / 233, two of 1024 x 2048 295 / 281, eight of
+// 512 x 2048 (2048 tiles) 258 / 247; five shapes of three matrices 755 / 432.
 // An item stays with its pool (equal padded s) unless all of the pool is grouped:
 // the pool's launches take it along for little or nothing, a chain of its own
 // runs before them.  Beside the rest of the pool, grouped / with the pool: 512^2

@@ -801,8 +801,8 @@ gemm_kernel(Operand A, Operand B, GemmShape sh, Epi epi) {
 // layout: the products of a stage of all small matrices of a step are one
 // launch, since at these sizes a launch costs more (5 to 8 us each in a chain of
 // dependent launches) than its products, and 64-wide tiles give a 256 x 256
-// matrix sixteen CUs.  Bound by the chain of launches: 5.9 us each at 256 x 256
-// (the fifteen of five iterations 88 us; with 128-wide tiles 98).  Operands are
+// matrix sixteen CUs.  Bound by the chain of launches: 5.7 us each at 256 x 256
+// (the fifteen of five iterations 85 us; with 128-wide tiles 98).  Operands are
 // staged as in gemm_kernel (two LDS stages, global loads three K-steps ahead);
 // results are stored from the accumulators.
 template <int LAYOUT>
